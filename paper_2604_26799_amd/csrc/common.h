@@ -53,13 +53,18 @@ __device__ __forceinline__ double dpp_f64(double v) {
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xF, true);
     return __hiloint2double(hi, lo);
 }
-__device__ __forceinline__ double wave_total_f64(double v) {
+// wave_sum63_*: the total in lane 63 only (other lanes hold partial sums).
+__device__ __forceinline__ double wave_sum63_f64(double v) {
     v += dpp_f64<0x111, 0xF>(v);  // row_shr:1   (inclusive prefix within rows of 16)
     v += dpp_f64<0x112, 0xF>(v);  // row_shr:2
     v += dpp_f64<0x114, 0xF>(v);  // row_shr:4
     v += dpp_f64<0x118, 0xF>(v);  // row_shr:8   -> lane 15 of each row: row sum
     v += dpp_f64<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
     v += dpp_f64<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3 -> lane 63: total
+    return v;
+}
+__device__ __forceinline__ double wave_total_f64(double v) {
+    v = wave_sum63_f64(v);
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
     return __hiloint2double(hi, lo);
@@ -70,14 +75,14 @@ template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ float dpp_f32(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xF, true));
 }
-__device__ __forceinline__ float wave_total_f32(float v) {
+__device__ __forceinline__ float wave_sum63_f32(float v) {
     v += dpp_f32<0x111, 0xF>(v);
     v += dpp_f32<0x112, 0xF>(v);
     v += dpp_f32<0x114, 0xF>(v);
     v += dpp_f32<0x118, 0xF>(v);
     v += dpp_f32<0x142, 0xA>(v);
     v += dpp_f32<0x143, 0xC>(v);
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+    return v;
 }
 __device__ __forceinline__ uint32_t wave_or_u32(uint32_t v) {
 #pragma unroll

@@ -112,6 +112,7 @@ int device_cus();
 int variant_count();
 Shape variant_shape(int i);
 bool variant_chunked(int i);
+bool variant_used(int i, int G);  // the variant that shape (nt, ept) stands for at group size G
 
 // Autotune registry: the shape chosen for (G, nb, bmax), if any.
 bool tuned_shape(int G, int nb, int bmax, Shape* out);

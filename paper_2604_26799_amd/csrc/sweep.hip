@@ -100,16 +100,22 @@ __device__ __forceinline__ double grid_round(double v, int K) {
 // paths, values scaled by 2^-E, so the terms stay far from FP32 overflow and
 // underflow) or in FP64 (literal-division and underflowed-step paths), and
 // the entropy increments (FP64, exact grid sum).
+// SUB: a thread may stand for SUB threads of a workgroup SUB times as wide,
+// with one loss sum for each (element i belongs to thread (i % SUB) * NT + tid
+// of the wide workgroup), so that both shapes add the same terms in the same
+// order.
+template <int SUB>
 struct Part {
-    float err;
-    double err64;
+    float err[SUB];
+    double err64[SUB];
     double ent;
 };
 
 // Entropy increment of one more element in a bin whose counter read c
 // before (the low 8 bits index the LDS table; the caller tracks larger
 // counts for the correction scan).
-__device__ __forceinline__ void add_increment(uint32_t c, const double* lf, Part& acc) {
+template <int SUB>
+__device__ __forceinline__ void add_increment(uint32_t c, const double* lf, Part<SUB>& acc) {
     acc.ent += lf[c & (uint32_t)(LGTAB - 1)];
 }
 
@@ -160,19 +166,22 @@ __device__ __forceinline__ uint32_t lds_add(uint32_t addr, uint32_t v) {
 // pass; elements past the ragged end carry w = 0 and x = 0, so they add
 // nothing to the loss.
 // Returns the OR of the counters the pass read (RTN) in `seen`.
-template <int NT, int EPT, bool PACKED, bool CHECK, bool RTN, bool REPL, bool WIN, bool ERR>
-__device__ __forceinline__ Part eval_fast(const float (&u)[EPT], const float (&xv)[EPT],
+template <int NT, int EPT, int SUB, bool PACKED, bool CHECK, bool RTN, bool REPL, bool WIN, bool ERR>
+__device__ __forceinline__ Part<SUB> eval_fast(const float (&u)[EPT], const float (&xv)[EPT],
                                           const float (&wv)[EPT], int n, int tid, float P, float Ss,
                                           float Z, uint32_t cadj, uint32_t wlo, uint32_t wbytes, int rl,
                                           const double* lf, uint32_t& seen) {
     const float M = 8388608.0f;  // 2^23
     const float MZ = M + Z;
     const float hi = M + (P - 1.0f);
+    // (opaque: the ragged masks are made afresh in every pass, rather than held
+    // in scalar registers across all of them)
+    if (CHECK) asm volatile("" : "+s"(n));
     const uint32_t shl = REPL ? (uint32_t)rl + 2u : 2u;
-    Part acc{0.0f, 0.0, 0.0};
+    Part<SUB> acc{};
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-        const bool valid = !CHECK || i * NT + tid < n;
+        const bool valid = !CHECK || tid < n - i * NT;
         if (!WIN && !valid) continue;
         float t = __builtin_fmaf(u[i], P, Z);
         float tm = __builtin_amdgcn_fmed3f(t + M, M, hi);
@@ -195,7 +204,10 @@ __device__ __forceinline__ Part eval_fast(const float (&u)[EPT], const float (&x
         if (ERR) {
             float xh = (tm - MZ) * Ss;
             float d = xh - xv[i];
-            acc.err = __builtin_fmaf(wv[i], d * d, acc.err);
+            acc.err[i % SUB] = __builtin_fmaf(wv[i], d * d, acc.err[i % SUB]);
+            // (windows: one element at a time, so that the rounded values do not
+            // all wait in registers behind the masked atomics)
+            if (WIN) asm volatile("" : "+v"(acc.err[i % SUB]));
         }
     }
     return acc;
@@ -204,17 +216,17 @@ __device__ __forceinline__ Part eval_fast(const float (&u)[EPT], const float (&x
 // The same pass for the rare cases, with runtime switches: |Z| > 2^23 (rint
 // path) or the literal division per element, bins possibly in windows.
 // Literal tiles are never scaled (E = 0, Ss = S) and keep the loss in FP64.
-template <int NT, int EPT>
-__device__ __forceinline__ Part eval_generic(const float (&u)[EPT], const float (&xv)[EPT],
+template <int NT, int EPT, int SUB>
+__device__ __forceinline__ Part<SUB> eval_generic(const float (&u)[EPT], const float (&xv)[EPT],
                                              const float (&wv)[EPT], int n, int tid, float P, float S,
                                              float Ss, float Z, uint32_t* hist, int base, int lo,
                                              int nwords, bool packed, int rl, int cpy, bool literal,
                                              bool err, bool rtn, const double* lf, uint32_t& seen) {
     const float qmax = P - 1.0f;
-    Part acc{0.0f, 0.0, 0.0};
+    Part<SUB> acc{};
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-        if (i * NT + tid >= n) continue;
+        if (tid >= n - i * NT) continue;
         float t;
         if (literal) {
             t = xv[i] / S;
@@ -238,10 +250,10 @@ __device__ __forceinline__ Part eval_generic(const float (&u)[EPT], const float 
             float xh = (q - Z) * Ss;
             if (literal) {
                 double d = (double)xh - as_f64(xv[i]);
-                acc.err64 = __builtin_fma(as_f64(wv[i]), d * d, acc.err64);
+                acc.err64[i % SUB] = __builtin_fma(as_f64(wv[i]), d * d, acc.err64[i % SUB]);
             } else {
                 float d = xh - xv[i];
-                acc.err = __builtin_fmaf(wv[i], d * d, acc.err);
+                acc.err[i % SUB] = __builtin_fmaf(wv[i], d * d, acc.err[i % SUB]);
             }
         }
     }
@@ -251,31 +263,33 @@ __device__ __forceinline__ Part eval_generic(const float (&u)[EPT], const float 
 // FP64 loss of one non-literal pass, recomputed from the registers (the same
 // codes and FP32 dequantized values as the pass, exact FP64 differences);
 // used when the FP32 sum of a wavefront cannot be trusted.
-template <int NT, int EPT>
+template <int NT, int EPT, int SUB>
 __device__ __forceinline__ double loss_f64(const float (&u)[EPT], const float (&xv)[EPT],
                                         const float (&wv)[EPT], int n, int tid, float P, float Ss,
-                                        float Z) {
+                                        float Z, int sub) {
     const float qmax = P - 1.0f;
     double e = 0.0;
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-        if (i * NT + tid >= n) continue;
+        if (SUB > 1 && i % SUB != sub) continue;
+        if (tid >= n - i * NT) continue;
         float t = __builtin_amdgcn_fmed3f(__builtin_fmaf(u[i], P, Z), 0.0f, qmax);
         float xh = (__builtin_rintf(t) - Z) * Ss;
         double d = (double)xh - (double)xv[i];
         e = __builtin_fma((double)wv[i], d * d, e);
+        asm volatile("" : "+v"(e));  // one element at a time (a rare path: no registers for it)
     }
     return e;
 }
 
-template <int NT, int EPT, bool PACKED>
-__device__ __forceinline__ Part eval_fast_dispatch(bool check, bool rtn, bool win, bool err,
+template <int NT, int EPT, int SUB, bool PACKED>
+__device__ __forceinline__ Part<SUB> eval_fast_dispatch(bool check, bool rtn, bool win, bool err,
                                                    uint32_t cadj, uint32_t wlo, uint32_t wbytes, int rl,
                                                    const float (&u)[EPT], const float (&xv)[EPT],
                                                    const float (&wv)[EPT], int n, int tid, float P,
                                                    float Ss, float Z, const double* lf, uint32_t& seen) {
 #define MGS_EVAL(CHK, RT, RP, WN, ER)                                                              \
-    eval_fast<NT, EPT, PACKED, CHK, RT, RP, WN, ER>(u, xv, wv, n, tid, P, Ss, Z, cadj, wlo, wbytes, \
+    eval_fast<NT, EPT, SUB, PACKED, CHK, RT, RP, WN, ER>(u, xv, wv, n, tid, P, Ss, Z, cadj, wlo, wbytes, \
                                                     rl, lf, seen)
     if constexpr (PACKED) {
         // bin windows only occur on packed histograms; the loss is summed in
@@ -320,35 +334,66 @@ __device__ __forceinline__ uint32_t group_sum_u32(uint32_t v, int rl) {
     return v;
 }
 
-// Wavefront min / max / OR by DPP row shifts and row broadcasts (lanes whose
-// source lies outside the row, or rows the mask leaves out, take the
-// identity); the result is read from lane 63, so every lane gets it.
+// Wavefront minimum / maximum by DPP row shifts and row broadcasts (lanes
+// whose source lies outside the row, or rows the mask leaves out, take the
+// identity); lane 63 ends with the result.  Floats are compared through
+// integers that order alike (the sign-magnitude bits folded to two's
+// complement): the float instructions would first quiet every operand, one
+// more instruction per step, and an integer step folds into one DPP
+// instruction.
 template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint32_t dpp_keep(uint32_t v, uint32_t ident) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)ident, (int)v, CTRL, ROW_MASK, 0xF, false);
+__device__ __forceinline__ int dpp_keep(int v, int ident) {
+    return __builtin_amdgcn_update_dpp(ident, v, CTRL, ROW_MASK, 0xF, false);
 }
 template <typename F>
-__device__ __forceinline__ uint32_t wave_reduce_dpp(uint32_t v, uint32_t ident, F op) {
+__device__ __forceinline__ int wave_reduce63(int v, int ident, F op) {
     v = op(v, dpp_keep<0x111, 0xF>(v, ident));
     v = op(v, dpp_keep<0x112, 0xF>(v, ident));
     v = op(v, dpp_keep<0x114, 0xF>(v, ident));
     v = op(v, dpp_keep<0x118, 0xF>(v, ident));
     v = op(v, dpp_keep<0x142, 0xA>(v, ident));
     v = op(v, dpp_keep<0x143, 0xC>(v, ident));
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    return v;
 }
-__device__ __forceinline__ float wave_min_dpp(float v) {
-    return __uint_as_float(wave_reduce_dpp(__float_as_uint(v), __float_as_uint(INFINITY), [](uint32_t a, uint32_t b) {
-        return __float_as_uint(fminf(__uint_as_float(a), __uint_as_float(b)));
-    }));
+__device__ __forceinline__ int ordered_bits(float v) {
+    const int b = __float_as_int(v);
+    return b ^ ((b >> 31) & 0x7fffffff);
 }
-__device__ __forceinline__ float wave_max_dpp(float v) {
-    return __uint_as_float(wave_reduce_dpp(__float_as_uint(v), __float_as_uint(-INFINITY), [](uint32_t a, uint32_t b) {
-        return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
-    }));
+__device__ __forceinline__ float from_ordered(int k) {
+    return __int_as_float(k ^ ((k >> 31) & 0x7fffffff));
 }
-__device__ __forceinline__ uint32_t wave_or_dpp(uint32_t v) {
-    return wave_reduce_dpp(v, 0u, [](uint32_t a, uint32_t b) { return a | b; });
+__device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
+__device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
+__device__ __forceinline__ int wave_imin63(int v) { return wave_reduce63(v, 0x7fffffff, imin); }
+__device__ __forceinline__ int wave_imax63(int v) { return wave_reduce63(v, (int)0x80000000, imax); }
+// The same over NW values that the lanes hold repeatedly, lane l the
+// (l mod NW)-th (NW = 4, 8 or 16: rotations within rows of 16 lanes); the
+// result as a scalar.
+template <int NW, typename F>
+__device__ __forceinline__ int reduce_row(int v, F op) {
+    static_assert(NW == 4 || NW == 8 || NW == 16, "wavefronts of a workgroup");
+    if (NW >= 16) v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true));
+    if (NW >= 8) v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true));
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, true));
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, true));
+    return __builtin_amdgcn_readfirstlane(v);
+}
+__device__ __forceinline__ uint32_t wave_umax63(uint32_t v) {
+    return (uint32_t)wave_reduce63((int)v, 0, [](int a, int b) {
+        return (int)((uint32_t)a > (uint32_t)b ? (uint32_t)a : (uint32_t)b);
+    });
+}
+// Smallest / largest of three values that are not NaN (one instruction; the
+// library functions first quiet every operand).
+__device__ __forceinline__ float min3_raw(float a, float b, float c) {
+    float r;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ float max3_raw(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 
 // Waves per SIMD the register budget must allow: <= 128 VGPRs for shapes
@@ -357,18 +402,31 @@ __device__ __forceinline__ uint32_t wave_or_dpp(uint32_t v) {
 template <int NT, int EPT, bool CHUNKED>
 constexpr int sweep_min_waves() { return (EPT <= 16 && !CHUNKED) ? 4 : 1; }
 
-template <int NT, int EPT, bool CHUNKED>
+// What bounds it: VALU issue (three quarters of the kernel with 17.9 lane
+// slots per evaluation, 9 of them the pass itself on scanned histograms; the
+// rest is each channel's gather, minimum / maximum and quotients, and each
+// wavefront's reductions per bit-width).  So the work outside the passes is
+// kept short: values are gathered by 32-bit byte offset from a scalar row base,
+// elements past a ragged end repeat the last one instead of being masked, one
+// instruction takes two elements' minimum, maximum or NaN check, weights are
+// checked once per tile, wavefront minima go through DPP steps on ordered
+// integers, the bit-widths' parameters sit in the lanes of every wavefront
+// (no barrier and no LDS round trip before the passes), and the loss totals
+// are rescaled only in the table entry.  One-workgroup-per-tile launches, before
+// and after: 5.3e6 x 20, 32 ratios, G = 16384, b = 1..16 16.2 -> 15.2 ms;
+// 1e6 x 20, 16 ratios, b = 2..16, G = 8192 2.69 -> 2.39 ms.
+template <int NT, int EPT, bool CHUNKED, int SUB>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sweep_min_waves<NT, EPT, CHUNKED>())))
 void sweep_kernel(SweepParams p) {
     constexpr int NW = NT / MGS_WAVE;
     extern __shared__ __align__(16) uint32_t hist[];  // 16-byte aligned: cleared and read as uint4
     __shared__ double lg[LGTAB];
     __shared__ double lf[LGTAB];
-    __shared__ double errpart[MGS_MAX_BITS][NW];
+    __shared__ double errpart[MGS_MAX_BITS][NW * SUB];
     __shared__ double bitpart[MGS_MAX_BITS][NW];
-    __shared__ float red_mn[NW], red_mx[NW], red_w[NW];
-    __shared__ uint32_t red_bad[NW];
-    __shared__ float prmS[MGS_MAX_BITS], prmZ[MGS_MAX_BITS];
+    __shared__ int red_mn[NW], red_mx[NW];  // ordered bits of each wavefront's minimum and maximum
+    __shared__ int red_w[NW];        // bits of the largest |weight| (integers order non-negative floats, NaN last)
+    __shared__ uint32_t chan_bad;    // some value of the channel is NaN; reset behind the first batch's barrier
     __shared__ uint32_t ovf_flag[MGS_MAX_ENTRIES];  // per batch: some bin passed the LDS increment table
 
     const int tid = threadIdx.x;
@@ -384,6 +442,13 @@ void sweep_kernel(SweepParams p) {
         lg[h] = h <= p.lgtab_max ? lgt[h] : 0.0;
         lf[h] = h <= p.lgtab_max ? lft[h] : 0.0;
     }
+    // cleared here once, then by each channel behind its own barriers
+    for (int i = tid; i < MGS_MAX_BITS * NW; i += NT) (&bitpart[0][0])[i] = 0.0;
+    if (CHUNKED)
+        for (int i = tid; i < MGS_MAX_BITS * NW * SUB; i += NT) (&errpart[0][0])[i] = 0.0;
+    for (int i = tid; i < MGS_MAX_ENTRIES; i += NT) ovf_flag[i] = 0u;
+    if (tid == 0) chan_bad = 0u;
+    __syncthreads();
     // grid value of T(LGTAB), what one full cycle of the LDS increments adds
     // up to (only counts above LGTAB need it)
     const double rt_cycle = p.lgtab_max >= LGTAB ? grid_round(lgt[LGTAB], p.kgrid) : 0.0;
@@ -406,31 +471,49 @@ void sweep_kernel(SweepParams p) {
     }
     __shared__ int64_t grabbed;
     const int qx0 = (int)(blockIdx.x % MGS_XCDS);
-    int qk = 0;
+    uint32_t live = (1u << MGS_XCDS) - 1u;  // (wavefront 0) runs not known to be drained, own run first
     for (int64_t it = it0 - step;;) {
         if (p.persist) {
-            bool got = false;
-            while (qk < MGS_XCDS) {
-                const int x = (qx0 + qk) % MGS_XCDS;
-                const int64_t hi = min(p.ntiles, (int64_t)(x + 1) * per);
-                if (tid == 0)
-                    grabbed = (int64_t)x * per +
-                              (int64_t)__hip_atomic_fetch_add(&p.status->queue[x], 1u, __ATOMIC_RELAXED,
-                                                              __HIP_MEMORY_SCOPE_AGENT);
-                __syncthreads();
-                {  // the same value in every lane: keep it (and all that derives from it) scalar
-                    const int64_t g = grabbed;
-                    it = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(g >> 32)) << 32) |
-                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)g));
+            // Wavefront 0 takes the next tile: from its own XCD's counter
+            // until that run is drained, then from the first other run whose
+            // counter, all of them read at once, is still below its end (one
+            // after the other, the seven drained counters cost every workgroup
+            // a chain of as many atomics at the end of a launch).  A counter
+            // that turns out drained is not tried again, so this ends after
+            // at most one failed attempt per run.
+            if (wave == 0) {
+                auto run_len = [&](int x) {
+                    return max((int64_t)0, min(p.ntiles, (int64_t)(x + 1) * per) - (int64_t)x * per);
+                };
+                int64_t got = -1;
+                while (live && got < 0) {
+                    if (!(live & 1u)) {
+                        const int x = (qx0 + lane) % MGS_XCDS;
+                        const uint32_t q = __hip_atomic_load(&p.status->queue[x], __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT);
+                        live &= (uint32_t)__builtin_amdgcn_ballot_w64(lane < MGS_XCDS && (int64_t)q < run_len(x));
+                        if (!live) break;
+                    }
+                    const int l = __builtin_ctz(live);
+                    const int x = (qx0 + l) % MGS_XCDS;
+                    uint32_t v = 0;
+                    if (lane == 0)
+                        v = __hip_atomic_fetch_add(&p.status->queue[x], 1u, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                    v = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+                    if ((int64_t)v < run_len(x)) got = (int64_t)x * per + v;
+                    else live &= ~(1u << l);
                 }
-                __syncthreads();  // every thread has read it before the next grab
-                if (it < hi) {
-                    got = true;
-                    break;
-                }
-                ++qk;
+                if (lane == 0) grabbed = got;
             }
-            if (!got) break;
+            __syncthreads();
+            {  // the same value in every lane: keep it (and all that derives from it) scalar
+                const int64_t g = grabbed;
+                it = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(g >> 32)) << 32) |
+                               (uint32_t)__builtin_amdgcn_readfirstlane((int)g));
+            }
+            __syncthreads();  // every thread has read it before the next grab
+            if (it < 0) break;
         } else {
             it += step;
             if (it >= it_end) break;
@@ -498,7 +581,7 @@ void sweep_kernel(SweepParams p) {
         const int n = (int)(krem < sc->G ? krem : sc->G);
         const int32_t* J = sc->kept + sc->koff[t] + j0;
         const int nb = sc->nb;
-        const int my_bl = tid < nb ? (int)sc->bl[tid] : 0;  // this thread's bit-width (tid < nb)
+        const int my_bl = lane < nb ? (int)sc->bl[lane] : 1;  // lane l: the list's l-th bit-width
 
         // ---- per-element state in registers.  The kept indices and the
         // weights are the same for every channel of the tile: they are
@@ -509,14 +592,28 @@ void sweep_kernel(SweepParams p) {
         constexpr int CAP = NT * EPT;
         const int nchunk = CHUNKED ? (n + CAP - 1) / CAP : 1;
         float u[EPT], xv[EPT], wv[EPT];
-        int32_t ids[CHUNKED ? 1 : EPT];
+        // Elements past a ragged end repeat the group's last one (its minimum,
+        // maximum and NaN check need no masks then) with weight 0; the passes
+        // leave them out.  `ids` holds the byte offset of the element in its
+        // row while 32 bits can (rows of up to 2^30 floats: one load per value
+        // with a scalar base and no address arithmetic), else the index.
+        uint32_t ids[CHUNKED ? 1 : EPT];
+        const bool near_row = sc->ld <= ((int64_t)1 << 30);
+        float wthr = 0.0f;  // FP32 loss totals below this are recomputed; NaN: some weight is not finite
 
         const float* imp = sc->imp;
         if constexpr (!CHUNKED) {
 #pragma unroll
-            for (int i = 0; i < EPT; ++i) ids[i] = i * NT + tid < n ? J[i * NT + tid] : 0;
+            for (int i = 0; i < EPT; ++i) ids[i] = (uint32_t)J[min(i * NT + tid, n - 1)];
+            uint32_t wmax = 0;
 #pragma unroll
-            for (int i = 0; i < EPT; ++i) wv[i] = i * NT + tid < n ? imp[ids[i]] : 0.0f;
+            for (int i = 0; i < EPT; ++i) {
+                wv[i] = tid < n - i * NT ? imp[ids[i]] : 0.0f;
+                wmax = max(wmax, __float_as_uint(wv[i]) & 0x7fffffffu);
+                if (near_row) ids[i] <<= 2;
+            }
+            wmax = wave_umax63(wmax);
+            if (lane == 63) red_w[wave] = (int)wmax;  // read behind the first channel's barrier
         }
         // the first batch's bins are cleared before the barrier of the
         // channel's min/max (the later batches clear their own)
@@ -535,8 +632,9 @@ void sweep_kernel(SweepParams p) {
             clear_batch(0);
             const float* row = sc->attr + (int64_t)c * sc->ld;
             const int64_t slot = ((int64_t)t * sc->C + c) * sc->gmaxn + g;
-            float mn = INFINITY, mx = -INFINITY, wm = 0.0f;  // wm: largest |weight|
-            uint32_t bad = 0;
+            float mn = INFINITY, mx = -INFINITY;
+            uint64_t nan_seen = 0;  // lanes that hold a NaN
+            uint32_t wmax = 0;      // (chunked groups: their weights come in with every channel)
             auto gather = [&](int ch) {
                 // Opaque copies of the index and weight pointers: otherwise
                 // their loads are hoisted out of the channel loop and held in
@@ -554,11 +652,11 @@ void sweep_kernel(SweepParams p) {
                         int32_t id = Jc[j];
                         x = rowg[id];
                         w = impc[id];
-                        bad |= (uint32_t)(!finite_f32(x) || !finite_f32(w));
                         mn = fminf(mn, x);
                         mx = fmaxf(mx, x);
-                        wm = fmaxf(wm, fabsf(w));
+                        wmax = max(wmax, __float_as_uint(w) & 0x7fffffffu);
                     }
+                    nan_seen |= __builtin_amdgcn_ballot_w64(__builtin_isnan(x));
                     xv[i] = x;
                     wv[i] = w;
                 }
@@ -566,55 +664,60 @@ void sweep_kernel(SweepParams p) {
             if constexpr (CHUNKED) {
                 for (int ch = nchunk - 1; ch >= 0; --ch) gather(ch);  // ends holding chunk 0
             } else {
-                // every load issued before the first is used: elements past n
-                // hold index 0, an in-bounds read of row[0] that is dropped.
-                // The opaque copy keeps each index a 32-bit register (a 64-bit
-                // offset per element held across channels costs registers).
-                const global_ptr<const float> rowg = (global_ptr<const float>)row;
+                // every load issued before the first is used; the opaque copy
+                // keeps each offset a 32-bit register
+                if (near_row) {
+                    const global_ptr<const char> rowb = (global_ptr<const char>)row;
 #pragma unroll
-                for (int i = 0; i < EPT; ++i) {
-                    int32_t id = ids[i];
-                    asm volatile("" : "+v"(id));
-                    xv[i] = rowg[id];
-                }
-#pragma unroll
-                for (int i = 0; i < EPT; ++i) {
-                    float x = 0.0f;
-                    if (i * NT + tid < n) {
-                        x = xv[i];
-                        const float w = wv[i];
-                        bad |= (uint32_t)(!finite_f32(x) || !finite_f32(w));
-                        mn = fminf(mn, x);
-                        mx = fmaxf(mx, x);
-                        wm = fmaxf(wm, fabsf(w));
+                    for (int i = 0; i < EPT; ++i) {
+                        uint32_t off = ids[i];
+                        asm volatile("" : "+v"(off));
+                        xv[i] = *(global_ptr<const float>)(rowb + off);
                     }
-                    xv[i] = x;
+                } else {
+                    const global_ptr<const float> rowg = (global_ptr<const float>)row;
+#pragma unroll
+                    for (int i = 0; i < EPT; ++i) {
+                        uint32_t id = ids[i];
+                        asm volatile("" : "+v"(id));
+                        xv[i] = rowg[id];
+                    }
+                }
+                // two elements per instruction each: minimum, maximum, NaN check
+#pragma unroll
+                for (int i = 0; i < EPT; i += 2) {
+                    const float xa = xv[i], xb = xv[i + 1 < EPT ? i + 1 : i];
+                    mn = min3_raw(mn, xa, xb);
+                    mx = max3_raw(mx, xa, xb);
+                    nan_seen |= __builtin_amdgcn_ballot_w64(__builtin_isunordered(xa, xb));
+                }
+                if (nan_seen) {  // rare: the group's bounds are those of its other values
+                    mn = INFINITY;
+                    mx = -INFINITY;
+#pragma unroll
+                    for (int i = 0; i < EPT; ++i) {
+                        mn = fminf(mn, xv[i]);
+                        mx = fmaxf(mx, xv[i]);
+                    }
                 }
             }
-            mn = wave_min_dpp(mn);
-            mx = wave_max_dpp(mx);
-            wm = wave_max_dpp(wm);
-            bad = wave_or_dpp(bad);
-            if (lane == 0) {
-                red_mn[wave] = mn;
-                red_mx[wave] = mx;
-                red_w[wave] = wm;
-                red_bad[wave] = bad;
+            const int kmn = wave_imin63(ordered_bits(mn)), kmx = wave_imax63(ordered_bits(mx));
+            if (CHUNKED) wmax = wave_umax63(wmax);
+            if (lane == 63) {
+                red_mn[wave] = kmn;
+                red_mx[wave] = kmx;
+                if (CHUNKED) red_w[wave] = (int)wmax;
+                if (nan_seen) chan_bad = 1u;
             }
             __syncthreads();
-            mn = red_mn[0];
-            mx = red_mx[0];
-            wm = red_w[0];
-            bad = red_bad[0];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) {
-                mn = fminf(mn, red_mn[w]);
-                mx = fmaxf(mx, red_mx[w]);
-                wm = fmaxf(wm, red_w[w]);
-                bad |= red_bad[w];
+            mn = from_ordered(reduce_row<NW>(red_mn[lane & (NW - 1)], imin));
+            mx = from_ordered(reduce_row<NW>(red_mx[lane & (NW - 1)], imax));
+            if (CHUNKED || c == c0) {
+                const float wf = __int_as_float(reduce_row<NW>(red_w[lane & (NW - 1)], imax));
+                wthr = finite_f32(wf) ? (wf + 1.0f) * 0x1p-112f : NAN;
             }
             const float R = mx - mn;
-            if (!finite_f32(R)) bad = 1;
+            const bool bad = chan_bad != 0u || !finite_f32(R) || __builtin_isnan(wthr);
             if (tid == 0) {
                 sc->gmin[slot] = mn;
                 sc->gmax[slot] = mx;
@@ -629,35 +732,33 @@ void sweep_kernel(SweepParams p) {
                 }
                 if (bad && tid == 0) atomicOr(&p.status->nonfinite, 1u);
                 __syncthreads();
+                if (tid == 0) chan_bad = 0u;
+                __syncthreads();
                 continue;
             }
 
-            // ---- per-b scale and zero point (literal FP32 definition)
-            if (tid < nb) {
-                float P = ldexpf(1.0f, my_bl);
-                float S = R / P;
-                float Z = 0.0f;
-                if (S != 0.0f) {
-                    float r = mx / S;
-                    Z = __builtin_rintf(P - r);
-                }
-                int t0 = tid;
-                asm volatile("" : "+v"(t0));
-                prmS[t0] = S;
-                prmZ[t0] = Z;
+            // ---- per-b scale and zero point (literal FP32 definition), lane l
+            // of every wavefront for the list's l-th bit-width: the passes read
+            // them from there as scalars, without a barrier or an LDS round trip
+            const float my_P = __uint_as_float((uint32_t)(127 + my_bl) << 23);
+            const float my_S = R / my_P;
+            float my_Z = 0.0f;
+            if (my_S != 0.0f) {
+                float r = mx / my_S;
+                my_Z = __builtin_rintf(my_P - r);
             }
+            const uint64_t zero_S = __builtin_amdgcn_ballot_w64(my_S == 0.0f);
             // a range that underflows at some b (S_b = 0; S only shrinks with b)
             const bool anyzero = R / ldexpf(1.0f, sc->bmax) == 0.0f;
-            for (int i = tid; i < MGS_MAX_BITS * NW; i += NT) {
-                (&bitpart[0][0])[i] = 0.0;
-                (&errpart[0][0])[i] = 0.0;
-            }
             const bool fast = R >= ldexpf(1.0f, sc->bmax - 126);
+            // bit-widths of the fast path
+            const uint64_t fast_Z =
+                fast ? __builtin_amdgcn_ballot_w64(my_S != 0.0f && fabsf(my_Z) <= 8388608.0f) : 0ull;
             // Fast tiles evaluate the loss on x * 2^-E with 2^E <= R < 2^(E+1)
             // (R is normal here): every step S_b * 2^-E is then normal and near
             // 2^-b, and the terms are rescaled by 2^(2E) in FP64.
             const int E = fast ? (int)((__float_as_uint(R) >> 23) & 0xFFu) - 127 : 0;
-            const double esc = ldexp(1.0, 2 * E);
+            const float my_Ss = ldexpf(my_S, -E);
             // u = x / R, correctly rounded, without a division per element:
             // with Rs = R * 2^-E in [1, 2) and y = RN(1 / Rs), q = RN(xs * y)
             // is within 1.5 ulp of xs / Rs; one correction by the exact FMA
@@ -689,8 +790,6 @@ void sweep_kernel(SweepParams p) {
                 }
             };
             quotients();
-            for (int i = tid; i < p.nbatches; i += NT) ovf_flag[i] = 0u;
-            __syncthreads();
 
             // ---- histogram batches
             for (int bt = 0; bt < p.nbatches; ++bt) {
@@ -712,28 +811,28 @@ void sweep_kernel(SweepParams p) {
                     for (int e = e0; e < e1; ++e) {
                         const HistEntry en = p.entries[e];
                         const int bi = en.bi;
-                        const float S = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(prmS[bi])));
-                        const float Z = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(prmZ[bi])));
-                        const float P = ldexpf(1.0f, en.b);
-                        const float Ss = ldexpf(S, -E);
+                        const bool zero = (zero_S >> bi) & 1ull;
+                        const float Z = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_Z), bi));
+                        const float P = __uint_as_float((uint32_t)(127 + en.b) << 23);
+                        const float Ss = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_Ss), bi));
                         const int base = en.lds_off - en.lo;
                         const int rl = en.rlog;
                         const int cpy = lane & ((1 << rl) - 1);
-                        Part acc{0.0f, 0.0, 0.0};
-                        if (S == 0.0f) {
+                        Part<SUB> acc{};
+                        if (zero) {
                             // the range underflows at this b: every code is 0, xhat = min
                             // (all counts go to bin 0: its entropy terms come from the scan)
                             if (en.lo == 0 && tid == 0) hist[en.lds_off] += (uint32_t)nc;
                             if (en.first) {
 #pragma unroll
                                 for (int i = 0; i < EPT; ++i) {
-                                    if (i * NT + tid < nc) {
+                                    if (tid < nc - i * NT) {
                                         double d = (double)mn - as_f64(xv[i]);
-                                        acc.err64 = __builtin_fma(as_f64(wv[i]), d * d, acc.err64);
+                                        acc.err64[i % SUB] = __builtin_fma(as_f64(wv[i]), d * d, acc.err64[i % SUB]);
                                     }
                                 }
                             }
-                        } else if (fast && fabsf(Z) <= 8388608.0f && (en.packed || !en.split)) {
+                        } else if (((fast_Z >> bi) & 1ull) && (en.packed || !en.split)) {
                             uint32_t seen = 0;
                             // byte address of bin word w: base + w, in the 0x4B000000-biased
                             // form the fast path uses (see eval_fast)
@@ -743,39 +842,54 @@ void sweep_kernel(SweepParams p) {
                                                 : hist_lds + 4u * (uint32_t)(base + cpy) - (0x4B000000u << (rl + 2));
                             asm volatile("" : "+v"(cadj));
                             if (en.packed)
-                                acc = eval_fast_dispatch<NT, EPT, true>(check, en.rtn, en.split, en.first, cadj, wlo,
+                                acc = eval_fast_dispatch<NT, EPT, SUB, true>(check, en.rtn, en.split, en.first, cadj, wlo,
                                                                         4u * (uint32_t)en.nwords, 0, u, xv, wv, nc,
                                                                         tid, P, Ss, Z, lf, seen);
                             else
-                                acc = eval_fast_dispatch<NT, EPT, false>(check, en.rtn, false, true, cadj, wlo,
+                                acc = eval_fast_dispatch<NT, EPT, SUB, false>(check, en.rtn, false, true, cadj, wlo,
                                                                          4u * (uint32_t)en.nwords, rl, u, xv, wv,
                                                                          nc, tid, P, Ss, Z, lf, seen);
                             ovf |= seen & big_count_mask(en.packed);
                         } else {
                             uint32_t seen = 0;
-                            acc = eval_generic<NT, EPT>(u, xv, wv, nc, tid, P, S, Ss, Z, hist, base, en.lo,
+                            acc = eval_generic<NT, EPT, SUB>(u, xv, wv, nc, tid, P,
+                                                        __int_as_float(__builtin_amdgcn_readlane(
+                                                            __float_as_int(my_S), bi)),
+                                                        Ss, Z, hist, base, en.lo,
                                                         en.nwords, en.packed, rl, cpy, !fast, en.first,
                                                         en.rtn, lf, seen);
                             ovf |= seen & big_count_mask(en.packed);
                         }
                         if (en.first) {
-                            double tot;
-                            if (fast && S != 0.0f) {
-                                // FP32 terms (scaled by 2^-2E): trusted when finite and
-                                // large enough that underflowed terms cannot matter
-                                const float t32 = wave_total_f32(acc.err);
-                                if (__builtin_isfinite(t32) && t32 >= (wm + 1.0f) * 0x1p-112f)
-                                    tot = (double)t32 * esc;
-                                else
-                                    tot = wave_total_f64(loss_f64<NT, EPT>(u, xv, wv, nc, tid, P, Ss, Z)) * esc;
-                            } else {
-                                tot = wave_total_f64(acc.err64);
+#pragma unroll
+                            for (int sub = 0; sub < SUB; ++sub) {
+                                // lane 63 has the wavefront's total; the rescaling by
+                                // 2^(2E) (1 on literal tiles) waits for the table entry
+                                double tot;
+                                bool trust = false;
+                                if (fast && !zero) {
+                                    // FP32 terms (scaled by 2^-2E): trusted when finite and
+                                    // large enough that underflowed terms cannot matter
+                                    const float t32 = wave_sum63_f32(acc.err[sub]);
+                                    tot = (double)t32;
+                                    trust = __builtin_amdgcn_ballot_w64(t32 >= wthr && t32 < INFINITY) >> 63;
+                                } else {
+                                    tot = acc.err64[sub];
+                                }
+                                if (!trust) {
+                                    if (fast && !zero)
+                                        tot = loss_f64<NT, EPT, SUB>(u, xv, wv, nc, tid, P, Ss, Z, sub);
+                                    tot = wave_total_f64(tot);
+                                }
+                                if (lane == 63) {
+                                    if (CHUNKED) errpart[bi][sub * NW + wave] += tot;
+                                    else errpart[bi][sub * NW + wave] = tot;
+                                }
                             }
-                            if (lane == 0) errpart[bi][wave] += tot;
                         }
-                        if (en.rtn && S != 0.0f) {
-                            const double tot = wave_total_f64(acc.ent);
-                            if (lane == 0) bitpart[bi][wave] += tot;
+                        if (en.rtn && !zero) {
+                            const double tot = wave_sum63_f64(acc.ent);
+                            if (lane == 63) bitpart[bi][wave] += tot;
                         }
                     }
                 }
@@ -784,6 +898,7 @@ void sweep_kernel(SweepParams p) {
                 if (__builtin_amdgcn_ballot_w64(ovf != 0u) != 0 && lane == 0) atomicOr(&ovf_flag[bt], 1u);
                 __syncthreads();
                 const bool any_ovf = ovf_flag[bt] != 0u;
+                if (tid == 0) chan_bad = 0u;  // (everyone has read it: one barrier ago)
                 const bool dbg = sc->hist != nullptr;
                 // ---- entropy terms of the scanned histograms (the batch's
                 // first entries): one lane per bin, which adds up the bin's
@@ -819,8 +934,8 @@ void sweep_kernel(SweepParams p) {
                             else
                                 s += hlog2h(h, lg, lgt);
                         }
-                        const double tot = wave_total_f64(s);
-                        if (lane == 0) bitpart[en.bi][wave] += tot;
+                        const double tot = wave_sum63_f64(s);
+                        if (lane == 63) bitpart[en.bi][wave] += tot;
                     }
                 }
                 // ---- the rest: incremental entries whose range underflows at
@@ -834,7 +949,7 @@ void sweep_kernel(SweepParams p) {
                 const int e_end = (any_ovf || anyzero || dbg) ? e1 : p.batch_scan_end[bt];
                 for (int e = e_beg; e < e_end; ++e) {
                     const HistEntry en = p.entries[e];
-                    const bool scan = !en.rtn || (anyzero && prmS[en.bi] == 0.0f);
+                    const bool scan = !en.rtn || ((zero_S >> en.bi) & 1ull);
                     const bool fix = !scan && any_ovf;
                     uint32_t* hout = sc->hist ? sc->hist + slot * sc->hist_bins + sc->hoff[en.bi] : nullptr;
                     if (!scan && !fix && !hout) continue;
@@ -877,25 +992,33 @@ void sweep_kernel(SweepParams p) {
                         }
                     }
                     if (scan || fix) {
-                        const double tot = wave_total_f64(s);
-                        if (lane == 0) bitpart[en.bi][wave] += tot;
+                        const double tot = wave_sum63_f64(s);
+                        if (lane == 63) bitpart[en.bi][wave] += tot;
                     }
                 }
                 __syncthreads();
+                if (tid == 0) ovf_flag[bt] = 0u;
             }
 
-            // ---- finalize the tile's table entries
+            // ---- finalize the channel's table entries.  No barrier follows:
+            // the next writes of these sums come behind the next channel's
+            // (or tile's) min/max barrier, which this wavefront has to reach.
             if (tid < nb) {
+                const double esc = ldexp(1.0, 2 * E);
                 double e = 0.0, s = 0.0;
 #pragma unroll
+                for (int w = 0; w < NW * SUB; ++w) {
+                    e += errpart[tid][w] * esc;
+                    if (CHUNKED) errpart[tid][w] = 0.0;
+                }
+#pragma unroll
                 for (int w = 0; w < NW; ++w) {
-                    e += errpart[tid][w];
                     s += bitpart[tid][w];
+                    bitpart[tid][w] = 0.0;
                 }
                 sc->err[slot * nb + tid] = e;
                 sc->bits[slot * nb + tid] = lgt[n] - s;  // n log2 n - sum_k h_k log2 h_k
             }
-            __syncthreads();
         }
     }
 }
@@ -1000,49 +1123,64 @@ __global__ void sweep_init_kernel(SceneDesc* __restrict__ scenes, int count,
 
 // ------------------------------------------------------------------ host side
 
-template <int NT, int EPT, bool CHUNKED>
+template <int NT, int EPT, bool CHUNKED, int SUB>
 static hipError_t launch_one(const SweepParams& p, int64_t grid, size_t lds,
                              hipStream_t s) {
     if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)sweep_kernel<NT, EPT, CHUNKED>,
+        hipError_t e = hipFuncSetAttribute((const void*)sweep_kernel<NT, EPT, CHUNKED, SUB>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         (void)e;
     }
-    hipLaunchKernelGGL((sweep_kernel<NT, EPT, CHUNKED>), dim3((unsigned)grid), dim3(NT), lds, s, p);
+    hipLaunchKernelGGL((sweep_kernel<NT, EPT, CHUNKED, SUB>), dim3((unsigned)grid), dim3(NT), lds, s, p);
     return hipGetLastError();
 }
 
 struct Variant {
     int nt, ept;
     bool chunked;
+    int sub;  // the loss sums are those of a workgroup of nt * sub threads
     hipError_t (*fn)(const SweepParams&, int64_t, size_t, hipStream_t);
     const void* kern;
 };
 
 #define MGS_V(NT, EPT) \
-    {NT, EPT, false, &launch_one<NT, EPT, false>, (const void*)&sweep_kernel<NT, EPT, false>}
+    {NT, EPT, false, 1, &launch_one<NT, EPT, false, 1>, (const void*)&sweep_kernel<NT, EPT, false, 1>}
+#define MGS_VS(NT, EPT, SUB) \
+    {NT, EPT, false, SUB, &launch_one<NT, EPT, false, SUB>, (const void*)&sweep_kernel<NT, EPT, false, SUB>}
 #define MGS_VC(NT, EPT) \
-    {NT, EPT, true, &launch_one<NT, EPT, true>, (const void*)&sweep_kernel<NT, EPT, true>}
+    {NT, EPT, true, 1, &launch_one<NT, EPT, true, 1>, (const void*)&sweep_kernel<NT, EPT, true, 1>}
 static const Variant kVariants[] = {
     MGS_V(256, 1),  MGS_V(256, 2),  MGS_V(256, 4),  MGS_V(256, 8),  MGS_V(256, 16), MGS_V(256, 32),
     MGS_V(512, 1),  MGS_V(512, 2),  MGS_V(512, 4),  MGS_V(512, 8),  MGS_V(512, 16), MGS_V(512, 32),
     MGS_V(1024, 1), MGS_V(1024, 2), MGS_V(1024, 4), MGS_V(1024, 8), MGS_V(1024, 16),
+    MGS_VS(256, 16, 2), MGS_VS(512, 16, 2),
     MGS_VC(512, 16),  // groups larger than any register-resident shape
 };
 #undef MGS_V
+#undef MGS_VS
 #undef MGS_VC
 
+// Threads whose loss sums a group of G elements is added up in (the width of
+// the default workgroup before the half-width shapes below).
+static int loss_width(int G) { return G <= 2048 ? 256 : G <= 4096 ? 512 : 1024; }
+
 // A non-chunked variant when nt * ept covers the group, else the chunked one.
+// A workgroup half as wide as loss_width takes the variant that keeps the wide
+// one's sums, so that its tables are those of the wide shape bit for bit.
 static const Variant* find_variant(int nt, int ept, int G = 0) {
     const bool need_chunk = (int64_t)nt * ept < G;
+    const Variant* found = nullptr;
     for (const Variant& v : kVariants)
-        if (v.nt == nt && v.ept == ept && v.chunked == need_chunk) return &v;
-    return nullptr;
+        if (v.nt == nt && v.ept == ept && v.chunked == need_chunk &&
+            (v.sub == 1 || v.nt * v.sub == loss_width(G)) && (!found || v.sub > found->sub))
+            found = &v;
+    return found;
 }
 
 int variant_count() { return (int)(sizeof(kVariants) / sizeof(kVariants[0])); }
 Shape variant_shape(int i) { return Shape{kVariants[i].nt, kVariants[i].ept, 0}; }
 bool variant_chunked(int i) { return kVariants[i].chunked; }
+bool variant_used(int i, int G) { return find_variant(kVariants[i].nt, kVariants[i].ept, G) == &kVariants[i]; }
 
 static int device_attr(hipDeviceAttribute_t a, int fallback) {
     int dev = 0, v = 0;
@@ -1640,7 +1778,7 @@ extern "C" int mgs_sweep_autotune(const mgs_sweep_desc* desc, const float* d_att
         const bool chunked = variant_chunked(candidate_variant(i));
         if (chunked != (capacity < sc.G)) continue;
         if (!chunked && capacity >= 4 * (int64_t)std::max(sc.G, 256)) continue;  // mostly idle lanes
-        if (!shape_valid(sh, sc.G)) continue;
+        if (!variant_used(candidate_variant(i), sc.G)) continue;
         rc = sweep_launch(desc, d_attr, d_imp, d_kept, d_err, d_bits, d_gmin, d_gmax, nullptr, d_ws,
                           ws_bytes, s, &sh);  // warm-up (and plan check)
         if (rc == MGS_EINVAL) continue;       // plan does not fit this capacity

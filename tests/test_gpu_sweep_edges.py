@@ -1,0 +1,108 @@
+"""Edges of the sweep kernel's variants: workgroups of half the width that keep the wide
+shape's sums, repeated elements past a ragged end, NaN pairs, rows beyond 32-bit offsets.
+Tolerances as in test_gpu_parity.py (loss 4e-6 relative, sizes 1e-9)."""
+import numpy as np
+import pytest
+
+from paper_2604_26799_amd import mgs, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as _t
+    if not _t.cuda.is_available():
+        pytest.skip("no GPU")
+    mgs.lib()
+    return _t
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def sweep(torch, attr, imp, kept, k, G, bits, check=True):
+    out = mgs.quant_sweep(dev(torch, attr), dev(torch, imp), dev(torch, kept.astype(np.int32)), k, G, bits,
+                          check=check)
+    torch.cuda.synchronize()
+    return {key: out[key].cpu().numpy() for key in ("err", "bits", "gmin", "gmax")}
+
+
+def assert_tables(got, want):
+    ok = ~np.isnan(want["err"])
+    assert np.array_equal(np.isnan(got["err"]), ~ok)
+    np.testing.assert_allclose(got["err"][ok], want["err"][ok], rtol=4e-6, atol=1e-300)
+    np.testing.assert_allclose(got["bits"][ok], want["bits"][ok], rtol=1e-9, atol=1e-6)
+    g = ~np.isnan(want["gmin"])
+    assert np.array_equal(got["gmin"][g], want["gmin"][g]) and np.array_equal(got["gmax"][g], want["gmax"][g])
+
+
+@pytest.mark.parametrize("G,wide,half", [
+    (2049, (512, 8), (256, 16)),    # the smallest and largest groups of each half-width shape,
+    (4096, (512, 8), (256, 16)),    # and one whose last elements are spread over few lanes
+    (4097, (1024, 8), (512, 16)),
+    (7777, (1024, 8), (512, 16)),
+    (8192, (1024, 8), (512, 16)),
+])
+@pytest.mark.parametrize("scale", [1.0, 1e-38])  # (tiny weights: the FP64 recomputation of the sums)
+def test_half_width_shapes(torch, orc, G, wide, half, scale):
+    attr, imp = synth.scene(30011, 20, seed=G)
+    attr = np.ascontiguousarray(attr[:5])
+    attr[4] = attr[4] * np.float32(1e-30)  # literal division at the largest bit-widths
+    imp = (imp / imp.max() * np.float32(scale)).astype(np.float32)
+    k = np.array([30011, 2 * G + 1, G - 1, 1], np.int64)
+    bits = [1, 4, 8, 12, 15, 16]
+    kept = orc.prune_select(imp, k)
+    want = orc.quant_sweep(attr, imp, kept, k, G, bits)
+    got = []
+    try:
+        for nt, ept in (wide, half):
+            for persist in (0, 1):
+                mgs.sweep_set_shape(G, len(bits), max(bits), nt, ept, 98304, 0, persist)
+                got.append(sweep(torch, attr, imp, kept, k, G, bits))
+    finally:
+        mgs.sweep_set_shape(G, len(bits), max(bits), 0, 0, 0, 0)
+    for one in got:
+        assert_tables(one, want)
+        for key in ("err", "gmin", "gmax"):  # the half-width shape adds the same terms in the same order
+            assert np.array_equal(one[key], got[0][key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("G", [1, 2, 255, 1025, 5000, 16384, 20000])  # 20000: the chunked kernel
+def test_nan_and_ragged_ends(torch, orc, G):
+    """One NaN in the last, ragged group (in turn in its last and its first element) makes that
+    group NaN and leaves every other one, and its bounds are those of its other values."""
+    n = 2 * G + max(1, G // 2)
+    attr, imp = synth.scene(n, 11, seed=G)
+    attr = np.ascontiguousarray(attr[:3])
+    k, bits = np.array([n], np.int64), [2, 7, 13]
+    kept = np.arange(n, dtype=np.int32)
+    want = orc.quant_sweep(attr, imp, kept, k, G, bits)
+    for at in (n - 1, 2 * G):
+        bad = attr.copy()
+        bad[1, at] = np.nan
+        got = sweep(torch, bad, imp, kept, k, G, bits, check=False)
+        assert np.isnan(got["err"][0, 1, -1]).all() and np.isnan(got["bits"][0, 1, -1]).all()
+        rest = np.delete(bad[1, 2 * G:], at - 2 * G)
+        if rest.size:
+            assert got["gmin"][0, 1, -1] == rest.min() and got["gmax"][0, 1, -1] == rest.max()
+        for key in ("err", "bits", "gmin", "gmax"):
+            got[key][0, 1, -1] = want[key][0, 1, -1]
+        assert_tables(got, want)
+
+
+def test_rows_beyond_32_bit_offsets(torch, orc):
+    """Rows with a stride above 2^30 floats are gathered by index, others by 32-bit byte offset."""
+    n, G, bits = 5000, 2048, [3, 9]
+    attr, imp = synth.scene(n, 11, seed=3)
+    k = np.array([n, 3333], np.int64)
+    kept = orc.prune_select(imp, k)
+    want = orc.quant_sweep(attr[:1], imp, kept, k, G, bits)
+    for ld in (1 << 30, (1 << 30) + 64):
+        wide = torch.zeros((1, ld), dtype=torch.float32, device="cuda")
+        wide[0, :n] = dev(torch, attr[0])
+        scene = {"attr": wide, "n": n, "imp": dev(torch, imp), "kept": dev(torch, kept.astype(np.int32)), "k": k}
+        (out,) = mgs.quant_sweep_multi([scene], G, bits)
+        assert_tables({key: out[key].cpu().numpy() for key in ("err", "bits", "gmin", "gmax")}, want)
+        del wide, scene
