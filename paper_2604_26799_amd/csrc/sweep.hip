@@ -1402,18 +1402,56 @@ int fill_scene(const mgs_sweep_desc* d, const float* attr, const float* imp, con
 
 bool shape_valid(const Shape& sh, int G) { return find_variant(sh.nt, sh.ept, G) != nullptr; }
 
-// Default launch shape: the fewest elements per thread that still gives each
-// thread >= 8 of them (or the largest workgroup when G is small); groups
-// beyond 1024 x 16 elements are processed in chunks of that size.
-Shape default_shape(int G, int nb, int bmax) {
-    (void)nb;
-    (void)bmax;
-    for (int e : {8, 16, 4, 2, 1, 32}) {
-        for (int t : {256, 512, 1024}) {
-            if ((int64_t)t * e >= G && find_variant(t, e, G)) return Shape{t, e, 0};
-        }
+// Default launch shape, by group size G and the launch's number of (group,
+// channel) pairs.
+//
+// Threads and elements per thread.  Each wavefront pays about 60 VALU
+// instructions per channel and bit-width around the pass over its elements, so
+// a thread takes up to 16 elements; and two or more workgroups per CU hide each
+// other's barriers, so they stay as narrow as 16 elements allow.  Half-width
+// shapes keep the wide shape's sums, so the choice changes no table.  Measured
+// on 1e6 x 20, 16 ratios: G = 8192, b = 2..16, 512 x 16 1.73 ms against 2.39
+// for 1024 x 8; G = 4096, b = 1..16, 256 x 16 2.22 ms against 3.59 for 512 x 8
+// with the whole LDS.  G <= 1024 leaves out the idle elements of 256 x 8.  A
+// launch of fewer pairs than resident workgroups would be a little faster in
+// the wide shape (55 against 62 us for 160 pairs of G = 8192), but the
+// histogram plan, and with it the last bits of the sizes, goes with the shape,
+// which therefore depends on G alone: a scene's tables are the same bit for
+// bit alone and in a batch.
+//
+// LDS.  A workgroup plans its histograms in its share of the CU's LDS at four
+// wavefronts per SIMD (1024 threads per CU): with a larger share fewer
+// workgroups fit, and that costs more than the extra bin windows save (500,000
+// x 20, 8 ratios, G = 1024, b = 2..16: 1.27 ms at a quarter of the LDS, 1.71 at
+// 96 KB, 2.97 with all of it).  The chunked kernel holds 256 VGPRs, one
+// workgroup per CU, and takes all of it (4.25 against 6.50 ms at G = 30000).
+//
+// Channels per tile and grid.  Tiles of one channel spread a small launch over
+// the chip; tiles of more channels gather the indices and weights fewer times
+// but leave a longer tail.  The lines, in pairs per resident workgroup, are
+// where the faster side changed on 100,000 to 1,000,000 x 20, 16 ratios:
+// G = 8192 4.7 pairs 245 us with one channel and a plain grid, 251 with two
+// and a persistent one, 318 with all; G = 4096 8.8 pairs 519 / 503 / 894 us,
+// G = 4096 26 pairs 1.40 / 1.36 (three: 1.38) / 1.65 ms, G = 8192 26 pairs
+// three 1.08 / all 1.08 ms, 44 pairs four 1.77 / all with the split tail 1.73.
+// The chunked kernel gathers indices and weights for every channel anyway: one
+// channel per tile, persistent (4.27 against 4.39 ms, 0.95 against 1.30 ms).
+Shape default_shape(int G, int64_t pairs, int channels) {
+    const int64_t cus = device_cus();
+    if (G > 16384) return Shape{512, 16, 0, 1, 1};
+    Shape sh;
+    sh.nt = G <= 4096 ? 256 : G <= 8192 ? 512 : 1024;
+    sh.ept = G <= 256 ? 1 : G <= 512 ? 2 : G <= 1024 ? 4 : G <= 2048 ? 8 : 16;
+    sh.lds_cap = sh.nt >= 1024 ? 0 : (int)((int64_t)device_lds_bytes() * sh.nt / 1024);
+    const double rounds = (double)pairs / (double)(cus * (1024 / sh.nt));
+    if (rounds >= 2.0 * channels) {
+        sh.cpb = 0;
+        sh.persist = 1;
+    } else {
+        sh.cpb = rounds < 6.0 ? 1 : rounds < 20.0 ? 2 : 3;
+        sh.persist = sh.cpb > 1;
     }
-    return Shape{512, 16, 0};  // chunked
+    return sh;
 }
 
 int launch_sweep(const SweepParams& p, const Shape& sh, size_t lds,
@@ -1571,7 +1609,13 @@ static int sweep_launch_scenes(mgs::SceneDesc* scs, int n, void* d_ws, size_t ws
     if (force) {
         sh = *force;
     } else if (!tuned_shape(s0.G, s0.nb, s0.bmax, &sh) || !shape_valid(sh, s0.G)) {
-        sh = default_shape(s0.G, s0.nb, s0.bmax);
+        int64_t pairs = 0;
+        int cm = 1;
+        for (int i = 0; i < n; ++i) {
+            pairs += (int64_t)scs[i].gpc * scs[i].C;
+            cm = std::max(cm, (int)scs[i].C);
+        }
+        sh = default_shape(s0.G, pairs, cm);
     }
     if (!shape_valid(sh, s0.G)) return MGS_EINVAL;
     SweepParams p;

@@ -106,3 +106,41 @@ def test_rows_beyond_32_bit_offsets(torch, orc):
         (out,) = mgs.quant_sweep_multi([scene], G, bits)
         assert_tables({key: out[key].cpu().numpy() for key in ("err", "bits", "gmin", "gmax")}, want)
         del wide, scene
+
+
+@pytest.mark.parametrize("G,n,C,T,wide", [
+    (200, 3000, 3, 2, (256, 8)), (256, 60000, 11, 4, (256, 8)), (257, 60000, 5, 4, (256, 8)),
+    (513, 60000, 5, 4, (256, 8)), (1024, 60000, 11, 6, (256, 8)), (1025, 60000, 11, 2, (256, 8)),
+    (2048, 60000, 3, 1, (256, 8)), (2049, 60000, 20, 6, (512, 8)), (4096, 60000, 11, 2, (512, 8)),
+    (4097, 120000, 20, 6, (1024, 8)), (8192, 9000, 2, 1, (1024, 8)), (8192, 300000, 20, 4, (1024, 8)),
+    (8193, 60000, 20, 3, (1024, 16)), (16384, 20000, 1, 1, (1024, 16)), (16385, 60000, 11, 3, (512, 16)),
+])
+def test_default_shape_keeps_the_tables(torch, G, n, C, T, wide):
+    """The default launch shape follows the launch's size; its losses and bounds are bit for bit those
+    of the wide shape in plain one-workgroup-per-tile form, its sizes the same to FP64 rounding."""
+    attr, imp = synth.scene(n, 20, seed=n + G)
+    attr = np.ascontiguousarray(attr[:C])
+    k = np.linspace(n // 3, n, T).astype(np.int64)
+    order = np.argsort(-imp, kind="stable")
+    kept = np.concatenate([np.sort(order[:kt]) for kt in k]).astype(np.int32)
+    bits = [2, 6, 11, 16]
+    got = sweep(torch, attr, imp, kept, k, G, bits)
+    try:
+        mgs.sweep_set_shape(G, len(bits), max(bits), *wide, 0, 0, 0)
+        want = sweep(torch, attr, imp, kept, k, G, bits)
+    finally:
+        mgs.sweep_set_shape(G, len(bits), max(bits), 0, 0, 0, 0)
+    for key in ("err", "gmin", "gmax"):
+        assert np.array_equal(got[key], want[key], equal_nan=True), key
+    ok = ~np.isnan(want["bits"])
+    np.testing.assert_allclose(got["bits"][ok], want["bits"][ok], rtol=1e-12, atol=1e-9)
+    # and bit for bit, sizes too, those of the same scene in a batch with a larger one
+    big = 400_000
+    attr2, imp2 = synth.scene(big, 20, seed=1)
+    k2 = np.array([big, big // 2], np.int64)
+    scenes = [{"attr": dev(torch, attr), "imp": dev(torch, imp), "kept": dev(torch, kept), "k": k},
+              {"attr": dev(torch, attr2), "imp": dev(torch, imp2), "k": k2,
+               "kept": dev(torch, np.concatenate([np.arange(v) for v in k2]).astype(np.int32))}]
+    both = mgs.quant_sweep_multi(scenes, G, bits)[0]
+    for key in ("err", "bits", "gmin", "gmax"):
+        assert np.array_equal(both[key].cpu().numpy(), got[key], equal_nan=True), key
