@@ -18,22 +18,34 @@
 // the merges in reverse:  a1 = (sqrt(w1) L - sqrt(w2) H) / sqrt(w1 + w2),
 //                         a2 = (sqrt(w2) L + sqrt(w1) H) / sqrt(w1 + w2).
 //
-// The merge structure follows from the codes alone, without running the
-// steps: every merge joins the leaves on the two sides of one boundary i
-// between neighbouring codes (N - 1 boundaries, N - 1 merges).  With d the
-// highest bit in which code[i] and code[i + 1] differ, the merge happens at
-// step d and joins the leaves [L, i] and [i + 1, R], the run of codes that
-// agree with code[i] above bit d (every boundary inside either side differs
-// lower, so each side is one node by then): L and R are binary searches in
-// the sorted codes, the weights are i - L + 1 and R - i, the slots L and
-// i + 1.  The AC index of the merge is its rank in (step, boundary) order:
-// per-block counts of each step, a scan over (step, block), and a scatter
-// that ranks a block's boundaries of each step with wavefront ballots.  The
-// values then go through one launch per step over that step's merges only;
-// they are stored node-major ([N][C]) and a merge is done by a team of lanes,
-// one per channel, so its two nodes' rows are read and written whole however
-// far apart the nodes are (with one node per lane and channel-major values a
-// merge touched a separate cache line per channel and node).
+// The merge structure follows from the codes alone: every merge joins the
+// leaves on the two sides of one boundary i between neighbouring codes (N - 1
+// boundaries, N - 1 merges).  With d the highest bit in which code[i] and
+// code[i + 1] differ, the merge happens at step d and joins the leaves [L, i]
+// and [i + 1, R], the run of codes that agree with code[i] above bit d (every
+// boundary inside either side differs lower, so each side is one node by then);
+// the weights are i - L + 1 and R - i.  The AC index of the merge is its rank
+// in (step, boundary) order: counts per (step, block of leaves), a scan over
+// them, and the rank within the block by wavefront ballots.
+//
+// Most merges are local: a run of 256 neighbouring leaves contains all but a
+// dozen of its merges whole, so the steps are not run one after the other over
+// all nodes.  One wavefront takes a tile of 256 leaves, does every merge whose
+// run [L, R] lies inside the tile, in step order, on values in LDS, and hands
+// on the nodes that are left: the maximal subtrees of a contiguous run of
+// leaves, at most two per step (6 depth), about 13 of 256 in a scene.  The
+// next level joins 16 such lists in the same way, and so on: five levels reach
+// the root of 8 million leaves.  The inverse builds the lists bottom-up without
+// values and undoes the merges level by level from the root.
+//
+// What bounds it: the transform reads and writes every attribute once (0.89 GB
+// at 5.3e6 x 20, 0.19 ms at the rate of a copy); the leaf level's FP64 issue
+// (two corrected quotients per merge and channel) and the chain of about 20
+// steps per tile, hidden by other wavefronts, come close behind.  Run as one
+// launch per step over node values in HBM (42 dependent launches, rows of both
+// nodes fetched from all over the array) the forward took 1.95 ms at 5.3e6 x 20
+// and the inverse 0.58 ms at 1e6 x 20.
+#include <algorithm>
 #include <cstring>
 
 #include "common.h"
@@ -41,14 +53,28 @@
 namespace mgs {
 namespace {
 
-constexpr int RH_THREADS = 256;
-constexpr int RH_ITEMS = 8;                          // boundaries per thread
-constexpr int RH_SPAN = RH_THREADS * RH_ITEMS;       // per block
-constexpr int RH_MAX_BLOCKS = 4096;                  // N - 1 <= RH_SPAN * RH_MAX_BLOCKS
-constexpr int RH_BINS = 64;                          // merge steps (3 depth <= 63)
-constexpr int RH_TEAM = 32;                          // lanes per merge (one channel each)
-constexpr int RH_TEAMS = RH_THREADS / RH_TEAM;
-constexpr int RH_GROUP = 16;                         // consecutive merges per block iteration
+constexpr int RH_STEPS = 64;                         // bins of merge steps (3 depth <= 63; 63: never merged)
+constexpr int RH_TILE = 256;                         // leaves per wavefront at the leaf level
+constexpr int RH_ROUNDS = RH_TILE / MGS_WAVE;
+constexpr int RH_WAVES = 4;
+constexpr int RH_THREADS = RH_WAVES * MGS_WAVE;
+constexpr int RH_SPAN = RH_TILE * RH_WAVES;          // leaves per block of the counts
+constexpr int RH_MAX_BLOCKS = 8192;                  // N <= RH_SPAN * RH_MAX_BLOCKS
+constexpr int RH_CH = 4;                             // channels in LDS at a time (48 KB per block: three per CU)
+constexpr int RH_VS = RH_TILE + 1;                   // row stride of the values (channels in different banks)
+constexpr int RH_GROUP = 16;                         // lists that an upper level joins
+constexpr int RH_CAP1 = 256;                          // nodes of a group in LDS at the first upper level,
+constexpr int RH_CAP2 = 768;                          // and above it (few groups, lists of more nodes)
+constexpr int RH_LEVELS = 5;                         // leaf level and up to four above it
+
+// The nodes that a level leaves, per tile (leaf level) or group of 16 lists.
+struct RahtLevel {
+    int32_t* cnt;     // [lists] nodes in the list
+    int32_t* first;   // [lists][stride] first leaf of each node (a node reaches to the next one's first leaf)
+    int32_t* ac;      // [lists][stride] AC index of the merge across the boundary after the node
+    double* rows;     // [lists][stride][C] values
+    int32_t lists;
+};
 
 struct RahtArgs {
     const uint64_t* codes;
@@ -60,388 +86,754 @@ struct RahtArgs {
     const float* coef_in;  // inverse input [C][ld]
     float* coef;           // forward output [C][ld]
     float* attr_out;       // inverse output [C][ld]
-    double* val;           // [N][C] node values by slot (a node's channels adjacent)
-    uint8_t* dstep;        // [N - 1] merge step of each boundary
-    int32_t* lb;           // [N - 1] first leaf of each boundary's merge
-    int32_t* rb;           // [N - 1] last leaf
-    int64_t* cnt;          // [RH_BINS][nblk] boundaries per (step, block), then their first AC index
-    int64_t* tot;          // [RH_BINS] boundaries per step
-    int64_t* ac_base;      // [RH_BINS + 1] first AC index of each step
-    int32_t* pa;           // [N - 1] per AC index: slot of the first node
-    int32_t* pb;           //                       slot of the second node
-    int64_t* wa;           //                       weights
-    int64_t* wb;
+    int32_t* cnt;          // [RH_STEPS][nblk] boundaries per (step, block), then their exclusive prefix in the step
+    int32_t* tot;          // [RH_STEPS] boundaries per step
+    // scratch of a group whose lists hold more than RH_TILE nodes, per node of the level below
+    uint64_t* big_code;
+    int32_t* big_i;        // [6][big_stride]
+    int64_t big_stride;
     mgs_status_block* status;
-    int32_t nblk;          // blocks over the N - 1 boundaries
-    int32_t values;        // forward: the leaves' values are loaded
+    int32_t nblk;          // blocks of RH_SPAN leaves
+    int32_t stride;        // node slots per list
+    int32_t top;           // the last level (one list, the root)
+    RahtLevel lev[RH_LEVELS];
 };
 
-// The codes must increase and stay below 2^(3 depth).
-__global__ void raht_init_kernel(RahtArgs a) {
-    const int64_t lim = a.depth >= 21 ? 0 : ((int64_t)1 << (3 * a.depth));
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.N;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t c = a.codes[i];
-        if ((i > 0 && a.codes[i - 1] >= c) || (lim && c >= (uint64_t)lim)) atomicOr(&a.status->nonfinite, 4u);
-    }
-    if (blockIdx.x == 0)
-        for (int b = threadIdx.x; b < RH_BINS; b += blockDim.x) a.tot[b] = 0;
-}
+enum { RH_FORWARD = 0, RH_STRUCTURE = 1, RH_INVERSE = 2 };
 
-// Transposes between the [C][ld] FP32 attribute layout and the [N][C] FP64
-// node values through an LDS tile of 64 nodes x 32 channels, so that both
-// sides are read and written in runs.
-constexpr int RH_TILE_N = 64, RH_TILE_C = 32;
-
-__global__ __launch_bounds__(RH_THREADS) void raht_load_kernel(RahtArgs a) {
-    __shared__ double t[RH_TILE_C][RH_TILE_N + 1];
-    for (int64_t i0 = (int64_t)blockIdx.x * RH_TILE_N; i0 < a.N; i0 += (int64_t)gridDim.x * RH_TILE_N) {
-        const int nn = (int)std::min<int64_t>(RH_TILE_N, a.N - i0);
-        for (int k0 = 0; k0 < a.C; k0 += RH_TILE_C) {
-            const int nk = std::min(RH_TILE_C, a.C - k0);
-            for (int e = threadIdx.x; e < nk * RH_TILE_N; e += RH_THREADS) {
-                const int kk = e / RH_TILE_N, n = e % RH_TILE_N;
-                if (n < nn) t[kk][n] = (double)a.attr[(int64_t)(k0 + kk) * a.ld + i0 + n];
-            }
-            __syncthreads();
-            for (int e = threadIdx.x; e < nk * nn; e += RH_THREADS) {
-                const int n = e / nk, kk = e % nk;
-                a.val[(i0 + n) * a.C + k0 + kk] = t[kk][n];
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// The merge across boundary i: its step d and the leaf range [L, R] it joins
-// ([L, i] first node, [i + 1, R] second).  Codes that do not increase give a
-// harmless stand-in (d = 0, L = i, R = i + 1; the status flag is raised by
-// the init kernel) so every index stays in bounds.
-struct Boundary {
-    int d;
-    int64_t L, R;
-};
-
-__device__ __forceinline__ int boundary_step(const RahtArgs& a, int64_t i) {
-    const uint64_t c0 = a.codes[i], c1 = a.codes[i + 1];
-    if (c1 <= c0) return 0;
+// The merge step of the boundary between two neighbouring codes.  Codes that
+// do not increase or lie outside the grid (flagged by the counting kernel) are
+// never merged; every index stays in bounds all the same.
+__device__ __forceinline__ int merge_step(uint64_t c0, uint64_t c1, int bits) {
+    if (c1 <= c0) return RH_STEPS - 1;
     const int d = 63 - __clzll((long long)(c0 ^ c1));
-    return d >= 3 * a.depth ? RH_BINS - 1 : d;  // beyond the grid: never merged (flagged by init)
+    return d >= bits ? RH_STEPS - 1 : d;
 }
 
-__device__ __forceinline__ Boundary boundary(const RahtArgs& a, int64_t i) {
-    const uint64_t c0 = a.codes[i], c1 = a.codes[i + 1];
-    Boundary b{0, i, i + 1};
-    if (c1 <= c0) return b;
-    const int d = 63 - __clzll((long long)(c0 ^ c1));
-    if (d >= 3 * a.depth) {
-        b.d = RH_BINS - 1;
-        return b;
+// Lanes (of `valid`) that hold the same bin as this one.
+__device__ __forceinline__ uint64_t same_bin(bool valid, int b) {
+    uint64_t eq = __builtin_amdgcn_ballot_w64(valid);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const uint64_t m = __builtin_amdgcn_ballot_w64(valid && ((b >> k) & 1));
+        eq &= ((b >> k) & 1) ? m : ~m;
     }
-    b.d = d;
-    const int sh = d + 1;                              // <= 63
-    const uint64_t lo_code = (c0 >> sh) << sh;         // first code of the run
-    const uint64_t hi_code = lo_code + (1ull << sh);   // first code past it
-    // a run spans at most 2^sh codes, hence at most that many leaves
-    const int64_t span = sh >= 62 ? a.N : std::min<int64_t>(a.N, (int64_t)1 << sh);
-    // L: first j in [max(0, i + 1 - span), i] with code[j] >= lo_code
-    int64_t lo = std::max<int64_t>(0, i + 1 - span), hi = i;
-    while (lo < hi) {
-        const int64_t m = lo + ((hi - lo) >> 1);
-        if (a.codes[m] >= lo_code) hi = m;
-        else lo = m + 1;
-    }
-    b.L = lo;
-    // R: last j in [i + 1, min(N - 1, i + span)] with code[j] < hi_code
-    lo = i + 1;
-    hi = std::min<int64_t>(a.N - 1, i + span);
-    while (lo < hi) {
-        const int64_t m = lo + ((hi - lo + 1) >> 1);
-        if (a.codes[m] < hi_code) lo = m;
-        else hi = m - 1;
-    }
-    b.R = lo;
-    return b;
+    return eq;
 }
 
-// Boundaries of each step in this block (boundary i = blockIdx.x * RH_SPAN +
-// e * RH_THREADS + threadIdx.x).
+__device__ __forceinline__ uint64_t lanes_below(int lane) { return lane == 0 ? 0ull : (~0ull >> (64 - lane)); }
+
+// LDS accesses of one wavefront complete in order: this only keeps the
+// compiler from moving them.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Rank of this lane's item among the items of its bin so far (`h`: the
+// wavefront's counters, which take this round's items up).
+__device__ __forceinline__ int bin_rank(bool valid, int b, uint32_t* h, int lane) {
+    const uint64_t eq = same_bin(valid, b);
+    const uint64_t below = eq & lanes_below(lane);
+    const uint32_t base = valid ? h[b] : 0u;
+    wave_order();
+    if (valid && below == 0ull) h[b] = base + (uint32_t)__popcll(eq);
+    wave_order();
+    return (int)base + __popcll(below);
+}
+
+// Chunk k of n over C channels: its first channel and their number (at most
+// one more in the first chunks than in the others).
+__device__ __forceinline__ int chunk_first(int C, int n, int k) { return k * (C / n) + min(k, C % n); }
+__device__ __forceinline__ int chunk_size(int C, int n, int k) { return C / n + (k < C % n ? 1 : 0); }
+
+// Exclusive prefix sum over the lanes of a wavefront.
+__device__ __forceinline__ int wave_exclusive(int v, int lane) {
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < MGS_WAVE; o <<= 1) {
+        const int y = __shfl_up(incl, o, MGS_WAVE);
+        if (lane >= o) incl += y;
+    }
+    return incl - v;
+}
+
+// Boundaries of each step per block of RH_SPAN leaves (boundary i belongs to
+// the block of leaf i); raises the status flag for codes that do not increase
+// or do not lie below 2^(3 depth).
 __global__ __launch_bounds__(RH_THREADS) void raht_count_kernel(RahtArgs a) {
-    __shared__ uint32_t h[RH_BINS];
-    for (int b = threadIdx.x; b < RH_BINS; b += RH_THREADS) h[b] = 0u;
-    __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * RH_SPAN + threadIdx.x;
-    for (int e = 0; e < RH_ITEMS; ++e) {
-        const int64_t i = i0 + (int64_t)e * RH_THREADS;
-        if (i >= a.N - 1) break;
-        const int d = boundary_step(a, i);
-        a.dstep[i] = (uint8_t)d;
-        atomicAdd(&h[d], 1u);
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < RH_BINS; b += RH_THREADS) {
-        a.cnt[(int64_t)b * a.nblk + blockIdx.x] = h[b];
-        if (h[b]) atomicAdd((unsigned long long*)&a.tot[b], (unsigned long long)h[b]);
-    }
-}
-
-// The leaf range of every boundary's merge (one boundary per thread: the
-// binary searches of many boundaries are in flight at once).
-__global__ void raht_bounds_kernel(RahtArgs a) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.N - 1;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const Boundary b = boundary(a, i);
-        a.lb[i] = (int32_t)b.L;
-        a.rb[i] = (int32_t)b.R;
-    }
-}
-
-// One block per step: the first AC index of each (step, block) -- the steps
-// before this one, then this step's counts of the earlier blocks -- in place,
-// and the first AC index of the step.
-__global__ __launch_bounds__(RH_THREADS) void raht_scan_kernel(RahtArgs a) {
-    __shared__ int64_t v[RH_MAX_BLOCKS];
-    __shared__ int64_t part[RH_THREADS];
-    const int st = blockIdx.x;
-    int64_t base = 0;
-    for (int b = 0; b < st; ++b) base += a.tot[b];
-    int64_t* c = a.cnt + (int64_t)st * a.nblk;
-    for (int j = threadIdx.x; j < a.nblk; j += RH_THREADS) v[j] = c[j];
-    __syncthreads();
-    constexpr int PER = RH_MAX_BLOCKS / RH_THREADS;
-    const int j0 = threadIdx.x * PER;
-    int64_t sum = 0;
-    for (int e = 0; e < PER; ++e)
-        if (j0 + e < a.nblk) sum += v[j0 + e];
-    part[threadIdx.x] = sum;
-    __syncthreads();
-    for (int o = 1; o < RH_THREADS; o <<= 1) {
-        const int64_t add = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
-    }
-    int64_t run = base + part[threadIdx.x] - sum;
-    for (int e = 0; e < PER; ++e)
-        if (j0 + e < a.nblk) {
-            const int64_t x = v[j0 + e];
-            v[j0 + e] = run;
-            run += x;
-        }
-    __syncthreads();
-    for (int j = threadIdx.x; j < a.nblk; j += RH_THREADS) c[j] = v[j];
-    if (threadIdx.x == 0) {
-        a.ac_base[st] = base;
-        if (st == RH_BINS - 1) a.ac_base[RH_BINS] = base + a.tot[st];
-    }
-}
-
-// Every boundary's merge at its AC index: the block's offset for the step,
-// plus the boundaries of that step in earlier (round, wave) pairs of the
-// block, plus the lanes below with the same step (lanes grouped by step with
-// six ballots, one per bit of the step).
-__global__ __launch_bounds__(RH_THREADS) void raht_pairs_kernel(RahtArgs a) {
-    constexpr int NW = RH_THREADS / MGS_WAVE;
-    __shared__ uint32_t cw[RH_ITEMS][NW][RH_BINS];
-    for (int j = threadIdx.x; j < RH_ITEMS * NW * RH_BINS; j += RH_THREADS) (&cw[0][0][0])[j] = 0u;
-    __syncthreads();
+    __shared__ uint32_t h[RH_WAVES][RH_STEPS];
     const int lane = threadIdx.x & (MGS_WAVE - 1), wave = threadIdx.x / MGS_WAVE;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int64_t i0 = (int64_t)blockIdx.x * RH_SPAN + threadIdx.x;
-    int bin[RH_ITEMS];
-    uint32_t rank[RH_ITEMS];
+    h[wave][lane] = 0u;
+    wave_order();
+    const int64_t i0 = (int64_t)blockIdx.x * RH_SPAN + wave * RH_TILE + lane;
+    uint64_t c0[RH_ROUNDS], c1[RH_ROUNDS];
 #pragma unroll
-    for (int e = 0; e < RH_ITEMS; ++e) {
-        const int64_t i = i0 + (int64_t)e * RH_THREADS;
+    for (int e = 0; e < RH_ROUNDS; ++e) {
+        const int64_t i = i0 + e * MGS_WAVE;
+        c0[e] = a.codes[min(i, a.N - 1)];
+        c1[e] = a.codes[min(i + 1, a.N - 1)];
+    }
+    const int bits = 3 * a.depth;
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e) {
+        const int64_t i = i0 + e * MGS_WAVE;
         const bool valid = i < a.N - 1;
-        const int b = valid ? (int)a.dstep[i] : 0;
-        bin[e] = b;
-        uint64_t eq = __ballot(valid);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const uint64_t m = __ballot(valid && ((b >> k) & 1));
-            eq &= ((b >> k) & 1) ? m : ~m;
-        }
-        rank[e] = (uint32_t)__popcll(eq & lt);
-        if (valid && (eq & lt) == 0ull) cw[e][wave][b] = (uint32_t)__popcll(eq);
+        bad |= (i < a.N && (c0[e] >> bits) != 0) || (valid && c1[e] <= c0[e]);
+        bin_rank(valid, merge_step(c0[e], c1[e], bits), h[wave], lane);
     }
+    if (__builtin_amdgcn_ballot_w64(bad) && lane == 0) atomicOr(&a.status->nonfinite, 4u);
     __syncthreads();
-    if (threadIdx.x < RH_BINS) {
-        uint32_t run = 0;
-        for (int e = 0; e < RH_ITEMS; ++e)
-            for (int w = 0; w < NW; ++w) {
-                const uint32_t v = cw[e][w][threadIdx.x];
-                cw[e][w][threadIdx.x] = run;
-                run += v;
-            }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < RH_ITEMS; ++e) {
-        const int64_t i = i0 + (int64_t)e * RH_THREADS;
-        if (i >= a.N - 1) continue;
-        const int b = bin[e];
-        const int64_t p = a.cnt[(int64_t)b * a.nblk + blockIdx.x] + cw[e][wave][b] + rank[e];
-        const int64_t L = a.lb[i], R = a.rb[i];
-        a.pa[p] = (int32_t)L;
-        a.pb[p] = (int32_t)(i + 1);
-        a.wa[p] = i - L + 1;
-        a.wb[p] = R - i;
+    if (threadIdx.x < RH_STEPS) {
+        uint32_t n = 0;
+        for (int w = 0; w < RH_WAVES; ++w) n += h[w][threadIdx.x];
+        a.cnt[(int64_t)threadIdx.x * a.nblk + blockIdx.x] = (int32_t)n;
     }
 }
 
-// The merges of step s (independent of each other), RH_GROUP consecutive AC
-// indices per block iteration: a team of RH_TEAM lanes takes one merge, lane
-// k channel k (channels beyond the team in further rounds), so the two
-// nodes' rows are read and written whole; the coefficients of the group go
-// through LDS and out as runs of consecutive AC indices per channel.
-__global__ __launch_bounds__(RH_THREADS) void raht_merge_kernel(RahtArgs a, int s) {
-    __shared__ float hs[RH_TEAM][RH_GROUP];
-    const int64_t b0 = a.ac_base[s], b1 = a.ac_base[s + 1];
-    const int team = threadIdx.x / RH_TEAM, tl = threadIdx.x % RH_TEAM;
-    for (int64_t g0 = b0 + (int64_t)blockIdx.x * RH_GROUP; g0 < b1; g0 += (int64_t)gridDim.x * RH_GROUP) {
-        const int ng = (int)std::min<int64_t>(RH_GROUP, b1 - g0);
-        for (int k0 = 0; k0 < a.C; k0 += RH_TEAM) {
-            const int k = k0 + tl;
-            for (int q = team; q < ng; q += RH_TEAMS) {
-                const int64_t p = g0 + q;
-                const int32_t sa = a.pa[p], sb = a.pb[p];
-                const int64_t w1 = a.wa[p], w2 = a.wb[p];
-                if (k < a.C) {
-                    const double s1 = sqrt((double)w1), s2 = sqrt((double)w2), sw = sqrt((double)(w1 + w2));
-                    double* va = a.val + (int64_t)sa * a.C;
-                    const double a1 = va[k], a2 = a.val[(int64_t)sb * a.C + k];
-                    const double L = (s1 * a1 + s2 * a2) / sw;
-                    const double H = (s1 * a2 - s2 * a1) / sw;
-                    va[k] = L;
-                    hs[tl][q] = (float)H;
+// One block per step: exclusive prefix of its counts over the blocks, in place,
+// and its total (the leaf level adds the totals of the earlier steps).
+constexpr int RH_SCAN_THREADS = 1024;
+__global__ __launch_bounds__(RH_SCAN_THREADS) void raht_scan_kernel(RahtArgs a) {
+    constexpr int PER = RH_MAX_BLOCKS / RH_SCAN_THREADS;
+    constexpr int NW = RH_SCAN_THREADS / MGS_WAVE;
+    __shared__ int wsum[NW];
+    const int lane = threadIdx.x & (MGS_WAVE - 1), wave = threadIdx.x / MGS_WAVE;
+    int32_t* c = a.cnt + (int64_t)blockIdx.x * a.nblk;
+    const int per = (a.nblk + RH_SCAN_THREADS - 1) / RH_SCAN_THREADS;  // consecutive blocks per thread (<= PER)
+    const int j0 = threadIdx.x * per;
+    int v[PER], sum = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        v[e] = e < per && j0 + e < a.nblk ? c[j0 + e] : 0;
+        sum += v[e];
+    }
+    int run = wave_exclusive(sum, lane);
+    if (lane == MGS_WAVE - 1) wsum[wave] = run + sum;
+    __syncthreads();
+    int total = 0;
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave) run += wsum[w];
+        total += wsum[w];
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+        if (e < per && j0 + e < a.nblk) {
+            c[j0 + e] = run;
+            run += v[e];
+        }
+    if (threadIdx.x == 0) a.tot[blockIdx.x] = total;
+}
+
+// n / s, correctly rounded, with y = RN(1 / s): RN(n y) is within 1.5 ulp, one
+// correction by the exact FMA remainder makes it faithful and a second one the
+// correctly rounded quotient (Markstein's theorem), five operations instead of
+// the division's dozen.  Zeros, non-finite values and magnitudes whose
+// remainders could leave the normal range take the division.
+__device__ __forceinline__ double quotient(double n, double s, double y) {
+    double q = n * y;
+    const bool odd = !(fabs(q) > 0x1p-900 && fabs(q) < 0x1p900);
+    double r = __builtin_fma(-s, q, n);
+    q = __builtin_fma(r, y, q);
+    r = __builtin_fma(-s, q, n);
+    q = __builtin_fma(r, y, q);
+    if (__builtin_amdgcn_ballot_w64(odd)) {  // (rare; the empty asm keeps it a branch)
+        asm volatile("" : "+v"(n));
+        if (odd) q = n / s;
+    }
+    return q;
+}
+
+// Blocks go round-robin over the XCDs: each XCD takes a contiguous run of
+// them, so that neighbouring blocks, which share the cache lines at the ends of
+// their runs of coefficients, share an L2.
+constexpr int RH_XCDS = 8;
+__device__ __forceinline__ int64_t xcd_block(int64_t nblk) {
+    const int64_t per = (nblk + RH_XCDS - 1) / RH_XCDS;
+    const int64_t b = (int64_t)(blockIdx.x % RH_XCDS) * per + blockIdx.x / RH_XCDS;
+    return blockIdx.x / RH_XCDS < per && b < nblk ? b : -1;
+}
+unsigned xcd_grid(int64_t nblk) { return (unsigned)((nblk + RH_XCDS - 1) / RH_XCDS * RH_XCDS); }
+
+// Leaf level: one wavefront per tile of RH_TILE leaves.
+template <int MODE>
+__global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
+    __shared__ double val[RH_WAVES][RH_CH * RH_VS];
+    __shared__ double sq[RH_TILE + 1], inv[RH_TILE + 1];  // sqrt(w) and RN(1 / sqrt(w))
+    __shared__ uint32_t hist[RH_WAVES][RH_STEPS], mcnt[RH_WAVES][RH_STEPS];
+    __shared__ int32_t base[RH_STEPS];                    // first AC index of each step in this block
+    __shared__ int32_t ac[RH_WAVES][RH_TILE];
+    __shared__ uint32_t pk[RH_WAVES][RH_TILE];            // the tile's merges in step order: i | L << 8 | R << 16
+    __shared__ uint8_t leaf_of[RH_WAVES][RH_TILE];        // first leaf of each node that is left
+    const int tid = threadIdx.x;
+    const int lane = tid & (MGS_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / MGS_WAVE);
+    const int64_t blk = xcd_block(a.nblk);
+    if (blk < 0) return;
+    const int64_t tile = blk * RH_WAVES + wave;
+    const int64_t s = tile * RH_TILE;
+    const int n = (int)max((int64_t)0, min((int64_t)RH_TILE, a.N - s));
+    const int bits = 3 * a.depth;
+    if (MODE != RH_STRUCTURE)
+        for (int k = tid; k <= RH_TILE; k += RH_THREADS) {
+            sq[k] = sqrt((double)k);
+            inv[k] = k ? 1.0 / sq[k] : 0.0;
+        }
+    hist[wave][lane] = 0u;
+    mcnt[wave][lane] = 0u;
+    uint64_t* cd = (uint64_t*)val[wave];
+    uint64_t c[RH_ROUNDS];
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e) c[e] = a.codes[min(s + e * MGS_WAVE + lane, a.N - 1)];
+    // forward: the attributes of a chunk of channels, loaded while the tile's
+    // structure is made or the chunk before is transformed (channels past the
+    // chunk and leaves past the tile repeat the last one)
+    const int nchunk = (a.C + RH_CH - 1) / RH_CH;
+    float x[RH_CH][RH_ROUNDS];
+    auto load_chunk = [&](int k) {
+        const int k0 = chunk_first(a.C, nchunk, k), nch = chunk_size(a.C, nchunk, k);
+#pragma unroll
+        for (int cc = 0; cc < RH_CH; ++cc)
+#pragma unroll
+            for (int e = 0; e < RH_ROUNDS; ++e)
+                x[cc][e] = a.attr[(int64_t)(k0 + min(cc, nch - 1)) * a.ld + min(s + e * MGS_WAVE + lane, a.N - 1)];
+    };
+    if (MODE == RH_FORWARD) load_chunk(0);
+    const uint64_t before = a.codes[max(min(s, a.N) - 1, (int64_t)0)];
+    const uint64_t after = a.codes[min(s + n, a.N - 1)];
+    if (wave == 0) {
+        const int t = a.tot[lane];
+        base[lane] = wave_exclusive(t, lane) + a.cnt[(int64_t)lane * a.nblk + blk];
+    }
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e) cd[e * MGS_WAVE + lane] = c[e];
+    wave_order();
+    // ---- steps and ranks of the tile's boundaries (the last one leads out of it)
+    int d[RH_ROUNDS], rank[RH_ROUNDS];
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e) {
+        const int j = e * MGS_WAVE + lane;
+        const uint64_t nx = j + 1 < n ? cd[j + 1] : after;
+        const bool valid = j + 1 < n || (j + 1 == n && s + n < a.N);
+        d[e] = valid ? merge_step(c[e], nx, bits) : RH_STEPS - 1;
+        rank[e] = bin_rank(valid, d[e], hist[wave], lane);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e) {
+        int r = base[d[e]] + rank[e];
+        for (int w = 0; w < wave; ++w) r += (int)hist[w][d[e]];
+        ac[wave][e * MGS_WAVE + lane] = r;
+    }
+    // ---- the run each boundary's merge joins, by binary search in the tile's
+    // codes, and whether it lies inside the tile
+    uint32_t run[RH_ROUNDS];
+    uint64_t merged[RH_ROUNDS];
+    int mrank[RH_ROUNDS];
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e) {
+        const int j = e * MGS_WAVE + lane;
+        const int sh = d[e] + 1;  // <= 63 for a step that merges
+        const uint64_t lo = d[e] < RH_STEPS - 1 ? (c[e] >> sh) << sh : 0ull;
+        const uint64_t hi = d[e] < RH_STEPS - 1 ? lo + (1ull << sh) : 0ull;
+        int L = min(j, RH_TILE - 1), R = min(j + 1, RH_TILE - 1);
+#pragma unroll
+        for (int o = RH_TILE / 2; o >= 1; o >>= 1) {
+            const int pl = max(L - o, 0), pr = min(R + o, RH_TILE - 1);
+            const uint64_t cl = cd[pl], cr = cd[pr];
+            if (L - o >= 0 && cl >= lo) L = pl;
+            if (R + o < n && cr < hi) R = pr;
+        }
+        const bool left = L > 0 || s == 0 || before < lo;
+        const bool right = R < n - 1 || s + n >= a.N || after >= hi;
+        const bool m = j + 1 < n && d[e] < RH_STEPS - 1 && left && right;
+        run[e] = (uint32_t)j | ((uint32_t)L << 8) | ((uint32_t)R << 16);
+        merged[e] = __builtin_amdgcn_ballot_w64(m);
+        mrank[e] = bin_rank(m, d[e], mcnt[wave], lane);
+    }
+    const int msize = (int)mcnt[wave][lane];              // lane b: merges of step b
+    const int mstart = wave_exclusive(msize, lane);
+    const uint64_t steps = __builtin_amdgcn_ballot_w64(msize > 0);
+    wave_order();
+    mcnt[wave][lane] = (uint32_t)mstart;
+    wave_order();
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e)
+        if ((merged[e] >> lane) & 1ull) pk[wave][mcnt[wave][d[e]] + mrank[e]] = run[e];
+    const int nm = __popcll(merged[0]) + __popcll(merged[1]) + __popcll(merged[2]) + __popcll(merged[3]);
+    static_assert(RH_ROUNDS == 4, "four masks");
+    // ---- the nodes that are left: leaf j starts one unless boundary j - 1 merged
+    int live = 0;
+    {
+        uint64_t carry = 0;
+#pragma unroll
+        for (int e = 0; e < RH_ROUNDS; ++e) {
+            const int j = e * MGS_WAVE + lane;
+            const uint64_t sm = ~((merged[e] << 1) | carry) & __builtin_amdgcn_ballot_w64(j < n);
+            carry = merged[e] >> 63;
+            const int at = live + __popcll(sm & lanes_below(lane));
+            const bool starts = (sm >> lane) & 1ull;
+            if (starts) leaf_of[wave][at] = (uint8_t)j;
+            if (MODE != RH_INVERSE && tile < a.lev[0].lists) {
+                const int64_t o = tile * a.stride;
+                if (starts && at < a.stride) a.lev[0].first[o + at] = (int32_t)(s + j);
+                // the node that ends at this boundary
+                const int upto = at + (int)starts - 1;
+                if (j < n && !((merged[e] >> lane) & 1ull) && upto >= 0 && upto < a.stride)
+                    a.lev[0].ac[o + upto] = ac[wave][j];
+            }
+            live += __popcll(sm);
+        }
+        live = min(live, a.stride);
+        if (MODE != RH_INVERSE && lane == 0 && tile < a.lev[0].lists) a.lev[0].cnt[tile] = live;
+    }
+    if (MODE == RH_STRUCTURE || n == 0) return;
+    // ---- values, RH_CH channels at a time
+    double* v = val[wave];
+    for (int k = 0; k < nchunk; ++k) {
+        const int k0 = chunk_first(a.C, nchunk, k), nch = chunk_size(a.C, nchunk, k);
+        wave_order();
+        if (MODE == RH_FORWARD) {
+#pragma unroll
+            for (int cc = 0; cc < RH_CH; ++cc)
+#pragma unroll
+                for (int e = 0; e < RH_ROUNDS; ++e) v[cc * RH_VS + e * MGS_WAVE + lane] = (double)x[cc][e];
+            if (k + 1 < nchunk) load_chunk(k + 1);
+        } else {
+            // each merge's coefficient in the slot of its second node, the
+            // nodes' values in theirs (all loads issued before the first is used)
+            float hx[RH_CH][RH_ROUNDS];
+            int dst[RH_ROUNDS];
+#pragma unroll
+            for (int e = 0; e < RH_ROUNDS; ++e) {
+                const int q = e * MGS_WAVE + lane;
+                const int i = q < nm ? (int)(pk[wave][q] & 255u) : 0;
+                dst[e] = q < nm ? i + 1 : -1;
+                const int64_t p = q < nm ? 1 + (int64_t)ac[wave][i] : 0;
+#pragma unroll
+                for (int cc = 0; cc < RH_CH; ++cc)
+                    hx[cc][e] = a.coef_in[(int64_t)(k0 + min(cc, nch - 1)) * a.ld + p];
+            }
+            for (int t = lane; t < live; t += MGS_WAVE) {
+                double rv[RH_CH];
+#pragma unroll
+                for (int cc = 0; cc < RH_CH; ++cc) {
+                    const int ch = k0 + min(cc, nch - 1);
+                    rv[cc] = a.top == 0 ? (double)a.coef_in[(int64_t)ch * a.ld]
+                                        : a.lev[0].rows[(tile * a.stride + t) * a.C + ch];
+                }
+                const int j = leaf_of[wave][t];
+#pragma unroll
+                for (int cc = 0; cc < RH_CH; ++cc) v[cc * RH_VS + j] = rv[cc];
+            }
+#pragma unroll
+            for (int e = 0; e < RH_ROUNDS; ++e)
+                if (dst[e] >= 0)
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc) v[cc * RH_VS + dst[e]] = (double)hx[cc][e];
+        }
+        wave_order();
+        // ---- the steps.  Lanes over (merge, channel) pairs, channel fastest;
+        // the first 64 pairs of the next step get their weights while this
+        // step's values are on their way (only the values depend on it).
+        struct Pair {
+            int va, vb;
+            double s1, s2, sw, y;
+        };
+        const float inch = 1.0f / (float)nch;
+        auto weights = [&](int m0, int q, int cc) {
+            const uint32_t w = pk[wave][m0 + q];
+            const int i = (int)(w & 255u), L = (int)((w >> 8) & 255u), R = (int)((w >> 16) & 255u);
+            const int w1 = i - L + 1, w2 = R - i;
+            Pair r;
+            r.va = cc * RH_VS + L;
+            r.vb = cc * RH_VS + i + 1;
+            r.s1 = sq[w1];
+            r.s2 = sq[w2];
+            r.sw = sq[w1 + w2];
+            r.y = inv[w1 + w2];
+            return r;
+        };
+        auto merge = [&](const Pair& r) {
+            const double x1 = v[r.va], x2 = v[r.vb];
+            double lo, hi;
+            if (MODE == RH_FORWARD) {
+                lo = quotient(r.s1 * x1 + r.s2 * x2, r.sw, r.y);
+                hi = quotient(r.s1 * x2 - r.s2 * x1, r.sw, r.y);
+            } else {
+                lo = quotient(r.s1 * x1 - r.s2 * x2, r.sw, r.y);
+                hi = quotient(r.s2 * x1 + r.s1 * x2, r.sw, r.y);
+            }
+            v[r.va] = lo;
+            v[r.vb] = hi;
+        };
+        auto split = [&](int p, int& q, int& cc) {  // p / nch, p % nch (p < 2^11)
+            q = (int)(((float)p + 0.5f) * inch);
+            cc = p - q * nch;
+        };
+        int q0, cc0;
+        split(lane, q0, cc0);
+        uint64_t todo = steps;
+        int m0 = 0, m = 0;
+        auto next_step = [&]() {
+            const int b = MODE == RH_FORWARD ? __builtin_ctzll(todo) : 63 - __builtin_clzll(todo);
+            todo &= ~(1ull << b);
+            m0 = __builtin_amdgcn_readlane(mstart, b);
+            m = __builtin_amdgcn_readlane(msize, b);
+        };
+        Pair cur{};
+        if (todo) {
+            next_step();
+            if (q0 < m) cur = weights(m0, q0, cc0);
+        }
+        while (m > 0) {
+            const int pm0 = m0, pm = m;
+            const Pair now = cur;
+            m = 0;
+            if (todo) {
+                next_step();
+                if (q0 < m) cur = weights(m0, q0, cc0);
+            }
+            if (q0 < pm) merge(now);
+            for (int p = lane + MGS_WAVE; p < pm * nch; p += MGS_WAVE) {
+                int q, cc;
+                split(p, q, cc);
+                merge(weights(pm0, q, cc));
+            }
+            wave_order();
+        }
+        if (MODE == RH_FORWARD) {
+            // the next chunk's attributes have had the steps' time to arrive:
+            // waited for here, they are not waited for behind the stores below
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+            // coefficients in step order: runs of consecutive AC indices per channel
+#pragma unroll
+            for (int e = 0; e < RH_ROUNDS; ++e) {
+                const int q = e * MGS_WAVE + lane;
+                if (q < nm) {
+                    const int i = (int)(pk[wave][q] & 255u);
+                    const int64_t p = 1 + (int64_t)ac[wave][i];
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc)
+                        if (cc < nch) a.coef[(int64_t)(k0 + cc) * a.ld + p] = (float)v[cc * RH_VS + i + 1];
+                }
+            }
+            for (int t = lane; t < live; t += MGS_WAVE) {
+                const int j = leaf_of[wave][t];
+#pragma unroll
+                for (int cc = 0; cc < RH_CH; ++cc) {
+                    const double r = v[cc * RH_VS + j];
+                    if (cc >= nch) continue;
+                    if (a.top == 0) a.coef[(int64_t)(k0 + cc) * a.ld] = (float)r;  // the root: DC
+                    else a.lev[0].rows[(tile * a.stride + t) * a.C + k0 + cc] = r;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < RH_ROUNDS; ++e) {
+                const int j = e * MGS_WAVE + lane;
+                if (j < n)
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc)
+                        if (cc < nch) a.attr_out[(int64_t)(k0 + cc) * a.ld + s + j] = (float)v[cc * RH_VS + j];
+            }
+        }
+    }
+}
+
+// One group of an upper level: the nodes of RH_GROUP lists of the level below,
+// as above but with nodes in place of leaves.  Its arrays lie in LDS for up to
+// CAP nodes, else (BIG: codes whose trees are combs) in the workspace, with
+// the values worked on in place, in the rows of the level below.  The block is
+// one wavefront.
+struct UpperArrays {
+    uint64_t* code;
+    int32_t *first, *ac, *row, *left, *right, *rank, *order;  // first has one entry more
+};
+constexpr int RH_BIG_ARRAYS = 7;
+
+template <int MODE, bool BIG, int CAP>
+__device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t g, int n, const UpperArrays& u,
+                                           int my_pre, uint32_t* h, double* v, int k_first, int k_step) {
+    const RahtLevel& in = a.lev[level - 1];
+    const RahtLevel& out = a.lev[level];
+    const int lane = threadIdx.x;
+    const int bits = 3 * a.depth;
+    const bool root = level == a.top;
+    // ---- the lists, one after the other: node j of the group is node
+    // j - pre of the list whose prefix covers it
+    const int64_t list0 = g * RH_GROUP;
+    int pre[RH_GROUP];
+#pragma unroll
+    for (int t = 0; t < RH_GROUP; ++t) pre[t] = __builtin_amdgcn_readlane(my_pre, t);
+    int64_t span = RH_TILE;  // leaves of a group of this level
+    for (int l = 0; l < level; ++l) span *= RH_GROUP;
+    const int64_t end = min(a.N, (g + 1) * span);
+    const uint64_t after = a.codes[min(end, a.N - 1)];
+    h[lane] = 0u;
+    for (int j0 = 0; j0 < n; j0 += RH_TILE) {
+        int at[RH_ROUNDS], fi[RH_ROUNDS], ai[RH_ROUNDS];
+        uint64_t co[RH_ROUNDS];
+#pragma unroll
+        for (int e = 0; e < RH_ROUNDS; ++e) {
+            const int j = min(j0 + e * MGS_WAVE + lane, n - 1);
+            int t = 0, p = 0;
+#pragma unroll
+            for (int l = 1; l < RH_GROUP; ++l)
+                if (j >= pre[l]) {
+                    t = l;
+                    p = pre[l];
+                }
+            at[e] = (int)((list0 + t) * a.stride) + j - p;
+            fi[e] = in.first[at[e]];
+            ai[e] = in.ac[at[e]];
+        }
+#pragma unroll
+        for (int e = 0; e < RH_ROUNDS; ++e) co[e] = a.codes[fi[e]];
+#pragma unroll
+        for (int e = 0; e < RH_ROUNDS; ++e) {
+            const int j = j0 + e * MGS_WAVE + lane;
+            if (j < n) {
+                u.first[j] = fi[e];
+                u.ac[j] = ai[e];
+                u.row[j] = at[e];
+                u.code[j] = co[e];
+            }
+        }
+    }
+    if (lane == 0) u.first[n] = (int32_t)end;
+    __syncthreads();
+    const int64_t start = u.first[0];
+    const uint64_t before = a.codes[max(start - 1, (int64_t)0)];
+    // ---- each boundary's run; the merges inside the group, ranked in their step
+    int top = 1;
+    while (2 * top < n) top *= 2;
+    for (int j0 = 0; j0 < n; j0 += MGS_WAVE) {
+        const int j = j0 + lane;
+        bool m = false;
+        int d = RH_STEPS - 1;
+        if (j + 1 < n) {
+            const uint64_t c0 = u.code[j];
+            d = merge_step(c0, u.code[j + 1], bits);
+            if (d < RH_STEPS - 1) {
+                const uint64_t lo = (c0 >> (d + 1)) << (d + 1), hi = lo + (1ull << (d + 1));
+                int L = j, R = j + 1;
+                for (int o = top; o >= 1; o >>= 1) {
+                    if (L - o >= 0 && u.code[L - o] >= lo) L -= o;
+                    if (R + o < n && u.code[R + o] < hi) R += o;
+                }
+                m = (L > 0 || start == 0 || before < lo) && (R < n - 1 || end >= a.N || after >= hi);
+                u.left[j] = L;
+                u.right[j] = R;
+            }
+        }
+        const int r = bin_rank(m, d, h, lane);
+        if (j < n) u.rank[j] = m ? (d << 16) | r : -1;  // -1: no merge here
+    }
+    __syncthreads();
+    const int msize = (int)h[lane];  // lane b: merges of step b
+    const int mstart = wave_exclusive(msize, lane);
+    const uint64_t steps = __builtin_amdgcn_ballot_w64(msize > 0);
+    const int nm = __builtin_amdgcn_readlane(mstart + msize, MGS_WAVE - 1);
+    __syncthreads();
+    h[lane] = (uint32_t)mstart;
+    __syncthreads();
+    for (int j = lane; j < n; j += MGS_WAVE) {
+        const int r = u.rank[j];
+        if (r >= 0) u.order[h[r >> 16] + (r & 0xFFFF)] = j;
+    }
+    // ---- the nodes that are left: fn(j, slot) for each
+    auto for_live = [&](auto fn) {
+        int seen = 0;
+        for (int j0 = 0; j0 < n; j0 += MGS_WAVE) {
+            const int j = j0 + lane;
+            const bool starts = j < n && !(j > 0 && u.rank[j - 1] >= 0);
+            const uint64_t sm = __builtin_amdgcn_ballot_w64(starts);
+            fn(j, starts, seen + __popcll(sm & lanes_below(lane)));
+            seen += __popcll(sm);
+        }
+        return seen;
+    };
+    if (MODE != RH_INVERSE) {
+        const int64_t o = g * a.stride;
+        const int live = for_live([&](int j, bool starts, int slot) {
+            if (starts && slot < a.stride) out.first[o + slot] = u.first[j];
+            const int upto = slot + (starts ? 1 : 0) - 1;  // the node that ends at boundary j
+            if (j < n && u.rank[j] < 0 && upto >= 0 && upto < a.stride) out.ac[o + upto] = u.ac[j];
+        });
+        if (lane == 0) out.cnt[g] = min(live, a.stride);
+    }
+    if (MODE == RH_STRUCTURE) return;
+    // ---- values
+    const int nchunk = BIG ? 1 : (a.C + RH_CH - 1) / RH_CH;
+    for (int k = k_first; k < nchunk; k += k_step) {
+        const int k0 = chunk_first(a.C, nchunk, k), nch = chunk_size(a.C, nchunk, k);
+        auto value = [&](int cc, int j) -> double& {  // channel k0 + cc of node j
+            if constexpr (BIG) return in.rows[(int64_t)u.row[j] * a.C + k0 + cc];
+            else return v[cc * (CAP + 1) + j];
+        };
+        __syncthreads();
+        if (MODE == RH_FORWARD && !BIG) {  // (all loads issued before the first is used)
+            for (int j0 = 0; j0 < n; j0 += RH_TILE) {
+                double r[RH_ROUNDS][RH_CH];
+#pragma unroll
+                for (int e = 0; e < RH_ROUNDS; ++e) {
+                    const int64_t o = (int64_t)u.row[min(j0 + e * MGS_WAVE + lane, n - 1)] * a.C + k0;
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc) r[e][cc] = in.rows[o + min(cc, nch - 1)];
+                }
+#pragma unroll
+                for (int e = 0; e < RH_ROUNDS; ++e)
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc) value(cc, j0 + e * MGS_WAVE + lane) = r[e][cc];
+            }
+        }
+        if (MODE == RH_INVERSE) {
+            for_live([&](int j, bool starts, int slot) {
+                if (!starts || slot >= a.stride) return;
+                for (int c0 = 0; c0 < nch; c0 += RH_CH) {
+                    double r[RH_CH];
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc) {
+                        const int ch = k0 + min(c0 + cc, nch - 1);
+                        r[cc] = root ? (double)a.coef_in[(int64_t)ch * a.ld]
+                                     : out.rows[(g * a.stride + slot) * a.C + ch];
+                    }
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc)
+                        if (c0 + cc < nch) value(c0 + cc, j) = r[cc];
+                }
+            });
+            for (int q = lane; q < nm; q += MGS_WAVE) {
+                const int j = u.order[q];
+                const int64_t p = 1 + (int64_t)u.ac[j];
+                for (int c0 = 0; c0 < nch; c0 += RH_CH) {
+                    float r[RH_CH];
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc)
+                        r[cc] = a.coef_in[(int64_t)(k0 + min(c0 + cc, nch - 1)) * a.ld + p];
+#pragma unroll
+                    for (int cc = 0; cc < RH_CH; ++cc)
+                        if (c0 + cc < nch) value(c0 + cc, j + 1) = (double)r[cc];
+                }
+            }
+        }
+        __syncthreads();
+        uint64_t todo = steps;
+        while (todo) {
+            const int b = MODE == RH_FORWARD ? __builtin_ctzll(todo) : 63 - __builtin_clzll(todo);
+            todo &= ~(1ull << b);
+            const int m0 = __builtin_amdgcn_readlane(mstart, b);
+            const uint32_t pairs = (uint32_t)__builtin_amdgcn_readlane(msize, b) * (uint32_t)nch;
+            for (uint32_t p = lane; p < pairs; p += MGS_WAVE) {
+                const uint32_t q = p / (uint32_t)nch;
+                const int cc = (int)(p - q * (uint32_t)nch);
+                const int j = u.order[m0 + (int)q];
+                const int L = u.left[j];
+                const double w1 = (double)(u.first[j + 1] - u.first[L]);
+                const double w2 = (double)(u.first[u.right[j] + 1] - u.first[j + 1]);
+                const double s1 = sqrt(w1), s2 = sqrt(w2), sw = sqrt(w1 + w2);
+                double &va = value(cc, L), &vb = value(cc, j + 1);
+                const double x1 = va, x2 = vb;
+                if (MODE == RH_FORWARD) {
+                    va = (s1 * x1 + s2 * x2) / sw;
+                    vb = (s1 * x2 - s2 * x1) / sw;
+                } else {
+                    va = (s1 * x1 - s2 * x2) / sw;
+                    vb = (s2 * x1 + s1 * x2) / sw;
                 }
             }
             __syncthreads();
-            const int nk = std::min(RH_TEAM, a.C - k0);
-            for (int j = threadIdx.x; j < nk * RH_GROUP; j += RH_THREADS) {
-                const int kk = j / RH_GROUP, q = j % RH_GROUP;
-                if (q < ng) a.coef[(int64_t)(k0 + kk) * a.ld + 1 + g0 + q] = hs[kk][q];
-            }
-            __syncthreads();
         }
-    }
-}
-
-// DC coefficients: the value of the root (slot of the first leaf).
-__global__ void raht_dc_kernel(RahtArgs a) {
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < a.C; k += gridDim.x * blockDim.x)
-        a.coef[(int64_t)k * a.ld] = (float)a.val[k];  // slot 0, channel k
-}
-
-// Inverse: the root's value from the DC, then the merges of one step undone
-// (steps in reverse order; the merges of a step are independent).
-__global__ void raht_inv_init_kernel(RahtArgs a) {
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < a.C; k += gridDim.x * blockDim.x)
-        a.val[k] = (double)a.coef_in[(int64_t)k * a.ld];
-}
-
-// The inverse of one step in the same layout: the group's coefficients come
-// in through LDS as runs per channel, a team undoes one merge.
-__global__ __launch_bounds__(RH_THREADS) void raht_unmerge_kernel(RahtArgs a, int s) {
-    __shared__ float hs[RH_TEAM][RH_GROUP];
-    const int64_t b0 = a.ac_base[s], b1 = a.ac_base[s + 1];
-    const int team = threadIdx.x / RH_TEAM, tl = threadIdx.x % RH_TEAM;
-    for (int64_t g0 = b0 + (int64_t)blockIdx.x * RH_GROUP; g0 < b1; g0 += (int64_t)gridDim.x * RH_GROUP) {
-        const int ng = (int)std::min<int64_t>(RH_GROUP, b1 - g0);
-        for (int k0 = 0; k0 < a.C; k0 += RH_TEAM) {
-            const int nk = std::min(RH_TEAM, a.C - k0);
-            for (int j = threadIdx.x; j < nk * RH_GROUP; j += RH_THREADS) {
-                const int kk = j / RH_GROUP, q = j % RH_GROUP;
-                if (q < ng) hs[kk][q] = a.coef_in[(int64_t)(k0 + kk) * a.ld + 1 + g0 + q];
-            }
-            __syncthreads();
-            const int k = k0 + tl;
-            for (int q = team; q < ng; q += RH_TEAMS) {
-                const int64_t p = g0 + q;
-                const int32_t sa = a.pa[p], sb = a.pb[p];
-                const int64_t w1 = a.wa[p], w2 = a.wb[p];
-                if (k < a.C) {
-                    const double s1 = sqrt((double)w1), s2 = sqrt((double)w2), sw = sqrt((double)(w1 + w2));
-                    double* va = a.val + (int64_t)sa * a.C;
-                    const double L = va[k];
-                    const double H = (double)hs[tl][q];
-                    va[k] = (s1 * L - s2 * H) / sw;
-                    a.val[(int64_t)sb * a.C + k] = (s2 * L + s1 * H) / sw;
+        if (MODE == RH_FORWARD) {
+            for_live([&](int j, bool starts, int slot) {
+                if (!starts || slot >= a.stride) return;
+                for (int cc = 0; cc < nch; ++cc) {
+                    if (root) a.coef[(int64_t)(k0 + cc) * a.ld] = (float)value(cc, j);  // DC
+                    else out.rows[(g * a.stride + slot) * a.C + k0 + cc] = value(cc, j);
                 }
+            });
+            for (int q = lane; q < nm; q += MGS_WAVE) {
+                const int j = u.order[q];
+                const int64_t p = 1 + (int64_t)u.ac[j];
+                for (int cc = 0; cc < nch; ++cc) a.coef[(int64_t)(k0 + cc) * a.ld + p] = (float)value(cc, j + 1);
             }
-            __syncthreads();
+        } else if (!BIG) {
+            for (int j = lane; j < n; j += MGS_WAVE)
+                for (int cc = 0; cc < nch; ++cc) in.rows[(int64_t)u.row[j] * a.C + k0 + cc] = value(cc, j);
         }
     }
 }
 
-__global__ __launch_bounds__(RH_THREADS) void raht_store_kernel(RahtArgs a) {
-    __shared__ double t[RH_TILE_C][RH_TILE_N + 1];
-    for (int64_t i0 = (int64_t)blockIdx.x * RH_TILE_N; i0 < a.N; i0 += (int64_t)gridDim.x * RH_TILE_N) {
-        const int nn = (int)std::min<int64_t>(RH_TILE_N, a.N - i0);
-        for (int k0 = 0; k0 < a.C; k0 += RH_TILE_C) {
-            const int nk = std::min(RH_TILE_C, a.C - k0);
-            for (int e = threadIdx.x; e < nk * nn; e += RH_THREADS) {
-                const int n = e / nk, kk = e % nk;
-                t[kk][n] = a.val[(i0 + n) * a.C + k0 + kk];
-            }
-            __syncthreads();
-            for (int e = threadIdx.x; e < nk * RH_TILE_N; e += RH_THREADS) {
-                const int kk = e / RH_TILE_N, n = e % RH_TILE_N;
-                if (n < nn) a.attr_out[(int64_t)(k0 + kk) * a.ld + i0 + n] = (float)t[kk][n];
-            }
-            __syncthreads();
-        }
+// Upper levels: one wavefront per group of RH_GROUP lists and chunk of RH_CH
+// channels (blockIdx.y; few groups are left, so the chunks are spread out and
+// each builds the group's structure again).
+template <int MODE, int CAP>
+__global__ __launch_bounds__(MGS_WAVE) void raht_upper_kernel(RahtArgs a, int level) {
+    static_assert(CAP % RH_TILE == 0, "values are loaded in rounds of RH_TILE nodes");
+    __shared__ double v[RH_CH * (CAP + 1)];
+    __shared__ uint64_t code[CAP];
+    __shared__ int32_t ints[RH_BIG_ARRAYS][CAP + 1];
+    __shared__ uint32_t h[RH_STEPS];
+    const int64_t g = xcd_block(a.lev[level].lists);
+    if (g < 0) return;
+    const RahtLevel& in = a.lev[level - 1];
+    const int64_t list0 = g * RH_GROUP;
+    const int lane = threadIdx.x;
+    const int m = lane < RH_GROUP && list0 + lane < in.lists ? in.cnt[list0 + lane] : 0;
+    const int my_pre = wave_exclusive(m, lane);  // lane t: nodes of the group before list t
+    const int n = __builtin_amdgcn_readlane(my_pre + m, MGS_WAVE - 1);
+    if (n <= CAP) {
+        const UpperArrays u{code, ints[0], ints[1], ints[2], ints[3], ints[4], ints[5], ints[6]};
+        raht_group<MODE, false, CAP>(a, level, g, n, u, my_pre, h, v, blockIdx.y, gridDim.y);
+    } else if (blockIdx.y == 0) {
+        const int64_t o = list0 * a.stride + g;  // one entry more per group
+        const int64_t st = a.big_stride;
+        const UpperArrays u{a.big_code + o,           a.big_i + o,          a.big_i + st + o,
+                            a.big_i + 2 * st + o,     a.big_i + 3 * st + o, a.big_i + 4 * st + o,
+                            a.big_i + 5 * st + o,     a.big_i + 6 * st + o};
+        raht_group<MODE, true, CAP>(a, level, g, n, u, my_pre, h, v, 0, 1);
     }
 }
 
 struct RahtLayout {
-    size_t val, dstep, lb, rb, cnt, tot, ac, pa, pb, wa, wb, total;
-    int nblk, steps;
+    size_t cnt, tot, big_code, big_i, total;
+    size_t lcnt[RH_LEVELS], first[RH_LEVELS], ac[RH_LEVELS], rows[RH_LEVELS];
+    int64_t lists[RH_LEVELS], big_stride;
+    int64_t nblk;
+    int stride, top;
 };
 
 RahtLayout raht_layout(int64_t N, int32_t C, int32_t depth) {
     RahtLayout L;
-    const size_t n = (size_t)std::max<int64_t>(N, 1);
-    L.nblk = (int)((N - 1 + RH_SPAN - 1) / RH_SPAN);
-    L.steps = 3 * depth;
+    std::memset(&L, 0, sizeof(L));
+    L.nblk = std::max<int64_t>(1, (N + RH_SPAN - 1) / RH_SPAN);
+    // a contiguous run of leaves holds at most two maximal subtrees per step
+    L.stride = std::min(128, 6 * depth + 2);
     size_t o = MGS_STATUS_BYTES;
     auto take = [&](size_t bytes) {
         size_t at = o;
         o += mgs_align_up(bytes, 256);
         return at;
     };
-    L.val = take(sizeof(double) * n * (size_t)C);
-    L.dstep = take(n);
-    L.lb = take(sizeof(int32_t) * n);
-    L.rb = take(sizeof(int32_t) * n);
-    L.cnt = take(sizeof(int64_t) * (size_t)RH_BINS * (size_t)std::max(L.nblk, 1));
-    L.tot = take(sizeof(int64_t) * RH_BINS);
-    L.ac = take(sizeof(int64_t) * (RH_BINS + 1));
-    L.pa = take(sizeof(int32_t) * n);
-    L.pb = take(sizeof(int32_t) * n);
-    L.wa = take(sizeof(int64_t) * n);
-    L.wb = take(sizeof(int64_t) * n);
+    L.cnt = take(sizeof(int32_t) * RH_STEPS * (size_t)L.nblk);
+    L.tot = take(sizeof(int32_t) * RH_STEPS);
+    int64_t lists = std::max<int64_t>(1, (N + RH_TILE - 1) / RH_TILE);
+    L.big_stride = lists * L.stride + (lists + RH_GROUP - 1) / RH_GROUP + 1;
+    for (int l = 0; l < RH_LEVELS; ++l) {
+        L.lists[l] = lists;
+        L.top = l;
+        L.lcnt[l] = take(sizeof(int32_t) * (size_t)lists);
+        L.first[l] = take(sizeof(int32_t) * (size_t)lists * L.stride);
+        L.ac[l] = take(sizeof(int32_t) * (size_t)lists * L.stride);
+        if (lists == 1) break;  // the root: its value is the DC coefficient
+        L.rows[l] = take(sizeof(double) * (size_t)lists * L.stride * (size_t)C);
+        lists = (lists + RH_GROUP - 1) / RH_GROUP;
+    }
+    L.big_code = take(sizeof(uint64_t) * (size_t)L.big_stride);
+    L.big_i = take(sizeof(int32_t) * RH_BIG_ARRAYS * (size_t)L.big_stride);
     L.total = o;
     return L;
-}
-
-unsigned rh_grid(int64_t n) {
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 4096));
-}
-
-// Leaf values (forward) and the merge structure: every merge's step, slots
-// and weights at its AC index.
-int raht_structure(RahtArgs& a, const RahtLayout& L, hipStream_t s) {
-    hipLaunchKernelGGL(raht_init_kernel, dim3(rh_grid(a.N)), dim3(256), 0, s, a);
-    if (a.values) hipLaunchKernelGGL(raht_load_kernel, dim3(rh_grid(a.N / 4 + 1)), dim3(RH_THREADS), 0, s, a);
-    if (L.nblk > 0) {
-        hipLaunchKernelGGL(raht_count_kernel, dim3(L.nblk), dim3(RH_THREADS), 0, s, a);
-        hipLaunchKernelGGL(raht_bounds_kernel, dim3(rh_grid(a.N - 1)), dim3(256), 0, s, a);
-    }
-    hipLaunchKernelGGL(raht_scan_kernel, dim3(RH_BINS), dim3(RH_THREADS), 0, s, a);
-    if (L.nblk > 0) hipLaunchKernelGGL(raht_pairs_kernel, dim3(L.nblk), dim3(RH_THREADS), 0, s, a);
-    return mgs_last_launch();
 }
 
 int raht_setup(RahtArgs& a, RahtLayout& L, const uint64_t* codes, int64_t N, int32_t C, int64_t ld,
@@ -458,21 +850,44 @@ int raht_setup(RahtArgs& a, RahtLayout& L, const uint64_t* codes, int64_t N, int
     a.C = C;
     a.depth = depth;
     a.ld = ld;
-    a.val = (double*)(ws + L.val);
-    a.dstep = (uint8_t*)(ws + L.dstep);
-    a.lb = (int32_t*)(ws + L.lb);
-    a.rb = (int32_t*)(ws + L.rb);
-    a.cnt = (int64_t*)(ws + L.cnt);
-    a.tot = (int64_t*)(ws + L.tot);
-    a.ac_base = (int64_t*)(ws + L.ac);
-    a.pa = (int32_t*)(ws + L.pa);
-    a.pb = (int32_t*)(ws + L.pb);
-    a.wa = (int64_t*)(ws + L.wa);
-    a.wb = (int64_t*)(ws + L.wb);
+    a.cnt = (int32_t*)(ws + L.cnt);
+    a.tot = (int32_t*)(ws + L.tot);
+    a.big_code = (uint64_t*)(ws + L.big_code);
+    a.big_i = (int32_t*)(ws + L.big_i);
+    a.big_stride = L.big_stride;
     a.status = (mgs_status_block*)ws;
-    a.nblk = L.nblk;
+    a.nblk = (int32_t)L.nblk;
+    a.stride = L.stride;
+    a.top = L.top;
+    for (int l = 0; l <= L.top; ++l) {
+        a.lev[l].cnt = (int32_t*)(ws + L.lcnt[l]);
+        a.lev[l].first = (int32_t*)(ws + L.first[l]);
+        a.lev[l].ac = (int32_t*)(ws + L.ac[l]);
+        a.lev[l].rows = (double*)(ws + L.rows[l]);
+        a.lev[l].lists = (int32_t)L.lists[l];
+    }
     return MGS_OK;
 }
+
+// Status reset and the AC indices' counts.
+int raht_counts(RahtArgs& a, hipStream_t s) {
+    int rc = mgs_fill<uint32_t>((uint32_t*)a.status, 64, 0u, s);
+    if (rc) return rc;
+    hipLaunchKernelGGL(raht_count_kernel, dim3(a.nblk), dim3(RH_THREADS), 0, s, a);
+    hipLaunchKernelGGL(raht_scan_kernel, dim3(RH_STEPS), dim3(RH_SCAN_THREADS), 0, s, a);
+    return mgs_last_launch();
+}
+
+template <int MODE>
+void raht_upper(const RahtArgs& a, int level, unsigned chunks, hipStream_t s) {
+    const dim3 grid(xcd_grid(a.lev[level].lists), chunks);
+    if (level == 1)
+        hipLaunchKernelGGL((raht_upper_kernel<MODE, RH_CAP1>), grid, dim3(MGS_WAVE), 0, s, a, level);
+    else
+        hipLaunchKernelGGL((raht_upper_kernel<MODE, RH_CAP2>), grid, dim3(MGS_WAVE), 0, s, a, level);
+}
+
+unsigned raht_chunks(int32_t C) { return (unsigned)std::min(65535, (C + RH_CH - 1) / RH_CH); }
 
 }  // namespace
 }  // namespace mgs
@@ -493,13 +908,11 @@ extern "C" int mgs_raht_forward(const uint64_t* d_codes, int64_t N, int32_t C, i
     hipStream_t s = (hipStream_t)stream;
     a.attr = d_attr;
     a.coef = d_coef;
-    a.values = 1;
-    rc = mgs_fill<uint32_t>((uint32_t*)d_ws, 64, 0u, s);
-    if (!rc) rc = raht_structure(a, L, s);
+    rc = raht_counts(a, s);
     if (rc) return rc;
-    for (int st = 0; st < L.steps; ++st)
-        hipLaunchKernelGGL(raht_merge_kernel, dim3(rh_grid(N / 2 + 1)), dim3(RH_THREADS), 0, s, a, st);
-    hipLaunchKernelGGL(raht_dc_kernel, dim3(1), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(raht_leaf_kernel<RH_FORWARD>, dim3(xcd_grid(a.nblk)), dim3(RH_THREADS), 0, s, a);
+    for (int l = 1; l <= a.top; ++l)
+        raht_upper<RH_FORWARD>(a, l, raht_chunks(C), s);
     return mgs_last_launch();
 }
 
@@ -514,13 +927,14 @@ extern "C" int mgs_raht_inverse(const uint64_t* d_codes, int64_t N, int32_t C, i
     hipStream_t s = (hipStream_t)stream;
     a.coef_in = d_coef;
     a.attr_out = d_attr;
-    a.values = 0;
-    rc = mgs_fill<uint32_t>((uint32_t*)d_ws, 64, 0u, s);
-    if (!rc) rc = raht_structure(a, L, s);
+    rc = raht_counts(a, s);
     if (rc) return rc;
-    hipLaunchKernelGGL(raht_inv_init_kernel, dim3(1), dim3(64), 0, s, a);
-    for (int st = L.steps - 1; st >= 0; --st)
-        hipLaunchKernelGGL(raht_unmerge_kernel, dim3(rh_grid(N / 2 + 1)), dim3(RH_THREADS), 0, s, a, st);
-    hipLaunchKernelGGL(raht_store_kernel, dim3(rh_grid(N / 4 + 1)), dim3(RH_THREADS), 0, s, a);
+    // the lists of every level from the leaves up, then the values from the root down
+    if (a.top > 0) hipLaunchKernelGGL(raht_leaf_kernel<RH_STRUCTURE>, dim3(xcd_grid(a.nblk)), dim3(RH_THREADS), 0, s, a);
+    for (int l = 1; l < a.top; ++l)
+        raht_upper<RH_STRUCTURE>(a, l, 1, s);
+    for (int l = a.top; l >= 1; --l)
+        raht_upper<RH_INVERSE>(a, l, raht_chunks(C), s);
+    hipLaunchKernelGGL(raht_leaf_kernel<RH_INVERSE>, dim3(xcd_grid(a.nblk)), dim3(RH_THREADS), 0, s, a);
     return mgs_last_launch();
 }
