@@ -38,13 +38,17 @@
 // the root of 8 million leaves.  The inverse builds the lists bottom-up without
 // values and undoes the merges level by level from the root.
 //
-// What bounds it: the transform reads and writes every attribute once (0.89 GB
-// at 5.3e6 x 20, 0.19 ms at the rate of a copy); the leaf level's FP64 issue
-// (two corrected quotients per merge and channel) and the chain of about 20
-// steps per tile, hidden by other wavefronts, come close behind.  Run as one
+// What bounds it, at 5.3e6 x 20 on an MI355X: the leaf level (0.40 ms of 0.58)
+// reads and writes every attribute once (0.93 GB by the counters, 0.19 ms at
+// the rate of a copy) and adds the steps' FP64 and LDS work, half of which its
+// 16 wavefronts per CU do not hide (0.29 ms without the steps; with 12 per CU,
+// 4 wavefronts per block, 0.62 ms in all); the upper levels are chains of
+// about 20 steps each (0.17 ms).  Tiles of 128 leaves and 10 channels measured
+// 0.69 ms against 0.62, of 64 leaves and 20 channels 0.84: fewer steps per
+// channel, but twice and four times the nodes for the upper levels.  Run as one
 // launch per step over node values in HBM (42 dependent launches, rows of both
 // nodes fetched from all over the array) the forward took 1.95 ms at 5.3e6 x 20
-// and the inverse 0.58 ms at 1e6 x 20.
+// and the inverse 0.58 ms at 1e6 x 20, which is 0.20 ms now.
 #include <algorithm>
 #include <cstring>
 
@@ -56,11 +60,12 @@ namespace {
 constexpr int RH_STEPS = 64;                         // bins of merge steps (3 depth <= 63; 63: never merged)
 constexpr int RH_TILE = 256;                         // leaves per wavefront at the leaf level
 constexpr int RH_ROUNDS = RH_TILE / MGS_WAVE;
-constexpr int RH_WAVES = 4;
+constexpr int RH_WAVES = 8;
 constexpr int RH_THREADS = RH_WAVES * MGS_WAVE;
 constexpr int RH_SPAN = RH_TILE * RH_WAVES;          // leaves per block of the counts
-constexpr int RH_MAX_BLOCKS = 8192;                  // N <= RH_SPAN * RH_MAX_BLOCKS
-constexpr int RH_CH = 4;                             // channels in LDS at a time (48 KB per block: three per CU)
+constexpr int RH_MAX_BLOCKS = 4096;                  // N <= RH_SPAN * RH_MAX_BLOCKS
+constexpr int RH_CH = 4;                             // channels in LDS at a time (77 KB per block: two per CU)
+constexpr int RH_UCH = 4;                            // the same at the upper levels
 constexpr int RH_VS = RH_TILE + 1;                   // row stride of the values (channels in different banks)
 constexpr int RH_GROUP = 16;                         // lists that an upper level joins
 constexpr int RH_CAP1 = 256;                          // nodes of a group in LDS at the first upper level,
@@ -226,23 +231,27 @@ __global__ __launch_bounds__(RH_SCAN_THREADS) void raht_scan_kernel(RahtArgs a) 
     if (threadIdx.x == 0) a.tot[blockIdx.x] = total;
 }
 
-// n / s, correctly rounded, with y = RN(1 / s): RN(n y) is within 1.5 ulp, one
-// correction by the exact FMA remainder makes it faithful and a second one the
-// correctly rounded quotient (Markstein's theorem), five operations instead of
-// the division's dozen.  Zeros, non-finite values and magnitudes whose
-// remainders could leave the normal range take the division.
-__device__ __forceinline__ double quotient(double n, double s, double y) {
-    double q = n * y;
-    const bool odd = !(fabs(q) > 0x1p-900 && fabs(q) < 0x1p900);
-    double r = __builtin_fma(-s, q, n);
-    q = __builtin_fma(r, y, q);
-    r = __builtin_fma(-s, q, n);
-    q = __builtin_fma(r, y, q);
-    if (__builtin_amdgcn_ballot_w64(odd)) {  // (rare; the empty asm keeps it a branch)
-        asm volatile("" : "+v"(n));
-        if (odd) q = n / s;
+// n1 / s and n2 / s, correctly rounded, with y = RN(1 / s): RN(n y) is within
+// 1.5 ulp, one correction by the exact FMA remainder makes it faithful and a
+// second one the correctly rounded quotient (Markstein's theorem), five
+// operations instead of the division's dozen.  Zeros, non-finite values and
+// magnitudes whose remainders could leave the normal range take the division.
+__device__ __forceinline__ void quotients(double n1, double n2, double s, double y, double& q1, double& q2) {
+    q1 = n1 * y;
+    q2 = n2 * y;
+    const bool odd = !(fabs(q1) > 0x1p-900 && fabs(q1) < 0x1p900 && fabs(q2) > 0x1p-900 && fabs(q2) < 0x1p900);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        q1 = __builtin_fma(__builtin_fma(-s, q1, n1), y, q1);
+        q2 = __builtin_fma(__builtin_fma(-s, q2, n2), y, q2);
     }
-    return q;
+    if (__builtin_amdgcn_ballot_w64(odd)) {  // (rare; the empty asm keeps it a branch)
+        asm volatile("" : "+v"(n1), "+v"(n2));
+        if (odd) {
+            q1 = n1 / s;
+            q2 = n2 / s;
+        }
+    }
 }
 
 // Blocks go round-robin over the XCDs: each XCD takes a contiguous run of
@@ -256,18 +265,25 @@ __device__ __forceinline__ int64_t xcd_block(int64_t nblk) {
 }
 unsigned xcd_grid(int64_t nblk) { return (unsigned)((nblk + RH_XCDS - 1) / RH_XCDS * RH_XCDS); }
 
-// Leaf level: one wavefront per tile of RH_TILE leaves.
+// Leaf level: one wavefront per tile of RH_TILE leaves.  16 wavefronts per CU
+// (LDS and registers allow no more): what only the structure needs (the tile's
+// codes, counters, AC indices) lies in the LDS that holds the values later.
 template <int MODE>
-__global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
+__global__ __launch_bounds__(RH_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+void raht_leaf_kernel(RahtArgs a) {
     __shared__ double val[RH_WAVES][RH_CH * RH_VS];
-    __shared__ double sq[RH_TILE + 1], inv[RH_TILE + 1];  // sqrt(w) and RN(1 / sqrt(w))
-    __shared__ uint32_t hist[RH_WAVES][RH_STEPS], mcnt[RH_WAVES][RH_STEPS];
-    __shared__ int32_t base[RH_STEPS];                    // first AC index of each step in this block
-    __shared__ int32_t ac[RH_WAVES][RH_TILE];
-    __shared__ uint32_t pk[RH_WAVES][RH_TILE];            // the tile's merges in step order: i | L << 8 | R << 16
-    __shared__ uint8_t leaf_of[RH_WAVES][RH_TILE];        // first leaf of each node that is left
+    __shared__ double sq[RH_TILE], inv[RH_TILE];  // sqrt(w) and RN(1 / sqrt(w)) at w - 1
+    __shared__ int32_t base[RH_STEPS];            // first AC index of each step in this block
+    // the tile's merges in step order: first node's slot, second node's, and
+    // their weights less one, a byte each
+    __shared__ uint32_t pk[RH_WAVES][RH_TILE];
     const int tid = threadIdx.x;
     const int lane = tid & (MGS_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / MGS_WAVE);
+    uint64_t* cd = (uint64_t*)val[wave];                               // [RH_TILE]
+    uint32_t* mcnt = (uint32_t*)(cd + RH_TILE);                        // [RH_STEPS]
+    int32_t* ac = (int32_t*)(mcnt + RH_STEPS);                         // [RH_TILE]
+    auto hist = [&](int w) { return (uint32_t*)(val[w] + 2 * RH_TILE); };  // [RH_STEPS]
+    static_assert(RH_CH * RH_VS >= 2 * RH_TILE + RH_STEPS / 2 && RH_TILE % 64 == 0, "scratch beside the values");
     const int64_t blk = xcd_block(a.nblk);
     if (blk < 0) return;
     const int64_t tile = blk * RH_WAVES + wave;
@@ -275,13 +291,12 @@ __global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
     const int n = (int)max((int64_t)0, min((int64_t)RH_TILE, a.N - s));
     const int bits = 3 * a.depth;
     if (MODE != RH_STRUCTURE)
-        for (int k = tid; k <= RH_TILE; k += RH_THREADS) {
-            sq[k] = sqrt((double)k);
-            inv[k] = k ? 1.0 / sq[k] : 0.0;
+        for (int k = tid; k < RH_TILE; k += RH_THREADS) {
+            sq[k] = sqrt((double)(k + 1));
+            inv[k] = 1.0 / sq[k];
         }
-    hist[wave][lane] = 0u;
-    mcnt[wave][lane] = 0u;
-    uint64_t* cd = (uint64_t*)val[wave];
+    hist(wave)[lane] = 0u;
+    mcnt[lane] = 0u;
     uint64_t c[RH_ROUNDS];
 #pragma unroll
     for (int e = 0; e < RH_ROUNDS; ++e) c[e] = a.codes[min(s + e * MGS_WAVE + lane, a.N - 1)];
@@ -316,15 +331,16 @@ __global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
         const uint64_t nx = j + 1 < n ? cd[j + 1] : after;
         const bool valid = j + 1 < n || (j + 1 == n && s + n < a.N);
         d[e] = valid ? merge_step(c[e], nx, bits) : RH_STEPS - 1;
-        rank[e] = bin_rank(valid, d[e], hist[wave], lane);
+        rank[e] = bin_rank(valid, d[e], hist(wave), lane);
     }
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < RH_ROUNDS; ++e) {
         int r = base[d[e]] + rank[e];
-        for (int w = 0; w < wave; ++w) r += (int)hist[w][d[e]];
-        ac[wave][e * MGS_WAVE + lane] = r;
+        for (int w = 0; w < wave; ++w) r += (int)hist(w)[d[e]];
+        ac[e * MGS_WAVE + lane] = r;
     }
+    __syncthreads();  // every wavefront has read the others' counters
     // ---- the run each boundary's merge joins, by binary search in the tile's
     // codes, and whether it lies inside the tile
     uint32_t run[RH_ROUNDS];
@@ -347,25 +363,33 @@ __global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
         const bool left = L > 0 || s == 0 || before < lo;
         const bool right = R < n - 1 || s + n >= a.N || after >= hi;
         const bool m = j + 1 < n && d[e] < RH_STEPS - 1 && left && right;
-        run[e] = (uint32_t)j | ((uint32_t)L << 8) | ((uint32_t)R << 16);
+        run[e] = (uint32_t)(L & 255) | ((uint32_t)((j + 1) & 255) << 8) | ((uint32_t)((j - L) & 255) << 16) |
+                 ((uint32_t)((R - j - 1) & 255) << 24);
         merged[e] = __builtin_amdgcn_ballot_w64(m);
-        mrank[e] = bin_rank(m, d[e], mcnt[wave], lane);
+        mrank[e] = bin_rank(m, d[e], mcnt, lane);
     }
-    const int msize = (int)mcnt[wave][lane];              // lane b: merges of step b
+    const int msize = (int)mcnt[lane];                    // lane b: merges of step b
     const int mstart = wave_exclusive(msize, lane);
     const uint64_t steps = __builtin_amdgcn_ballot_w64(msize > 0);
     wave_order();
-    mcnt[wave][lane] = (uint32_t)mstart;
+    mcnt[lane] = (uint32_t)mstart;
     wave_order();
 #pragma unroll
     for (int e = 0; e < RH_ROUNDS; ++e)
-        if ((merged[e] >> lane) & 1ull) pk[wave][mcnt[wave][d[e]] + mrank[e]] = run[e];
-    const int nm = __popcll(merged[0]) + __popcll(merged[1]) + __popcll(merged[2]) + __popcll(merged[3]);
-    static_assert(RH_ROUNDS == 4, "four masks");
-    // ---- the nodes that are left: leaf j starts one unless boundary j - 1 merged
+        if ((merged[e] >> lane) & 1ull) pk[wave][mcnt[d[e]] + mrank[e]] = run[e];
+    int nm = 0;
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e) nm += __popcll(merged[e]);
+    // ---- the nodes that are left: leaf j starts one unless boundary j - 1
+    // merged; lane t keeps the first leaf of nodes t and t + 64
     int live = 0;
+    int32_t node0 = 0, node1 = 0;
     {
+        // (the counters' place is free now: a list of the first leaves)
+        uint8_t* leaf_of = (uint8_t*)hist(wave);
+        static_assert(RH_TILE <= 4 * RH_STEPS, "one byte per leaf in the counters' place");
         uint64_t carry = 0;
+        wave_order();
 #pragma unroll
         for (int e = 0; e < RH_ROUNDS; ++e) {
             const int j = e * MGS_WAVE + lane;
@@ -373,21 +397,34 @@ __global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
             carry = merged[e] >> 63;
             const int at = live + __popcll(sm & lanes_below(lane));
             const bool starts = (sm >> lane) & 1ull;
-            if (starts) leaf_of[wave][at] = (uint8_t)j;
+            if (starts) leaf_of[at] = (uint8_t)j;
             if (MODE != RH_INVERSE && tile < a.lev[0].lists) {
                 const int64_t o = tile * a.stride;
                 if (starts && at < a.stride) a.lev[0].first[o + at] = (int32_t)(s + j);
                 // the node that ends at this boundary
                 const int upto = at + (int)starts - 1;
                 if (j < n && !((merged[e] >> lane) & 1ull) && upto >= 0 && upto < a.stride)
-                    a.lev[0].ac[o + upto] = ac[wave][j];
+                    a.lev[0].ac[o + upto] = ac[j];
             }
             live += __popcll(sm);
         }
-        live = min(live, a.stride);
+        wave_order();
+        live = min(live, a.stride);  // (<= 128)
+        if (lane < live) node0 = leaf_of[lane];
+        if (lane + MGS_WAVE < live) node1 = leaf_of[lane + MGS_WAVE];
         if (MODE != RH_INVERSE && lane == 0 && tile < a.lev[0].lists) a.lev[0].cnt[tile] = live;
     }
     if (MODE == RH_STRUCTURE || n == 0) return;
+    // lane's merges in step order, RH_ROUNDS of them: the second node's slot
+    // (0: none) and the coefficient's column
+    int second[RH_ROUNDS];
+    int32_t column[RH_ROUNDS];
+#pragma unroll
+    for (int e = 0; e < RH_ROUNDS; ++e) {
+        const int q = e * MGS_WAVE + lane;
+        second[e] = q < nm ? (int)((pk[wave][q] >> 8) & 255u) : 0;
+        column[e] = q < nm ? 1 + ac[second[e] - 1] : 0;
+    }
     // ---- values, RH_CH channels at a time
     double* v = val[wave];
     for (int k = 0; k < nchunk; ++k) {
@@ -403,34 +440,29 @@ __global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
             // each merge's coefficient in the slot of its second node, the
             // nodes' values in theirs (all loads issued before the first is used)
             float hx[RH_CH][RH_ROUNDS];
-            int dst[RH_ROUNDS];
+            double rv[RH_CH][2];
 #pragma unroll
-            for (int e = 0; e < RH_ROUNDS; ++e) {
-                const int q = e * MGS_WAVE + lane;
-                const int i = q < nm ? (int)(pk[wave][q] & 255u) : 0;
-                dst[e] = q < nm ? i + 1 : -1;
-                const int64_t p = q < nm ? 1 + (int64_t)ac[wave][i] : 0;
+            for (int cc = 0; cc < RH_CH; ++cc) {
+                const int ch = k0 + min(cc, nch - 1);
 #pragma unroll
-                for (int cc = 0; cc < RH_CH; ++cc)
-                    hx[cc][e] = a.coef_in[(int64_t)(k0 + min(cc, nch - 1)) * a.ld + p];
-            }
-            for (int t = lane; t < live; t += MGS_WAVE) {
-                double rv[RH_CH];
+                for (int e = 0; e < RH_ROUNDS; ++e) hx[cc][e] = a.coef_in[(int64_t)ch * a.ld + column[e]];
 #pragma unroll
-                for (int cc = 0; cc < RH_CH; ++cc) {
-                    const int ch = k0 + min(cc, nch - 1);
-                    rv[cc] = a.top == 0 ? (double)a.coef_in[(int64_t)ch * a.ld]
-                                        : a.lev[0].rows[(tile * a.stride + t) * a.C + ch];
+                for (int t = 0; t < 2; ++t) {
+                    const int node = t * MGS_WAVE + lane;
+                    rv[cc][t] = 0.0;
+                    if (node < live)
+                        rv[cc][t] = a.top == 0 ? (double)a.coef_in[(int64_t)ch * a.ld]
+                                               : a.lev[0].rows[(tile * a.stride + node) * a.C + ch];
                 }
-                const int j = leaf_of[wave][t];
-#pragma unroll
-                for (int cc = 0; cc < RH_CH; ++cc) v[cc * RH_VS + j] = rv[cc];
             }
 #pragma unroll
-            for (int e = 0; e < RH_ROUNDS; ++e)
-                if (dst[e] >= 0)
+            for (int cc = 0; cc < RH_CH; ++cc) {
 #pragma unroll
-                    for (int cc = 0; cc < RH_CH; ++cc) v[cc * RH_VS + dst[e]] = (double)hx[cc][e];
+                for (int e = 0; e < RH_ROUNDS; ++e)
+                    if (second[e]) v[cc * RH_VS + second[e]] = (double)hx[cc][e];
+                if (lane < live) v[cc * RH_VS + node0] = rv[cc][0];
+                if (lane + MGS_WAVE < live) v[cc * RH_VS + node1] = rv[cc][1];
+            }
         }
         wave_order();
         // ---- the steps.  Lanes over (merge, channel) pairs, channel fastest;
@@ -440,39 +472,30 @@ __global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
             int va, vb;
             double s1, s2, sw, y;
         };
-        const float inch = 1.0f / (float)nch;
-        auto weights = [&](int m0, int q, int cc) {
-            const uint32_t w = pk[wave][m0 + q];
-            const int i = (int)(w & 255u), L = (int)((w >> 8) & 255u), R = (int)((w >> 16) & 255u);
-            const int w1 = i - L + 1, w2 = R - i;
+        auto weights = [&](int q, int cc) {
+            const uint32_t w = pk[wave][q];
+            const int w1 = (int)((w >> 16) & 255u), w2 = (int)(w >> 24);
             Pair r;
-            r.va = cc * RH_VS + L;
-            r.vb = cc * RH_VS + i + 1;
+            r.va = cc * RH_VS + (int)(w & 255u);
+            r.vb = cc * RH_VS + (int)((w >> 8) & 255u);
             r.s1 = sq[w1];
             r.s2 = sq[w2];
-            r.sw = sq[w1 + w2];
-            r.y = inv[w1 + w2];
+            r.sw = sq[w1 + w2 + 1];
+            r.y = inv[w1 + w2 + 1];
             return r;
         };
         auto merge = [&](const Pair& r) {
             const double x1 = v[r.va], x2 = v[r.vb];
             double lo, hi;
-            if (MODE == RH_FORWARD) {
-                lo = quotient(r.s1 * x1 + r.s2 * x2, r.sw, r.y);
-                hi = quotient(r.s1 * x2 - r.s2 * x1, r.sw, r.y);
-            } else {
-                lo = quotient(r.s1 * x1 - r.s2 * x2, r.sw, r.y);
-                hi = quotient(r.s2 * x1 + r.s1 * x2, r.sw, r.y);
-            }
+            if (MODE == RH_FORWARD)
+                quotients(r.s1 * x1 + r.s2 * x2, r.s1 * x2 - r.s2 * x1, r.sw, r.y, lo, hi);
+            else
+                quotients(r.s1 * x1 - r.s2 * x2, r.s2 * x1 + r.s1 * x2, r.sw, r.y, lo, hi);
             v[r.va] = lo;
             v[r.vb] = hi;
         };
-        auto split = [&](int p, int& q, int& cc) {  // p / nch, p % nch (p < 2^11)
-            q = (int)(((float)p + 0.5f) * inch);
-            cc = p - q * nch;
-        };
-        int q0, cc0;
-        split(lane, q0, cc0);
+        const int q0 = lane / nch, cc0 = lane - q0 * nch;    // the lane's first pair
+        const int dq = MGS_WAVE / nch, dc = MGS_WAVE - dq * nch;  // and what 64 pairs on add to it
         uint64_t todo = steps;
         int m0 = 0, m = 0;
         auto next_step = [&]() {
@@ -481,26 +504,37 @@ __global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
             m0 = __builtin_amdgcn_readlane(mstart, b);
             m = __builtin_amdgcn_readlane(msize, b);
         };
-        Pair cur{};
-        if (todo) {
-            next_step();
-            if (q0 < m) cur = weights(m0, q0, cc0);
-        }
-        while (m > 0) {
+        // one step with the weights in `now`; those of the next step go to `then`
+        auto step = [&](const Pair& now, Pair& then) {
             const int pm0 = m0, pm = m;
-            const Pair now = cur;
             m = 0;
             if (todo) {
                 next_step();
-                if (q0 < m) cur = weights(m0, q0, cc0);
+                if (q0 < m) then = weights(m0 + q0, cc0);
             }
             if (q0 < pm) merge(now);
-            for (int p = lane + MGS_WAVE; p < pm * nch; p += MGS_WAVE) {
-                int q, cc;
-                split(p, q, cc);
-                merge(weights(pm0, q, cc));
+            int q = q0, cc = cc0;
+            for (;;) {
+                q += dq;
+                cc += dc;
+                if (cc >= nch) {
+                    cc -= nch;
+                    ++q;
+                }
+                if (q >= pm) break;
+                merge(weights(pm0 + q, cc));
             }
             wave_order();
+        };
+        Pair pa{}, pb{};
+        if (todo) {
+            next_step();
+            if (q0 < m) pa = weights(m0 + q0, cc0);
+        }
+        while (m > 0) {
+            step(pa, pb);
+            if (m == 0) break;
+            step(pb, pa);
         }
         if (MODE == RH_FORWARD) {
             // the next chunk's attributes have had the steps' time to arrive:
@@ -508,24 +542,24 @@ __global__ __launch_bounds__(RH_THREADS) void raht_leaf_kernel(RahtArgs a) {
             __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
             // coefficients in step order: runs of consecutive AC indices per channel
 #pragma unroll
-            for (int e = 0; e < RH_ROUNDS; ++e) {
-                const int q = e * MGS_WAVE + lane;
-                if (q < nm) {
-                    const int i = (int)(pk[wave][q] & 255u);
-                    const int64_t p = 1 + (int64_t)ac[wave][i];
+            for (int e = 0; e < RH_ROUNDS; ++e)
+                if (second[e]) {
 #pragma unroll
                     for (int cc = 0; cc < RH_CH; ++cc)
-                        if (cc < nch) a.coef[(int64_t)(k0 + cc) * a.ld + p] = (float)v[cc * RH_VS + i + 1];
+                        if (cc < nch)
+                            a.coef[(int64_t)(k0 + cc) * a.ld + column[e]] = (float)v[cc * RH_VS + second[e]];
                 }
-            }
-            for (int t = lane; t < live; t += MGS_WAVE) {
-                const int j = leaf_of[wave][t];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int node = t * MGS_WAVE + lane;
+                if (node >= live) continue;
+                const int j = t ? node1 : node0;
 #pragma unroll
                 for (int cc = 0; cc < RH_CH; ++cc) {
                     const double r = v[cc * RH_VS + j];
                     if (cc >= nch) continue;
                     if (a.top == 0) a.coef[(int64_t)(k0 + cc) * a.ld] = (float)r;  // the root: DC
-                    else a.lev[0].rows[(tile * a.stride + t) * a.C + k0 + cc] = r;
+                    else a.lev[0].rows[(tile * a.stride + node) * a.C + k0 + cc] = r;
                 }
             }
         } else {
@@ -665,7 +699,7 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
     }
     if (MODE == RH_STRUCTURE) return;
     // ---- values
-    const int nchunk = BIG ? 1 : (a.C + RH_CH - 1) / RH_CH;
+    const int nchunk = BIG ? 1 : (a.C + RH_UCH - 1) / RH_UCH;
     for (int k = k_first; k < nchunk; k += k_step) {
         const int k0 = chunk_first(a.C, nchunk, k), nch = chunk_size(a.C, nchunk, k);
         auto value = [&](int cc, int j) -> double& {  // channel k0 + cc of node j
@@ -675,45 +709,45 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
         __syncthreads();
         if (MODE == RH_FORWARD && !BIG) {  // (all loads issued before the first is used)
             for (int j0 = 0; j0 < n; j0 += RH_TILE) {
-                double r[RH_ROUNDS][RH_CH];
+                double r[RH_ROUNDS][RH_UCH];
 #pragma unroll
                 for (int e = 0; e < RH_ROUNDS; ++e) {
                     const int64_t o = (int64_t)u.row[min(j0 + e * MGS_WAVE + lane, n - 1)] * a.C + k0;
 #pragma unroll
-                    for (int cc = 0; cc < RH_CH; ++cc) r[e][cc] = in.rows[o + min(cc, nch - 1)];
+                    for (int cc = 0; cc < RH_UCH; ++cc) r[e][cc] = in.rows[o + min(cc, nch - 1)];
                 }
 #pragma unroll
                 for (int e = 0; e < RH_ROUNDS; ++e)
 #pragma unroll
-                    for (int cc = 0; cc < RH_CH; ++cc) value(cc, j0 + e * MGS_WAVE + lane) = r[e][cc];
+                    for (int cc = 0; cc < RH_UCH; ++cc) value(cc, j0 + e * MGS_WAVE + lane) = r[e][cc];
             }
         }
         if (MODE == RH_INVERSE) {
             for_live([&](int j, bool starts, int slot) {
                 if (!starts || slot >= a.stride) return;
-                for (int c0 = 0; c0 < nch; c0 += RH_CH) {
-                    double r[RH_CH];
+                for (int c0 = 0; c0 < nch; c0 += RH_UCH) {
+                    double r[RH_UCH];
 #pragma unroll
-                    for (int cc = 0; cc < RH_CH; ++cc) {
+                    for (int cc = 0; cc < RH_UCH; ++cc) {
                         const int ch = k0 + min(c0 + cc, nch - 1);
                         r[cc] = root ? (double)a.coef_in[(int64_t)ch * a.ld]
                                      : out.rows[(g * a.stride + slot) * a.C + ch];
                     }
 #pragma unroll
-                    for (int cc = 0; cc < RH_CH; ++cc)
+                    for (int cc = 0; cc < RH_UCH; ++cc)
                         if (c0 + cc < nch) value(c0 + cc, j) = r[cc];
                 }
             });
             for (int q = lane; q < nm; q += MGS_WAVE) {
                 const int j = u.order[q];
                 const int64_t p = 1 + (int64_t)u.ac[j];
-                for (int c0 = 0; c0 < nch; c0 += RH_CH) {
-                    float r[RH_CH];
+                for (int c0 = 0; c0 < nch; c0 += RH_UCH) {
+                    float r[RH_UCH];
 #pragma unroll
-                    for (int cc = 0; cc < RH_CH; ++cc)
+                    for (int cc = 0; cc < RH_UCH; ++cc)
                         r[cc] = a.coef_in[(int64_t)(k0 + min(c0 + cc, nch - 1)) * a.ld + p];
 #pragma unroll
-                    for (int cc = 0; cc < RH_CH; ++cc)
+                    for (int cc = 0; cc < RH_UCH; ++cc)
                         if (c0 + cc < nch) value(c0 + cc, j + 1) = (double)r[cc];
                 }
             }
@@ -765,13 +799,13 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
     }
 }
 
-// Upper levels: one wavefront per group of RH_GROUP lists and chunk of RH_CH
+// Upper levels: one wavefront per group of RH_GROUP lists and chunk of RH_UCH
 // channels (blockIdx.y; few groups are left, so the chunks are spread out and
 // each builds the group's structure again).
 template <int MODE, int CAP>
 __global__ __launch_bounds__(MGS_WAVE) void raht_upper_kernel(RahtArgs a, int level) {
     static_assert(CAP % RH_TILE == 0, "values are loaded in rounds of RH_TILE nodes");
-    __shared__ double v[RH_CH * (CAP + 1)];
+    __shared__ double v[RH_UCH * (CAP + 1)];
     __shared__ uint64_t code[CAP];
     __shared__ int32_t ints[RH_BIG_ARRAYS][CAP + 1];
     __shared__ uint32_t h[RH_STEPS];
@@ -809,7 +843,8 @@ RahtLayout raht_layout(int64_t N, int32_t C, int32_t depth) {
     std::memset(&L, 0, sizeof(L));
     L.nblk = std::max<int64_t>(1, (N + RH_SPAN - 1) / RH_SPAN);
     // a contiguous run of leaves holds at most two maximal subtrees per step
-    L.stride = std::min(128, 6 * depth + 2);
+    // (two nodes per lane at the leaf level)
+    L.stride = std::min(2 * MGS_WAVE, 6 * depth + 2);
     size_t o = MGS_STATUS_BYTES;
     auto take = [&](size_t bytes) {
         size_t at = o;
@@ -887,7 +922,7 @@ void raht_upper(const RahtArgs& a, int level, unsigned chunks, hipStream_t s) {
         hipLaunchKernelGGL((raht_upper_kernel<MODE, RH_CAP2>), grid, dim3(MGS_WAVE), 0, s, a, level);
 }
 
-unsigned raht_chunks(int32_t C) { return (unsigned)std::min(65535, (C + RH_CH - 1) / RH_CH); }
+unsigned raht_chunks(int32_t C) { return (unsigned)std::min(65535, (C + RH_UCH - 1) / RH_UCH); }
 
 }  // namespace
 }  // namespace mgs
