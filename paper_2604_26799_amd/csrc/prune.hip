@@ -3,23 +3,32 @@
 // Paper: section "Gaussians Pruning" (the reserve ratio tau keeps the most
 // important tau*N Gaussians and cuts the rest).
 //
-// Every Gaussian gets a unique 64-bit key
-//     ck(i) = (desc(imp[i]) << 32) | i
-// where desc() maps floats to uint32 so that larger importance gives a
-// smaller key (-0 and +0 map alike).  The kept set of count k is exactly
-// {i : ck(i) <= thr}, thr being the k-th smallest key, so ties need no
-// special treatment.  thr is found per k by a radix select over six digits
-// (13/11/8 bits of the importance key, then 11/11/10 bits of the index):
-// one histogram pass over the importance per digit, each followed by a tiny
-// per-k kernel that picks the digit holding the k-th key.  Passes after the
-// first only count keys that still match a k's prefix, found through an LDS
-// table indexed by the top digit.  A k whose key is the last of its digit
-// bucket is resolved there (every lower threshold bit set), and a pass with
-// no unresolved k exits at once: without ties across the k-th key the index
-// digits cost nothing.  A compaction then writes each kept set in index
-// order: per-chunk counts, a per-k scan over chunks, and a write pass that
-// ranks kept elements with wavefront ballots; a block of the counting and
-// writing passes takes one chunk and a group of k, sized for ~2048 blocks.
+// Importance maps to a 32-bit key, larger importance to a smaller key (-0 and
+// +0 alike).  The kept set of count k is every key below the k-th smallest, and
+// of the keys equal to it the first ones in index order.
+//
+// Large inputs.  The k-th key of every count comes from a radix select over
+// three digits: a histogram pass over the importance per digit, each of whose
+// blocks first picks the digit before from the finished histogram (redundantly:
+// a launch between the passes costs more).  The first digit has 15 bits, so that
+// few keys share a k's prefix in the second pass, whose bins are too many for
+// the blocks to sum them in LDS: about one global atomic per such key (with 13
+// bits a million of 5.3e6 keys, 100 us; with 15 a quarter of that).  A compaction then
+// writes each kept set in index order: a wavefront owns 1024 consecutive keys,
+// counts them against every threshold (one compare and a mask population count
+// for 64 keys), a scan per k turns the counts into positions, and the wavefront
+// writes its kept indices behind its own running position, without LDS or
+// barriers.  Ties across a threshold are counted beside the smaller keys, and
+// the scan gives them out in index order.  At 5.3e6 keys and 32 counts: 161 us,
+// of which 75 us write the 356 MB of indices (4.7 TB/s) and the three passes
+// take 12, 25 and 16 us, bound by the latency of picking the digits; with
+// three more digits for the index, a select launch per digit and an LDS scan per
+// (chunk, count) in the write it was 356 us.
+//
+// Inputs of up to 65,536 take one kernel: one workgroup per k holds all keys in
+// registers, selects the k-th in LDS and writes the kept set (36 us at n =
+// 50,000 and four counts; the launches of the general path take 52 us, and the
+// 17 of the earlier one took 81).
 #include <algorithm>
 #include <cstring>
 
@@ -28,33 +37,41 @@
 namespace mgs {
 namespace {
 
-constexpr int PR_LEVELS = 6;
-constexpr int PR_BINS = 8192;  // bins of the widest digit
-constexpr int PR_HIST_THREADS = 256;
-constexpr int PR_CHUNK_THREADS = 256;
-constexpr int PR_CHUNK_ROUNDS = 16;
-constexpr int PR_CHUNK = PR_CHUNK_THREADS * PR_CHUNK_ROUNDS;  // elements per compaction block
-// a wide first digit, so that few keys share a k's prefix in the second pass
-// (those are counted with global atomics)
-constexpr int PR_SHIFT[PR_LEVELS] = {51, 40, 32, 21, 10, 0};
-constexpr int PR_BITS[PR_LEVELS] = {13, 11, 8, 11, 11, 10};
+constexpr int PR_BITS0 = 15;                 // first digit: sign, exponent, 6 bits of the significand
+constexpr int PR_BINS0 = 1 << PR_BITS0;
+constexpr int PR_REST = 32 - PR_BITS0;       // bits of the second and third digit
+constexpr int PR_BITS1 = 9, PR_BITS2 = PR_REST - PR_BITS1;
+constexpr int PR_BINS = 1 << PR_BITS1;       // bins of the wider one
+constexpr int PR_LDS_ROWS = 58;              // counts whose histogram fits in LDS (the others add to global bins)
+constexpr int PR_THREADS = 1024;             // histogram blocks (one per CU: 128 KB of LDS)
+constexpr int PR_WAVES = PR_THREADS / MGS_WAVE;
+constexpr int PR_HIST_BLOCKS = 96;           // first pass: fewer blocks flush fewer bins
+constexpr int PR_ROUNDS = 16;
+constexpr int PR_RUN = PR_ROUNDS * MGS_WAVE; // consecutive keys of a compacting wavefront
+constexpr int PR_COMPACT_THREADS = 256;
+constexpr int64_t PR_SMALL = 65536;          // largest input of the one-kernel form
 
+// The k-th smallest key of one count, as far as it is known.
 struct PruneState {
-    uint64_t prefix;  // key bits fixed so far (above the current digit)
-    int64_t rem;      // rank (1-based) of the wanted key within that prefix; 0: resolved
+    uint32_t prefix;  // key bits fixed so far (the others 0)
+    uint32_t rem;     // rank (1-based) of the wanted key among those with that prefix
+    uint32_t have;    // how many there are (rem < have at the end: a tie across the threshold)
+    uint32_t pad;
 };
 
 struct PruneArgs {
     const float* imp;
     mgs_status_block* status;
-    PruneState* state;   // [T]
-    uint32_t* hist0;     // [PR_BINS]
-    uint32_t* histA;     // [T][PR_BINS]
-    uint32_t* histB;     // [T][PR_BINS]
-    uint32_t* cnt;       // [T][nblk]
+    PruneState* state;   // [3][MGS_MAX_RATIOS] after each digit
+    uint32_t* hist0;     // [PR_BINS0]
+    uint32_t* hist1;     // [T][PR_BINS]
+    uint32_t* hist2;     // [T][PR_BINS]
+    uint32_t* cnt;       // [T][nstride] keys below the threshold, then the run's first position
+    uint32_t* eqc;       // [T][nstride] keys equal to it, then how many of them the runs before take (tied k only)
     int32_t* kept;
     int64_t n;
-    int64_t nblk;
+    int64_t nrun;
+    int64_t nstride;     // nrun rounded up to 8: rows of cnt and eqc start on 32 bytes
     int32_t T;
     int32_t pad;
     int64_t k[MGS_MAX_RATIOS];
@@ -62,271 +79,635 @@ struct PruneArgs {
 };
 
 __device__ __forceinline__ uint32_t desc_key(float v) {
-    uint32_t b = __float_as_uint(v);
-    if (b == 0x80000000u) b = 0u;                             // -0 -> +0
-    uint32_t asc = (b & 0x80000000u) ? ~b : (b | 0x80000000u);  // ascending in v
-    return ~asc;                                              // descending in v
+    const uint32_t b = __float_as_uint(v + 0.0f);             // -0 -> +0
+    // negative values keep their bits, the others have all but the sign flipped
+    return b ^ (~(uint32_t)((int32_t)b >> 31) & 0x7FFFFFFFu);
 }
 
-__device__ __forceinline__ uint64_t comp_key(const float* imp, int64_t i) {
-    return ((uint64_t)desc_key(imp[i]) << 32) | (uint64_t)i;
-}
-
-__device__ __forceinline__ uint32_t digit(uint64_t ck, int level) {
-    return (uint32_t)(ck >> PR_SHIFT[level]) & ((1u << PR_BITS[level]) - 1u);
-}
-
-__device__ __forceinline__ uint32_t* level_hist(const PruneArgs& a, int level, int t) {
-    if (level == 0) return a.hist0;
-    return ((level & 1) ? a.histA : a.histB) + (int64_t)t * PR_BINS;
-}
-
-// Level 0: histogram of the top digit over all keys (LDS-privatised).
-__global__ __launch_bounds__(PR_HIST_THREADS) void prune_hist0_kernel(PruneArgs a) {
-    __shared__ uint32_t h[PR_BINS];
-    for (int i = threadIdx.x; i < PR_BINS; i += PR_HIST_THREADS) h[i] = 0u;
-    __syncthreads();
-    uint32_t bad = 0;
-    for (int64_t i = (int64_t)blockIdx.x * PR_HIST_THREADS + threadIdx.x; i < a.n;
-         i += (int64_t)gridDim.x * PR_HIST_THREADS) {
-        float v = a.imp[i];
-        bad |= (uint32_t)!finite_f32(v);
-        atomicAdd(&h[desc_key(v) >> (32 - PR_BITS[0])], 1u);
+// Inclusive prefix sum over the lanes of a wavefront.
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t v, int lane) {
+#pragma unroll
+    for (int o = 1; o < MGS_WAVE; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)v, o, MGS_WAVE);
+        if (lane >= o) v += y;
     }
+    return v;
+}
+
+// Exclusive prefix sum over a block of PR_THREADS; `part`: PR_WAVES words.
+__device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t* part, int lane, int wave, uint32_t* total) {
+    const uint32_t incl = wave_inclusive(v, lane);
+    if (lane == MGS_WAVE - 1) part[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < PR_WAVES; ++w) {
+        if (w < wave) before += part[w];
+        all += part[w];
+    }
+    __syncthreads();
+    if (total) *total = all;
+    return before + incl - v;
+}
+
+// Calls fn(importance) for this block's share of all keys, in any order
+// (16-byte loads, four in flight, where the array is aligned to them).
+template <typename F>
+__device__ __forceinline__ void for_each_importance(const PruneArgs& a, F fn) {
+    const int64_t step = (int64_t)gridDim.x * PR_THREADS, i0 = (int64_t)blockIdx.x * PR_THREADS + threadIdx.x;
+    if (((uintptr_t)a.imp & 15) == 0) {
+        const float4* v4 = (const float4*)a.imp;
+        const int64_t n4 = a.n / 4;
+        int64_t i = i0;
+        for (; i + 3 * step < n4; i += 4 * step) {
+            float4 q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = v4[i + u * step];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                fn(q[u].x);
+                fn(q[u].y);
+                fn(q[u].z);
+                fn(q[u].w);
+            }
+        }
+        for (; i < n4; i += step) {
+            const float4 q = v4[i];
+            fn(q.x);
+            fn(q.y);
+            fn(q.z);
+            fn(q.w);
+        }
+        if (i0 < a.n - 4 * n4) fn(a.imp[4 * n4 + i0]);
+    } else {
+        for (int64_t i = i0; i < a.n; i += step) fn(a.imp[i]);
+    }
+}
+
+// First digit: histogram over all keys (LDS-privatised).
+__global__ __launch_bounds__(PR_THREADS) void prune_hist0_kernel(PruneArgs a) {
+    extern __shared__ __align__(16) uint32_t h[];  // [PR_BINS0]
+    for (int i = threadIdx.x; i < PR_BINS0 / 4; i += PR_THREADS) ((uint4*)h)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    bool bad = false;
+    for_each_importance(a, [&](float v) {
+        bad |= !finite_f32(v);
+        atomicAdd(&h[desc_key(v) >> PR_REST], 1u);
+    });
     if (bad) atomicOr(&a.status->nonfinite, 1u);
     __syncthreads();
-    for (int i = threadIdx.x; i < PR_BINS; i += PR_HIST_THREADS)
+    for (int i = threadIdx.x; i < PR_BINS0; i += PR_THREADS)
         if (h[i]) atomicAdd(&a.hist0[i], h[i]);
 }
 
-// Levels 1..5: histogram of digit `level` over the keys matching a k's prefix.
-__global__ __launch_bounds__(PR_HIST_THREADS) void prune_hist_kernel(PruneArgs a, int level) {
-    __shared__ int16_t first[PR_BINS];
-    __shared__ int16_t next[MGS_MAX_RATIOS];
-    __shared__ uint64_t pre[MGS_MAX_RATIOS];
-    for (int i = threadIdx.x; i < PR_BINS; i += PR_HIST_THREADS) first[i] = -1;
-    __syncthreads();
-    __shared__ int active;
-    const int hs = PR_SHIFT[level - 1];  // bits at and above this shift are fixed
-    if (threadIdx.x < a.T && a.k[threadIdx.x] > 0) pre[threadIdx.x] = a.state[threadIdx.x].prefix >> hs;
-    __syncthreads();
-    // Build the per-top-digit lists serially (T <= 64 entries) of the k whose
-    // key is not resolved yet.
-    if (threadIdx.x == 0) {
-        int na = 0;
-        for (int t = a.T - 1; t >= 0; --t) {
-            if (a.k[t] <= 0 || a.state[t].rem == 0) continue;
-            uint32_t d0 = (uint32_t)(a.state[t].prefix >> PR_SHIFT[0]);
-            next[t] = first[d0];
-            first[d0] = (int16_t)t;
-            ++na;
+// LDS of the second and third pass.
+struct PruneShared {
+    uint32_t* hist;      // [min(T, PR_LDS_ROWS)][PR_BINS]
+    int8_t* slot;        // [PR_BINS0] the digit's first count (of those that own a histogram), -1: none
+    uint32_t* pre;       // [MGS_MAX_RATIOS] prefix of each count
+    uint32_t* part;      // [PR_WAVES]
+    int8_t* next;        // [MGS_MAX_RATIOS] the next count with the same first digit, -1: none
+    uint32_t* sums;      // [PR_THREADS] the first digit's counts, prefix sums of 32 bins each
+};
+__device__ __forceinline__ PruneShared prune_shared(void* base, int T) {
+    PruneShared s;
+    s.hist = (uint32_t*)base;
+    s.slot = (int8_t*)(s.hist + min(T, PR_LDS_ROWS) * PR_BINS);
+    s.pre = (uint32_t*)(s.slot + PR_BINS0);
+    s.part = s.pre + MGS_MAX_RATIOS;
+    s.next = (int8_t*)(s.part + PR_WAVES);
+    s.sums = s.pre + MGS_MAX_RATIOS + PR_WAVES + MGS_MAX_RATIOS / 4;
+    return s;
+}
+constexpr size_t prune_lds(int T) {
+    return sizeof(uint32_t) * (size_t)(T < PR_LDS_ROWS ? T : PR_LDS_ROWS) * PR_BINS + PR_BINS0 +
+           4 * MGS_MAX_RATIOS + 4 * PR_WAVES + MGS_MAX_RATIOS + 4 * PR_THREADS;
+}
+static_assert(prune_lds(MGS_MAX_RATIOS) <= 163840, "LDS of a CU");
+
+// One count's digit from a histogram of nbins <= PR_BINS bins, by one
+// wavefront (lane l: bins [8 l, 8 l + 8)): the digit that holds the rem-th key.
+__device__ __forceinline__ PruneState pick_digit(const uint32_t* h, int nbins, int shift, PruneState st, int lane) {
+    constexpr int PER = PR_BINS / MGS_WAVE;
+    uint32_t c[PER], mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        c[j] = lane * PER + j < nbins ? h[lane * PER + j] : 0u;
+        mine += c[j];
+    }
+    const uint32_t before = wave_inclusive(mine, lane) - mine;
+    const bool here = before < st.rem && st.rem <= before + mine;
+    uint32_t digit = 0, rem = 0, have = 0, cum = before;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (cum < st.rem && st.rem <= cum + c[j]) {
+            digit = (uint32_t)(lane * PER + j);
+            rem = st.rem - cum;
+            have = c[j];
         }
-        active = na;
+        cum += c[j];
+    }
+    const uint64_t m = __builtin_amdgcn_ballot_w64(here);
+    const int src = m ? __builtin_ctzll(m) : 0;
+    PruneState r{};
+    r.prefix = st.prefix | ((uint32_t)__builtin_amdgcn_readlane((int)digit, src) << shift);
+    r.rem = (uint32_t)__builtin_amdgcn_readlane((int)rem, src);
+    r.have = (uint32_t)__builtin_amdgcn_readlane((int)have, src);
+    return r;
+}
+
+// Second and third digit (LEVEL 1, 2): picks every count's digit before, then
+// counts the keys that share a count's prefix (counts with the same prefix
+// share a histogram, that of the first of them).
+template <int LEVEL>
+__global__ __launch_bounds__(PR_THREADS) void prune_hist_kernel(PruneArgs a) {
+    extern __shared__ __align__(16) uint32_t lds[];
+    const PruneShared s = prune_shared(lds, a.T);
+    const int tid = threadIdx.x, lane = tid & (MGS_WAVE - 1), wave = tid / MGS_WAVE;
+    for (int i = tid; i < PR_BINS0 / 4; i += PR_THREADS) ((int32_t*)s.slot)[i] = -1;
+    const int rows = min(a.T, PR_LDS_ROWS);
+    for (int i = tid; i < rows * PR_BINS; i += PR_THREADS) s.hist[i] = 0u;
+    // lane u: count u (T <= 64)
+    const uint32_t my_k = lane < a.T ? (uint32_t)a.k[lane] : 0u;
+    if (LEVEL == 1) {
+        // sums of 32 consecutive bins per thread and their prefix; a wavefront
+        // finds its count's sum among the 1024 and then its bin among the 32
+        constexpr int PER = PR_BINS0 / PR_THREADS;
+        static_assert(PER == 32 && PR_THREADS == 1024, "two lookups by ballots");
+        const uint4* h4 = (const uint4*)(a.hist0 + tid * PER);
+        uint32_t mine = 0;
+#pragma unroll
+        for (int j = 0; j < PER / 4; ++j) {
+            const uint4 q = h4[j];
+            mine += (q.x + q.y) + (q.z + q.w);
+        }
+        s.sums[tid] = block_exclusive(mine, s.part, lane, wave, nullptr) + mine;  // inclusive
+        __syncthreads();
+        for (int t = wave; t < a.T; t += PR_WAVES) {
+            const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)my_k, t);
+            if (k == 0) continue;
+            // the first sum >= k: in which 16 of them, then which one
+            const int seg = __popcll(__builtin_amdgcn_ballot_w64(s.sums[lane * 16 + 15] < k));
+            const int in = __popcll(__builtin_amdgcn_ballot_w64(lane < 16 && s.sums[seg * 16 + (lane & 15)] < k));
+            const int g = seg * 16 + in;
+            const uint32_t before = g ? s.sums[g - 1] : 0u;
+            const uint32_t c = lane < PER ? a.hist0[g * PER + lane] : 0u;
+            const uint32_t incl = before + wave_inclusive(c, lane);
+            const int bin = __popcll(__builtin_amdgcn_ballot_w64(lane < PER && incl < k));
+            const uint32_t have = (uint32_t)__builtin_amdgcn_readlane((int)c, bin);
+            const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)incl, bin);
+            const uint32_t prefix = (uint32_t)(g * PER + bin) << PR_REST;
+            if (lane == 0) {
+                s.pre[t] = prefix;
+                if (blockIdx.x == 0) a.state[t] = PruneState{prefix, k - (upto - have), have, 0u};
+            }
+        }
+    } else {
+        const uint32_t before = my_k ? a.state[lane].prefix : 0u;
+        for (int t = wave; t < a.T; t += PR_WAVES) {
+            if (__builtin_amdgcn_readlane((int)my_k, t) == 0) continue;
+            const PruneState st = a.state[t];
+            // the histogram of the first count with this prefix
+            const int own = __builtin_ctzll(__builtin_amdgcn_ballot_w64(my_k && before == st.prefix));
+            const PruneState r = pick_digit(a.hist1 + own * PR_BINS, 1 << PR_BITS1, PR_BITS2, st, lane);
+            if (lane == 0) {
+                s.pre[t] = r.prefix;
+                if (blockIdx.x == 0) a.state[MGS_MAX_RATIOS + t] = r;
+            }
+        }
     }
     __syncthreads();
-    if (active == 0) return;  // every k resolved at an earlier digit (no tie across it)
-    for (int64_t i = (int64_t)blockIdx.x * PR_HIST_THREADS + threadIdx.x; i < a.n;
-         i += (int64_t)gridDim.x * PR_HIST_THREADS) {
-        uint64_t ck = comp_key(a.imp, i);
-        int t = first[ck >> PR_SHIFT[0]];
-        if (t < 0) continue;
-        const uint64_t hi = ck >> hs;
-        const uint32_t d = digit(ck, level);
-        for (; t >= 0; t = next[t])
-            if (pre[t] == hi) atomicAdd(&level_hist(a, level, t)[d], 1u);
+    // ---- the first count with each prefix owns its histogram; owners with the
+    // same first digit form a list (one wavefront, lane u: count u)
+    if (wave == 0) {
+        const uint32_t pre = my_k ? s.pre[lane] : 0u;
+        uint64_t owners = 0, same = 0;  // same: owners with this lane's first digit
+        for (int t = 0; t < a.T; ++t) {
+            const uint32_t pt = (uint32_t)__builtin_amdgcn_readlane((int)pre, t);
+            const uint64_t m = __builtin_amdgcn_ballot_w64(my_k && pre == pt);
+            if (m && __builtin_ctzll(m) == t) owners |= 1ull << t;
+        }
+        const bool owner = (owners >> lane) & 1ull;
+        for (int t = 0; t < a.T; ++t) {
+            const uint32_t dt = (uint32_t)__builtin_amdgcn_readlane((int)pre, t) >> PR_REST;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(owner && (pre >> PR_REST) == dt);
+            if (lane == t) same = m;
+        }
+        if (owner) {
+            const uint64_t later = lane < 63 ? same >> (lane + 1) : 0ull;
+            s.next[lane] = later ? (int8_t)(lane + 1 + __builtin_ctzll(later)) : (int8_t)-1;
+            if (__builtin_ctzll(same) == lane) s.slot[pre >> PR_REST] = (int8_t)lane;
+        }
+    }
+    __syncthreads();
+    constexpr int fixed = LEVEL == 1 ? PR_REST : PR_BITS2;  // bits below the prefix
+    constexpr int bits = LEVEL == 1 ? PR_BITS1 : PR_BITS2;
+    uint32_t* out = LEVEL == 1 ? a.hist1 : a.hist2;
+    for_each_importance(a, [&](float v) {
+        const uint32_t key = desc_key(v);
+        int t = s.slot[key >> PR_REST];
+        while (t >= 0) {
+            if ((key >> fixed) == (s.pre[t] >> fixed)) {
+                const uint32_t bin = (uint32_t)t * PR_BINS + ((key >> (fixed - bits)) & ((1u << bits) - 1u));
+                if (t < PR_LDS_ROWS) atomicAdd(&s.hist[bin], 1u);
+                else atomicAdd(&out[bin], 1u);
+            }
+            t = LEVEL == 1 ? -1 : s.next[t];  // (one prefix per first digit at level 1)
+        }
+    });
+    __syncthreads();
+    // (each block starts elsewhere, so that they do not meet on the same lines)
+    const int total = rows * PR_BINS, first = (int)(blockIdx.x * 37 % (unsigned)rows) * PR_BINS;
+    for (int j = tid; j < total; j += PR_THREADS) {
+        const int i = first + j < total ? first + j : first + j - total;
+        if (s.hist[i]) atomicAdd(&out[i], s.hist[i]);
     }
 }
 
-// One block per k: pick the digit that holds the rem-th key of the prefix
-// bucket, extend the prefix, and clear this k's histogram of the next level.
-__global__ __launch_bounds__(256) void prune_select_kernel(PruneArgs a, int level) {
+// The last digit of every count, one wavefront each.
+__global__ __launch_bounds__(MGS_WAVE) void prune_last_kernel(PruneArgs a) {
+    const int t = blockIdx.x, lane = threadIdx.x;
+    if (a.k[t] <= 0) return;
+    const PruneState* st = a.state + MGS_MAX_RATIOS;
+    const bool any = lane < a.T && a.k[min(lane, a.T - 1)] > 0;
+    const uint32_t mine = any ? st[lane].prefix : 0u;
+    const int own = __builtin_ctzll(__builtin_amdgcn_ballot_w64(any && mine == st[t].prefix));
+    const PruneState r = pick_digit(a.hist2 + own * PR_BINS, 1 << PR_BITS2, 0, st[t], lane);
+    if (lane == 0) a.state[2 * MGS_MAX_RATIOS + t] = r;
+}
+
+// A wavefront's run of keys; past the end the largest key, which no finite
+// importance has.
+struct PruneRun {
+    uint32_t key[PR_ROUNDS];
+    __device__ __forceinline__ void load(const PruneArgs& a, int64_t run, int lane) {
+        float v[PR_ROUNDS];
+#pragma unroll
+        for (int r = 0; r < PR_ROUNDS; ++r) v[r] = a.imp[min(run * PR_RUN + r * MGS_WAVE + lane, a.n - 1)];
+#pragma unroll
+        for (int r = 0; r < PR_ROUNDS; ++r)
+            key[r] = run * PR_RUN + r * MGS_WAVE + lane < a.n ? desc_key(v[r]) : 0xFFFFFFFFu;
+    }
+};
+
+__device__ __forceinline__ PruneState final_state(const PruneArgs& a, int t) {
+    typedef const __attribute__((address_space(4))) uint32_t* const_u32;  // (scalar loads)
+    const const_u32 p = (const_u32)(a.state + 2 * MGS_MAX_RATIOS + t);
+    return PruneState{p[0], p[1], p[2], 0u};
+}
+
+// The final states of counts t0 + lane, read from the lanes as scalars.
+struct LaneStates {
+    uint32_t prefix, rem, have;  // have == 0: a count of 0
+    __device__ __forceinline__ LaneStates(const PruneArgs& a, int t0, int lane) {
+        const int t = min(t0 + lane, a.T - 1);
+        const PruneState st = a.state[2 * MGS_MAX_RATIOS + t];
+        prefix = st.prefix;
+        rem = st.rem;
+        have = a.k[t] > 0 ? st.have : 0u;
+    }
+    __device__ __forceinline__ PruneState get(int l) const {
+        return PruneState{(uint32_t)__builtin_amdgcn_readlane((int)prefix, l),
+                          (uint32_t)__builtin_amdgcn_readlane((int)rem, l),
+                          (uint32_t)__builtin_amdgcn_readlane((int)have, l), 0u};
+    }
+};
+
+// The run of a compacting wavefront: blocks go round-robin over the XCDs, each
+// of which takes a contiguous piece of the runs, so that the cache lines
+// between two runs' indices are written through one L2.  -1: none.
+constexpr int PR_XCDS = 8;
+__device__ __forceinline__ int64_t compact_run(const PruneArgs& a, int wave) {
+    const int64_t per = gridDim.x / PR_XCDS;  // (a whole number of rounds)
+    const int64_t b = (int64_t)(blockIdx.x % PR_XCDS) * per + blockIdx.x / PR_XCDS;
+    const int64_t run = b * (PR_COMPACT_THREADS / MGS_WAVE) + wave;
+    return run < a.nrun ? run : -1;
+}
+
+// Compaction, counts: one wavefront per (run, counts [blockIdx.y * tb, + tb)).
+__global__ __launch_bounds__(PR_COMPACT_THREADS) void prune_count_kernel(PruneArgs a, int tb) {
+    const int lane = threadIdx.x & (MGS_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MGS_WAVE);
+    const int64_t run = compact_run(a, wave);
+    if (run < 0) return;
+    PruneRun keys;
+    keys.load(a, run, lane);
+    const int t0 = blockIdx.y * tb, t1 = min(a.T, t0 + tb);
+    uint32_t mine = 0, mine_eq = 0;  // lane t - t0: the count's numbers
+    const LaneStates states(a, t0, lane);
+    for (int t = t0; t < t1; ++t) {
+        const PruneState st = states.get(t - t0);
+        if (st.have == 0) continue;  // its numbers are never read
+        const bool tied = st.rem < st.have;
+        uint32_t c = 0, e = 0;
+        if (!tied) {
+#pragma unroll
+            for (int r = 0; r < PR_ROUNDS; ++r)
+                c += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(keys.key[r] <= st.prefix));
+        } else {
+#pragma unroll
+            for (int r = 0; r < PR_ROUNDS; ++r) {
+                c += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(keys.key[r] < st.prefix));
+                e += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(keys.key[r] == st.prefix));
+            }
+        }
+        if (lane == t - t0) {
+            mine = c;
+            mine_eq = e;
+        }
+    }
+    if (t0 + lane < t1) {
+        a.cnt[(int64_t)(t0 + lane) * a.nstride + run] = mine;
+        a.eqc[(int64_t)(t0 + lane) * a.nstride + run] = mine_eq;
+    }
+}
+
+// Compaction, scan: each run's first position, one block per count.  A tied
+// count keeps, of the keys equal to its threshold, the first rem in index order.
+__global__ __launch_bounds__(PR_THREADS) void prune_scan_kernel(PruneArgs a) {
+    constexpr int PER = 8;
+    __shared__ uint32_t part[PR_WAVES];
     const int t = blockIdx.x;
     if (a.k[t] <= 0) return;
-    if (level > 0 && a.state[t].rem == 0) return;  // resolved
-    __shared__ uint32_t part[256];
-    __shared__ int64_t found_base;
-    __shared__ uint32_t found_digit, found_count;
-    const uint32_t* h = level_hist(a, level, t);
-    const int nbins = 1 << PR_BITS[level];
-    const int per = PR_BINS / 256;  // 32 bins per thread (only the first nbins used)
-    const int b0 = threadIdx.x * per;
-    uint32_t mine = 0;
-    for (int j = 0; j < per; ++j)
-        if (b0 + j < nbins) mine += h[b0 + j];
-    part[threadIdx.x] = mine;
-    __syncthreads();
-    // inclusive scan (Hillis-Steele) over the 256 partial sums
-    for (int o = 1; o < 256; o <<= 1) {
-        uint32_t v = threadIdx.x >= o ? part[threadIdx.x - o] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += v;
-        __syncthreads();
-    }
-    PruneState st = level == 0 ? PruneState{0ull, a.k[t]} : a.state[t];
-    const int64_t before = threadIdx.x ? part[threadIdx.x - 1] : 0;
-    if (before < st.rem && st.rem <= (int64_t)part[threadIdx.x]) {
-        int64_t cum = before;
-        for (int j = 0; j < per; ++j) {
-            uint32_t c = (b0 + j < nbins) ? h[b0 + j] : 0u;
-            if (cum + c >= st.rem) {
-                found_digit = (uint32_t)(b0 + j);
-                found_base = cum;
-                found_count = c;
-                break;
+    const int lane = threadIdx.x & (MGS_WAVE - 1), wave = threadIdx.x / MGS_WAVE;
+    uint32_t* c = a.cnt + (int64_t)t * a.nstride;
+    uint32_t* e = a.eqc + (int64_t)t * a.nstride;
+    const PruneState st = final_state(a, t);
+    const bool tied = st.rem < st.have;
+    uint32_t carry = 0, carry_eq = 0;
+    // (rows are whole groups of 8; the numbers past nrun are never read)
+    for (int64_t b0 = 0; b0 < a.nstride; b0 += PR_THREADS * PER) {
+        const int64_t b = b0 + (int64_t)threadIdx.x * PER;
+        const bool in = b < a.nstride;
+        uint32_t v[PER] = {}, sum = 0, total;
+        auto load = [&](const uint32_t* p, uint32_t (&x)[PER]) {
+            if (!in) return;
+            const uint4 lo = *(const uint4*)(p + b), hi = *(const uint4*)(p + b + 4);
+            x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w;
+            x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (b + j >= a.nrun) x[j] = 0u;
+        };
+        auto store = [&](uint32_t* p, const uint32_t (&x)[PER]) {
+            if (!in) return;
+            *(uint4*)(p + b) = make_uint4(x[0], x[1], x[2], x[3]);
+            *(uint4*)(p + b + 4) = make_uint4(x[4], x[5], x[6], x[7]);
+        };
+        load(c, v);
+        if (tied) {
+            uint32_t q[PER] = {}, sq = 0;
+            load(e, q);
+#pragma unroll
+            for (int j = 0; j < PER; ++j) sq += q[j];
+            uint32_t before = carry_eq + block_exclusive(sq, part, lane, wave, &total);
+            carry_eq += total;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const uint32_t taken = min(before, st.rem);  // by the runs before
+                before += q[j];
+                v[j] += min(before, st.rem) - taken;
+                q[j] = taken;
             }
-            cum += c;
+            store(e, q);
         }
-    }
-    __syncthreads();
-    if (level + 1 < PR_LEVELS) {
-        uint32_t* hn = level_hist(a, level + 1, t);
-        for (int i = threadIdx.x; i < PR_BINS; i += 256) hn[i] = 0u;
-    }
-    if (threadIdx.x == 0) {
-        st.prefix |= (uint64_t)found_digit << PR_SHIFT[level];
-        st.rem -= found_base;
-        if (st.rem == (int64_t)found_count) {
-            // the wanted key is the last of its bucket: the whole bucket is
-            // kept, and no other key lies between, so the threshold can take
-            // every lower bit set (with distinct importances this happens
-            // once the importance digits are fixed, and the index digits
-            // need no pass)
-            st.prefix |= (PR_SHIFT[level] ? (1ull << PR_SHIFT[level]) - 1ull : 0ull);
-            st.rem = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) sum += v[j];
+        uint32_t at = carry + block_exclusive(sum, part, lane, wave, &total);
+        carry += total;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const uint32_t x = v[j];
+            v[j] = at;
+            at += x;
         }
-        a.state[t] = st;
+        store(c, v);
     }
 }
 
-// Compaction, phase counts: kept keys of ratios [blockIdx.y * tb, + tb) in
-// one chunk (the chunk's keys are read once for the tb ratios).
-__global__ __launch_bounds__(PR_CHUNK_THREADS) void prune_count_kernel(PruneArgs a, int tb) {
-    __shared__ uint32_t wsum[PR_CHUNK_THREADS / MGS_WAVE];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t base = (int64_t)blockIdx.x * PR_CHUNK;
-    uint64_t ck[PR_CHUNK_ROUNDS];
+// The position of a lane among the set lanes of m, behind `base`.
+__device__ __forceinline__ uint32_t mask_position(uint64_t m, uint32_t base) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
+}
+
+// Writes the kept indices of one run (first index i0) for one count behind
+// `base`; for a tied count `eq_taken` of its `rem` equal keys went to earlier runs.
+template <int ROUNDS>
+__device__ __forceinline__ void write_run(const uint32_t (&key)[ROUNDS], uint32_t th, bool tied, uint32_t rem,
+                                          uint32_t base, uint32_t eq_taken, uint32_t k, int32_t* out, uint32_t i0,
+                                          int lane) {
+    if (!tied) {
 #pragma unroll
-    for (int r = 0; r < PR_CHUNK_ROUNDS; ++r) {
-        int64_t i = base + r * PR_CHUNK_THREADS + threadIdx.x;
-        ck[r] = i < a.n ? comp_key(a.imp, i) : ~0ull;
-    }
-    const int t1 = min(a.T, (int)(blockIdx.y + 1) * tb);
-    for (int t = blockIdx.y * tb; t < t1; ++t) {
-        if (a.k[t] <= 0) continue;  // uniform; its counts are never read
-        const uint64_t th = a.state[t].prefix;
-        uint32_t c = 0;
-#pragma unroll
-        for (int r = 0; r < PR_CHUNK_ROUNDS; ++r) c += (uint32_t)__popcll(__ballot(ck[r] <= th));
-        if (lane == 0) wsum[wave] = c;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t sum = 0;
-            for (int w = 0; w < PR_CHUNK_THREADS / MGS_WAVE; ++w) sum += wsum[w];
-            a.cnt[(int64_t)t * a.nblk + blockIdx.x] = sum;
+        for (int r = 0; r < ROUNDS; ++r) {
+            const bool keep = key[r] <= th;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+            const uint32_t pos = mask_position(m, base);
+            if (keep && pos < k) out[pos] = (int32_t)(i0 + r * MGS_WAVE + lane);
+            base += (uint32_t)__popcll(m);
         }
-        __syncthreads();
+    } else {
+        for (int r = 0; r < ROUNDS; ++r) {
+            uint32_t kr = key[0];
+#pragma unroll
+            for (int x = 1; x < ROUNDS; ++x)
+                if (x == r) kr = key[x];
+            const bool eq = kr == th;
+            const uint64_t me = __builtin_amdgcn_ballot_w64(eq);
+            const bool keep = kr < th || (eq && mask_position(me, eq_taken) < rem);
+            eq_taken += (uint32_t)__popcll(me);
+            const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+            const uint32_t pos = mask_position(m, base);
+            if (keep && pos < k) out[pos] = (int32_t)(i0 + r * MGS_WAVE + lane);
+            base += (uint32_t)__popcll(m);
+        }
     }
 }
 
-// Compaction, phase scan: exclusive prefix of the block counts, one block per k.
-__global__ __launch_bounds__(1024) void prune_scan_kernel(PruneArgs a) {
-    const int t = blockIdx.x;
-    __shared__ uint32_t carry;
-    __shared__ uint32_t part[1024];
-    uint32_t* c = a.cnt + (int64_t)t * a.nblk;
-    if (threadIdx.x == 0) carry = 0u;
+// Compaction, write.
+__global__ __launch_bounds__(PR_COMPACT_THREADS) void prune_write_kernel(PruneArgs a, int tb) {
+    const int lane = threadIdx.x & (MGS_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MGS_WAVE);
+    const int64_t run = compact_run(a, wave);
+    if (run < 0) return;
+    PruneRun keys;
+    keys.load(a, run, lane);
+    const int t0 = blockIdx.y * tb, t1 = min(a.T, t0 + tb);
+    const LaneStates states(a, t0, lane);
+    const int tl = min(t0 + lane, t1 - 1);  // lane t - t0: the run's first position and equal keys taken before
+    const uint32_t my_base = a.cnt[(int64_t)tl * a.nstride + run], my_eq = a.eqc[(int64_t)tl * a.nstride + run];
+    for (int t = t0; t < t1; ++t) {
+        const PruneState st = states.get(t - t0);
+        if (st.have == 0) continue;
+        const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)my_base, t - t0);
+        const uint32_t eq = (uint32_t)__builtin_amdgcn_readlane((int)my_eq, t - t0);
+        write_run<PR_ROUNDS>(keys.key, st.prefix, st.rem < st.have, st.rem, base, eq, (uint32_t)a.k[t],
+                             a.kept + a.koff[t], (uint32_t)(run * PR_RUN), lane);
+    }
+}
+
+// Inputs of up to 64 * ROUNDS * 16: one block per count, wavefront w holding
+// keys [w * 64 ROUNDS, + 64 ROUNDS).  Three digits (13, 10 and 9 bits) in LDS.
+//
+// What bounds it: the instructions of one CU's 16 wavefronts (64 keys per
+// thread).  So the keys that share the first digit, a few hundred, go to a list
+// in LDS, and the other digits look at that alone; more than PR_LIST of them
+// (ties, or values close together) are counted from the registers.
+constexpr int PR_SMALL_BITS[3] = {13, 10, 9};
+constexpr int PR_LIST = 4096;
+template <int ROUNDS>
+__global__ __launch_bounds__(PR_THREADS) void prune_small_kernel(PruneArgs a) {
+    __shared__ __align__(16) uint32_t h[1 << PR_SMALL_BITS[0]];
+    __shared__ uint32_t list[PR_LIST];
+    __shared__ uint32_t part[PR_WAVES], found[3], below[PR_WAVES], equal[PR_WAVES], nlist;
+    const int t = blockIdx.x, tid = threadIdx.x;
+    const int lane = tid & (MGS_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / MGS_WAVE);
+    const uint32_t i0 = (uint32_t)wave * (MGS_WAVE * ROUNDS);
+    const uint32_t n = (uint32_t)a.n;
+    uint32_t key[ROUNDS];
+    {
+        float v[ROUNDS], nan = 0.0f;
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) v[r] = a.imp[min(i0 + r * MGS_WAVE + lane, n - 1u)];
+        // (past the end the largest key: it ranks behind every finite one, so
+        // no pass has to leave it out)
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            nan = __builtin_fmaf(v[r], 0.0f, nan);  // NaN once a value is not finite
+            key[r] = i0 + r * MGS_WAVE + lane < n ? desc_key(v[r]) : 0xFFFFFFFFu;
+        }
+        // every block sees all keys: the first one sets the status word
+        const int any = __syncthreads_or(__builtin_isnan(nan));
+        if (t == 0 && tid == 0) a.status->nonfinite = any ? 1u : 0u;
+    }
+    const uint32_t k = (uint32_t)a.k[t];
+    if (k == 0) return;
+    uint32_t prefix = 0, rem = k, have = 0;
+    // the digit [fixed - bits, fixed) from the histogram just made
+    auto pick = [&](int fixed, int bits) {
+        const int nbins = 1 << bits, per = nbins > PR_THREADS ? nbins / PR_THREADS : 1;
+        __syncthreads();
+        uint32_t c[8], mine = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            c[j] = j < per && tid * per + j < nbins ? h[tid * per + j] : 0u;
+            mine += c[j];
+        }
+        uint32_t cum = block_exclusive(mine, part, lane, wave, nullptr);
+        if (cum < rem && rem <= cum + mine) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (cum < rem && rem <= cum + c[j]) {
+                    found[0] = (uint32_t)(tid * per + j);
+                    found[1] = rem - cum;
+                    found[2] = c[j];
+                }
+                cum += c[j];
+            }
+        }
+        __syncthreads();
+        prefix |= found[0] << (fixed - bits);
+        rem = found[1];
+        have = found[2];
+    };
+    auto clear = [&](int bits) {
+        for (int i = tid; i < 1 << bits; i += PR_THREADS) h[i] = 0u;
+        __syncthreads();
+    };
+    constexpr int F1 = 32 - PR_SMALL_BITS[0], F2 = F1 - PR_SMALL_BITS[1];
+    if (tid == 0) nlist = 0u;
+    clear(PR_SMALL_BITS[0]);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) atomicAdd(&h[key[r] >> F1], 1u);
+    pick(32, PR_SMALL_BITS[0]);
+    const bool listed = have <= PR_LIST;
+    const uint32_t nl = have;
+    if (listed) {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            if ((key[r] >> F1) == (prefix >> F1)) list[atomicAdd(&nlist, 1u) & (PR_LIST - 1)] = key[r];
+    }
+    clear(PR_SMALL_BITS[1]);
+    if (listed) {
+        for (uint32_t i = tid; i < nl; i += PR_THREADS)
+            atomicAdd(&h[(list[i] >> F2) & ((1u << PR_SMALL_BITS[1]) - 1u)], 1u);
+    } else {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            if ((key[r] >> F1) == (prefix >> F1))
+                atomicAdd(&h[(key[r] >> F2) & ((1u << PR_SMALL_BITS[1]) - 1u)], 1u);
+    }
+    pick(F1, PR_SMALL_BITS[1]);
+    clear(PR_SMALL_BITS[2]);
+    if (listed) {
+        for (uint32_t i = tid; i < nl; i += PR_THREADS)
+            if ((list[i] >> F2) == (prefix >> F2)) atomicAdd(&h[list[i] & ((1u << PR_SMALL_BITS[2]) - 1u)], 1u);
+    } else {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            if ((key[r] >> F2) == (prefix >> F2)) atomicAdd(&h[key[r] & ((1u << PR_SMALL_BITS[2]) - 1u)], 1u);
+    }
+    pick(F2, PR_SMALL_BITS[2]);
+    // ---- positions: keys below the threshold (and equal to it) in earlier wavefronts
+    const bool tied = rem < have;
+    uint32_t lt = 0, eq = 0;
+    if (!tied) {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) lt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[r] <= prefix));
+    } else {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            lt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[r] < prefix));
+            eq += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[r] == prefix));
+        }
+    }
+    if (lane == 0) {
+        below[wave] = lt;
+        equal[wave] = eq;
+    }
     __syncthreads();
-    for (int64_t b0 = 0; b0 < a.nblk; b0 += 1024) {
-        int64_t b = b0 + threadIdx.x;
-        uint32_t v = b < a.nblk ? c[b] : 0u;
-        part[threadIdx.x] = v;
-        __syncthreads();
-        for (int o = 1; o < 1024; o <<= 1) {
-            uint32_t x = threadIdx.x >= o ? part[threadIdx.x - o] : 0u;
-            __syncthreads();
-            part[threadIdx.x] += x;
-            __syncthreads();
-        }
-        if (b < a.nblk) c[b] = carry + part[threadIdx.x] - v;
-        __syncthreads();
-        if (threadIdx.x == 1023) carry += part[1023];
-        __syncthreads();
+    uint32_t base = 0, taken = 0;
+    for (int w = 0; w < wave; ++w) {
+        base += below[w];
+        taken += equal[w];
     }
-}
-
-// Compaction, phase write, one block per (chunk, group of tb ratios): each
-// kept key's position is the chunk's offset, plus the kept keys of earlier
-// (round, wave) pairs (an exclusive scan of the 64 ballot counts by one
-// wavefront), plus the lanes below.
-__global__ __launch_bounds__(PR_CHUNK_THREADS) void prune_write_kernel(PruneArgs a, int tb) {
-    constexpr int NW = PR_CHUNK_THREADS / MGS_WAVE;
-    static_assert(PR_CHUNK_ROUNDS * NW == MGS_WAVE, "one count per lane of the scanning wavefront");
-    __shared__ uint32_t off[PR_CHUNK_ROUNDS * NW];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t base = (int64_t)blockIdx.x * PR_CHUNK;
-    uint64_t ck[PR_CHUNK_ROUNDS];
-#pragma unroll
-    for (int r = 0; r < PR_CHUNK_ROUNDS; ++r) {
-        int64_t i = base + r * PR_CHUNK_THREADS + threadIdx.x;
-        ck[r] = i < a.n ? comp_key(a.imp, i) : ~0ull;
-    }
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int t1 = min(a.T, (int)(blockIdx.y + 1) * tb);
-    for (int t = blockIdx.y * tb; t < t1; ++t) {
-        if (a.k[t] <= 0) continue;  // uniform
-        const uint64_t th = a.state[t].prefix;
-        uint64_t m[PR_CHUNK_ROUNDS];
-#pragma unroll
-        for (int r = 0; r < PR_CHUNK_ROUNDS; ++r) m[r] = __ballot(ck[r] <= th);
-        if (lane == 0) {
-#pragma unroll
-            for (int r = 0; r < PR_CHUNK_ROUNDS; ++r) off[r * NW + wave] = (uint32_t)__popcll(m[r]);
-        }
-        __syncthreads();
-        if (wave == 0) {
-            const uint32_t v = off[lane];
-            uint32_t incl = v;
-#pragma unroll
-            for (int o = 1; o < MGS_WAVE; o <<= 1) {
-                const uint32_t y = (uint32_t)__shfl_up((int)incl, o, MGS_WAVE);
-                if (lane >= o) incl += y;
-            }
-            off[lane] = a.cnt[(int64_t)t * a.nblk + blockIdx.x] + incl - v;
-        }
-        __syncthreads();
-        int32_t* out = a.kept + a.koff[t];
-#pragma unroll
-        for (int r = 0; r < PR_CHUNK_ROUNDS; ++r) {
-            if ((m[r] >> lane) & 1ull) {
-                const uint32_t pos = off[r * NW + wave] + (uint32_t)__popcll(m[r] & lt_mask);
-                if (pos < (uint64_t)a.k[t]) out[pos] = (int32_t)(base + r * PR_CHUNK_THREADS + threadIdx.x);
-            }
-        }
-        __syncthreads();  // off is rewritten for the next ratio
-    }
+    taken = min(taken, rem);
+    write_run<ROUNDS>(key, prefix, tied, rem, base + (tied ? taken : 0u), taken, k, a.kept + a.koff[t], i0, lane);
 }
 
 // Workspace layout.
 struct PruneLayout {
-    size_t state, hist0, histA, histB, cnt, total;
+    size_t state, hist0, hist1, hist2, cnt, eqc, total;
+    int64_t nrun, nstride;
 };
 
 PruneLayout prune_layout(int64_t n, int32_t T) {
     PruneLayout L;
+    const size_t t = (size_t)std::max(T, 1);
+    L.nrun = (n + PR_RUN - 1) / PR_RUN;
+    L.nstride = (L.nrun + 7) / 8 * 8;
     size_t o = MGS_STATUS_BYTES;
     L.state = o;
-    o += mgs_align_up(sizeof(PruneState) * MGS_MAX_RATIOS, 256);
+    o += sizeof(PruneState) * 3 * MGS_MAX_RATIOS;
     L.hist0 = o;
-    o += sizeof(uint32_t) * PR_BINS;
-    L.histA = o;
-    o += sizeof(uint32_t) * PR_BINS * (size_t)std::max(T, 1);
-    L.histB = o;
-    o += sizeof(uint32_t) * PR_BINS * (size_t)std::max(T, 1);
+    o += sizeof(uint32_t) * PR_BINS0;
+    L.hist1 = o;
+    o += sizeof(uint32_t) * PR_BINS * t;
+    L.hist2 = o;
+    o += sizeof(uint32_t) * PR_BINS * t;
     L.cnt = o;
-    int64_t nblk = (n + PR_CHUNK - 1) / PR_CHUNK;
-    o += mgs_align_up(sizeof(uint32_t) * (size_t)std::max<int64_t>(nblk, 1) * (size_t)std::max(T, 1), 256);
+    o += mgs_align_up(sizeof(uint32_t) * (size_t)std::max<int64_t>(L.nstride, 1) * t, 256);
+    L.eqc = o;
+    o += mgs_align_up(sizeof(uint32_t) * (size_t)std::max<int64_t>(L.nstride, 1) * t, 256);
     L.total = o;
     return L;
+}
+
+// (A grid's LDS beyond 64 KB has to be allowed once per kernel and device;
+// repeating it is cheap and needs no state.)
+template <typename K>
+int prune_allow_lds(K kernel, size_t bytes) {
+    return mgs_hip_status(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                              (int)bytes));
 }
 
 }  // namespace
@@ -354,18 +735,21 @@ extern "C" int mgs_prune_select(const float* d_imp, int64_t n, const int64_t* h_
     if (!d_ws || ws_bytes < L.total) return MGS_EWORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)d_ws;
+    if (n == 0 || ksum == 0) return mgs_fill<uint32_t>((uint32_t*)ws, 64, 0u, s);
     PruneArgs a;
     std::memset(&a, 0, sizeof(a));
     a.imp = d_imp;
     a.status = (mgs_status_block*)ws;
     a.state = (PruneState*)(ws + L.state);
     a.hist0 = (uint32_t*)(ws + L.hist0);
-    a.histA = (uint32_t*)(ws + L.histA);
-    a.histB = (uint32_t*)(ws + L.histB);
+    a.hist1 = (uint32_t*)(ws + L.hist1);
+    a.hist2 = (uint32_t*)(ws + L.hist2);
     a.cnt = (uint32_t*)(ws + L.cnt);
+    a.eqc = (uint32_t*)(ws + L.eqc);
     a.kept = d_kept;
     a.n = n;
-    a.nblk = (n + PR_CHUNK - 1) / PR_CHUNK;
+    a.nrun = L.nrun;
+    a.nstride = L.nstride;
     a.T = T;
     int64_t off = 0;
     for (int t = 0; t < T; ++t) {
@@ -373,25 +757,35 @@ extern "C" int mgs_prune_select(const float* d_imp, int64_t n, const int64_t* h_
         a.koff[t] = off;
         off += h_k[t];
     }
-    int rc = mgs_fill<uint32_t>((uint32_t*)ws, 64, 0u, s);
-    if (rc) return rc;
-    rc = mgs_fill<uint32_t>(a.hist0, PR_BINS, 0u, s);
-    if (rc) return rc;
-    if (n == 0 || ksum == 0) return MGS_OK;
-    int64_t hblocks = std::min<int64_t>((n + PR_HIST_THREADS * 16 - 1) / (PR_HIST_THREADS * 16), 2048);
-    hipLaunchKernelGGL(prune_hist0_kernel, dim3((unsigned)hblocks), dim3(PR_HIST_THREADS), 0, s, a);
-    hipLaunchKernelGGL(prune_select_kernel, dim3(T), dim3(256), 0, s, a, 0);
-    for (int level = 1; level < PR_LEVELS; ++level) {
-        hipLaunchKernelGGL(prune_hist_kernel, dim3((unsigned)hblocks), dim3(PR_HIST_THREADS), 0, s, a,
-                           level);
-        hipLaunchKernelGGL(prune_select_kernel, dim3(T), dim3(256), 0, s, a, level);
+    if (n <= PR_SMALL) {
+        if (n <= PR_SMALL / 4)
+            hipLaunchKernelGGL(prune_small_kernel<16>, dim3(T), dim3(PR_THREADS), 0, s, a);
+        else
+            hipLaunchKernelGGL(prune_small_kernel<64>, dim3(T), dim3(PR_THREADS), 0, s, a);
+        return mgs_last_launch();
     }
-    // ratios per compaction block: about 2048 blocks in all (enough to fill
-    // the chip; more blocks would only read the same keys again)
-    const int tb = (int)std::min<int64_t>(T, std::max<int64_t>(1, (T * a.nblk + 2047) / 2048));
-    const unsigned tgroups = (unsigned)((T + tb - 1) / tb);
-    hipLaunchKernelGGL(prune_count_kernel, dim3((unsigned)a.nblk, tgroups), dim3(PR_CHUNK_THREADS), 0, s, a, tb);
-    hipLaunchKernelGGL(prune_scan_kernel, dim3(T), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(prune_write_kernel, dim3((unsigned)a.nblk, tgroups), dim3(PR_CHUNK_THREADS), 0, s, a, tb);
+    const size_t lds0 = sizeof(uint32_t) * PR_BINS0, lds = prune_lds(T);
+    int rc = prune_allow_lds(prune_hist0_kernel, lds0);
+    if (!rc) rc = prune_allow_lds(prune_hist_kernel<1>, lds);
+    if (!rc) rc = prune_allow_lds(prune_hist_kernel<2>, lds);
+    // status, states and histograms, in one piece
+    if (!rc) rc = mgs_fill<uint32_t>((uint32_t*)ws, (int64_t)(L.cnt / sizeof(uint32_t)), 0u, s);
+    if (rc) return rc;
+    const int64_t per_block = (int64_t)PR_THREADS * 16;
+    const unsigned hb0 = (unsigned)std::min<int64_t>((n + per_block - 1) / per_block, PR_HIST_BLOCKS);
+    const unsigned hb = (unsigned)std::min<int64_t>((n + per_block - 1) / per_block, 256);
+    hipLaunchKernelGGL(prune_hist0_kernel, dim3(hb0), dim3(PR_THREADS), lds0, s, a);
+    hipLaunchKernelGGL(prune_hist_kernel<1>, dim3(hb), dim3(PR_THREADS), lds, s, a);
+    hipLaunchKernelGGL(prune_hist_kernel<2>, dim3(hb), dim3(PR_THREADS), lds, s, a);
+    hipLaunchKernelGGL(prune_last_kernel, dim3(T), dim3(MGS_WAVE), 0, s, a);
+    // counts per compacting wavefront: about 16384 wavefronts, twice what the
+    // chip holds (5.3e6 keys, 32 counts: 161 us in all, 169 with 8192)
+    const int64_t groups = std::min<int64_t>(T, std::max<int64_t>(1, 16384 / a.nrun));
+    const int tb = (int)((T + groups - 1) / groups);
+    const int64_t cblocks = (a.nrun + PR_COMPACT_THREADS / MGS_WAVE - 1) / (PR_COMPACT_THREADS / MGS_WAVE);
+    const dim3 cgrid((unsigned)((cblocks + PR_XCDS - 1) / PR_XCDS * PR_XCDS), (unsigned)((T + tb - 1) / tb));
+    hipLaunchKernelGGL(prune_count_kernel, cgrid, dim3(PR_COMPACT_THREADS), 0, s, a, tb);
+    hipLaunchKernelGGL(prune_scan_kernel, dim3(T), dim3(PR_THREADS), 0, s, a);
+    hipLaunchKernelGGL(prune_write_kernel, cgrid, dim3(PR_COMPACT_THREADS), 0, s, a, tb);
     return mgs_last_launch();
 }
