@@ -51,6 +51,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 
@@ -62,9 +63,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int VQ_WAVES = 4;
 constexpr int VQ_THREADS = VQ_WAVES * MGS_WAVE;
-constexpr int VQ_ROWSETS = 2;                          // 32-row sets per wave
-constexpr int VQ_ROWS = VQ_WAVES * VQ_ROWSETS * 32;    // rows per workgroup
-constexpr int VQ_CHUNK = 64;                           // codewords per LDS chunk (two buffers)
+constexpr int VQ_CHUNK = 64;                           // codewords per chunk of the prepared codebook
+// Up to here one row set per wave and larger buffers: two workgroups per CU (one
+// where a buffer pair takes more than half of the LDS).  Measured, few / many
+// form: 65,000 rows x 36 against 4096 70 / 89 us, 100,000 114 / 105; 65,000 x 45
+// against 1024 49 / 59; 32,000 x 64 against 512 44 / 61, 65,000 64 / 60.
+constexpr int64_t vq_few_rows(int KS) { return KS <= 4 ? 65536 : 32768; }
 constexpr int VQ_CAND = 8;                             // candidate tiles per lane and row set
 
 struct VqArgs {
@@ -94,37 +98,44 @@ __device__ __forceinline__ float vq_scale(float cm) {
     return ldexpf(1.0f, min(max(7 - ex, -126), 126));
 }
 
+// A codeword's values, all loads issued before the first is used (KP: its
+// padded width; values past D repeat the last one).
+template <int KP>
+__device__ __forceinline__ void load_codeword(const float* __restrict__ c, int D, float (&v)[KP]) {
+#pragma unroll
+    for (int k = 0; k < KP; ++k) v[k] = c[min(k, D - 1)];
+}
+
 // The codeword-norm maximum, rounded up (the status word, the maximum and
 // the fallback counter are cleared before this kernel).  One thread per
-// codeword.
-__global__ __launch_bounds__(256) void vq_norm_kernel(VqArgs a) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// codeword, in blocks of one wavefront: a codebook has few codewords, so that
+// larger blocks would leave most CUs idle.
+constexpr int VQ_CB_THREADS = MGS_WAVE;
+template <int KS>
+__global__ __launch_bounds__(VQ_CB_THREADS) void vq_norm_kernel(VqArgs a) {
+    constexpr int KP = 16 * KS;
+    const int j = blockIdx.x * VQ_CB_THREADS + threadIdx.x;
     float nrm = 0.0f;  // FP32 bits of non-negative floats order as unsigned ints
     if (j < a.K) {
-        const float* c = a.cb + (int64_t)j * a.D;
+        float v[KP];
+        load_codeword<KP>(a.cb + (int64_t)j * a.D, a.D, v);
         double n2 = 0.0;
         bool bad = false;
-        for (int k = 0; k < a.D; ++k) {
-            const float v = c[k];
-            bad |= !finite_f32(v);
-            n2 += (double)v * (double)v;
-        }
+#pragma unroll
+        for (int k = 0; k < KP; ++k)
+            if (k < a.D) {
+                bad |= !finite_f32(v[k]);
+                n2 += (double)v[k] * (double)v[k];
+            }
         if (bad) atomicOr(&a.status->nonfinite, 1u);
         nrm = (float)sqrt(n2) * (1.0f + 1.0e-6f);
     }
     // the block's largest norm, then one atomic per block (thousands of
     // atomics on one address serialise)
-    __shared__ uint32_t red[256 / MGS_WAVE];
     uint32_t m = __float_as_uint(nrm);
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, MGS_WAVE));
-    if ((threadIdx.x & (MGS_WAVE - 1)) == 0) red[threadIdx.x / MGS_WAVE] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x / MGS_WAVE); ++w) m = max(m, red[w]);
-        m = max(m, red[0]);
-        atomicMax(a.cmax_bits, m);
-    }
+    if (threadIdx.x == 0) atomicMax(a.cmax_bits, m);
 }
 
 // Prepared codebook: -2 sigma c and the high and low FP16 parts of
@@ -135,9 +146,9 @@ __global__ __launch_bounds__(256) void vq_norm_kernel(VqArgs a) {
 // the compile-time row width, so the codeword's loads are all issued before
 // use and its row is written as 16-byte units.
 template <int KS>
-__global__ __launch_bounds__(256) void vq_prep_kernel(VqArgs a) {
+__global__ __launch_bounds__(VQ_CB_THREADS) void vq_prep_kernel(VqArgs a) {
     constexpr int KP = 16 * KS;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = blockIdx.x * VQ_CB_THREADS + threadIdx.x;
     if (j >= a.Kpad) return;
     // unit u of codeword j: chunk j / 64, unit-major inside the chunk
     f16x8* row = (f16x8*)(a.cbp + (int64_t)(j / VQ_CHUNK) * VQ_CHUNK * KP) + (j % VQ_CHUNK);
@@ -153,10 +164,10 @@ __global__ __launch_bounds__(256) void vq_prep_kernel(VqArgs a) {
         return;
     }
     const float sg = vq_scale(__uint_as_float(*a.cmax_bits));
-    const float* c = a.cb + (int64_t)j * a.D;
     float v[KP];
+    load_codeword<KP>(a.cb + (int64_t)j * a.D, a.D, v);
 #pragma unroll
-    for (int k = 0; k < KP; ++k) v[k] = k < a.D ? c[k] * sg : 0.0f;  // exact power-of-two scaling
+    for (int k = 0; k < KP; ++k) v[k] = k < a.D ? v[k] * sg : 0.0f;  // exact power-of-two scaling
     double n2 = 0.0;
 #pragma unroll
     for (int k = 0; k < KP; ++k)
@@ -226,19 +237,58 @@ __device__ __forceinline__ void exact_dist_vec2(const float* __restrict__ x, con
     *d1 = s1;
 }
 
-template <int KS>
-// Four waves per SIMD (at most 128 VGPRs) for D <= 46; wider rows take three.
-__global__ __launch_bounds__(VQ_THREADS) __attribute__((amdgpu_waves_per_eu(KS <= 3 ? 4 : 3)))
+// The same for any D and 4-byte alignment, from single loads in batches of 16
+// (values past D repeat the last one and are ignored).  With one load after the
+// other this was a chain of D round trips per candidate: 14 of the 61 us of the
+// main kernel at 10,007 x 45 against 1000.
+__device__ __forceinline__ void exact_dist2(const float* __restrict__ x, const float* __restrict__ c0,
+                                            const float* __restrict__ c1, int D, double* d0, double* d1) {
+    constexpr int NB = 16;
+    double s0 = 0.0, s1 = 0.0;
+    for (int k0 = 0; k0 < D; k0 += NB) {
+        float xv[NB], av[NB], bv[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int k = min(k0 + i, D - 1);
+            xv[i] = x[k];
+            av[i] = c0[k];
+            bv[i] = c1[k];
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (k0 + i < D) {
+                const double da = (double)xv[i] - (double)av[i];
+                const double db = (double)xv[i] - (double)bv[i];
+                s0 += da * da;
+                s1 += db * db;
+            }
+    }
+    *d0 = s0;
+    *d1 = s1;
+}
+
+// VEC: D % 4 == 0 and x 16-byte aligned (rows load as float4).  VQ_ROWSETS: 32-row
+// sets per wave.  SUB: chunks per LDS buffer.
+// Many rows: two row sets (an A load feeds twice as many MFMAs) and one chunk per
+// buffer, four workgroups per CU hide the copies.  Few rows (the launch rule
+// below): one row set spreads them over twice as many waves, and with one
+// workgroup per CU each buffer's copy has to be hidden by its own wave's work on
+// the other one: four chunks (main kernel at 10,007 x 45 against 1000: 47 -> 27 us).
+template <int KS, bool VEC, int VQ_ROWSETS, int SUB>
+// Four waves per SIMD (at most 128 VGPRs) for D <= 46; wider rows take three,
+// and the large buffers leave room for one or two.
+__global__ __launch_bounds__(VQ_THREADS) __attribute__((amdgpu_waves_per_eu(SUB > 1 ? 1 : KS <= 3 ? 4 : 3)))
 void vq_main_kernel(VqArgs a) {
     constexpr int KP = 16 * KS;
     constexpr int UNITS = KP / 8;  // 16-byte units per prepared codeword
-    // two chunk buffers, filled by direct global-to-LDS loads (64 lanes x 16
+    constexpr int VQ_ROWS = VQ_WAVES * VQ_ROWSETS * 32;  // rows per workgroup
+    // two buffers, filled by direct global-to-LDS loads (64 lanes x 16
     // contiguous bytes per instruction, so the rows are not padded).  They are
-    // two variables and every chunk step reads a fixed one, so the compiler
+    // two variables and every step reads a fixed one, so the compiler
     // can tell that the copy into one buffer leaves the other alone and does
     // not wait for the copy before reading.
-    __shared__ __attribute__((aligned(16))) _Float16 cbs0[VQ_CHUNK * KP];
-    __shared__ __attribute__((aligned(16))) _Float16 cbs1[VQ_CHUNK * KP];
+    __shared__ __attribute__((aligned(16))) _Float16 cbs0[SUB * VQ_CHUNK * KP];
+    __shared__ __attribute__((aligned(16))) _Float16 cbs1[SUB * VQ_CHUNK * KP];
     // candidate tiles: tile index and the mask of the lane's codewords in it
     __shared__ int32_t cand_t[VQ_WAVES][VQ_ROWSETS][VQ_CAND][MGS_WAVE];
     __shared__ uint16_t cand_m[VQ_WAVES][VQ_ROWSETS][VQ_CAND][MGS_WAVE];
@@ -247,17 +297,19 @@ void vq_main_kernel(VqArgs a) {
     const int lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5;  // which 8 of each 16 dims / which 4-row blocks of the output
     const int D = a.D, K = a.K;
-    const int64_t row0 = (int64_t)blockIdx.x * VQ_ROWS + wave * (VQ_ROWSETS * 32);
+    const int64_t row0 = (int64_t)blockIdx.x * VQ_ROWS +
+                         __builtin_amdgcn_readfirstlane(wave) * (VQ_ROWSETS * 32);
 
-    // Asynchronous copy of chunk c0 of the prepared codebook into buffer
-    // `dst`: wave w moves units [(i*VQ_WAVES + w)*64, +64) of the chunk; the
+    // Asynchronous copy of the SUB chunks from c0 on (fewer at the codebook's
+    // end) into buffer `dst`: wave w moves units [(i*VQ_WAVES + w)*64, +64); the
     // LDS base of each instruction is uniform over the wave.
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     auto prefetch = [&](int c0, _Float16* dst) {
-        constexpr int nunits = VQ_CHUNK * UNITS;  // Kpad is a whole number of chunks
+        // Kpad is a whole number of chunks
+        const int nunits = SUB == 1 ? VQ_CHUNK * UNITS : min(SUB * VQ_CHUNK, a.Kpad - c0) * UNITS;
         const char* src = (const char*)(a.cbp + (int64_t)c0 * KP);
 #pragma unroll
-        for (int i = 0; i < (VQ_CHUNK * UNITS + VQ_THREADS - 1) / VQ_THREADS; ++i) {
+        for (int i = 0; i < (SUB * VQ_CHUNK * UNITS + VQ_THREADS - 1) / VQ_THREADS; ++i) {
             const int ublk = (i * VQ_WAVES + wave_u) * MGS_WAVE;
             if (ublk + lane < nunits)
                 __builtin_amdgcn_global_load_lds(
@@ -281,7 +333,7 @@ void vq_main_kernel(VqArgs a) {
         const int64_t r = row0 + rs * 32 + (lane & 31);
         float n2 = 0.0f;
         bool bg = false;
-        if (a.xvec) {
+        if constexpr (VEC) {
             // D % 4 == 0 and 16-byte aligned rows: every group of 4 dims is one
             // unconditional float4 load from an in-bounds address (row and
             // group clamped), all issued before any is used; values outside
@@ -317,15 +369,25 @@ void vq_main_kernel(VqArgs a) {
                     breg[rs][ks][i] = (_Float16)v;
                 }
         } else {
+            // the same from single loads, at 32-bit offsets from the wave's
+            // first row (a 64-bit address per load would take the registers)
+            const int64_t rbase = row0 < a.N ? row0 : a.N - 1, rr = r < a.N ? r : a.N - 1;
+            const float* xw = a.x + rbase * D;
+            const uint32_t rel = (uint32_t)(rr - rbase) * (uint32_t)D;
+            float t[KS][8];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) t[ks][i] = xw[rel + (uint32_t)min(16 * ks + 8 * half + i, D - 1)];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int k = 16 * ks + 8 * half + i;
+                    const float e = t[ks][i];
                     float v = 0.0f;
                     if (k < D) {
                         if (r < a.N) {
-                            const float e = a.x[r * D + k];
                             bad |= (uint32_t)!finite_f32(e);
                             n2 += e * e;
                             v = e * sg;
@@ -336,7 +398,6 @@ void vq_main_kernel(VqArgs a) {
                     }
                     breg[rs][ks][i] = (_Float16)v;
                 }
-            }
         }
         n2 += __shfl_xor(n2, 32, MGS_WAVE);
         big[rs] = (bg | (__shfl_xor((int)bg, 32, MGS_WAVE) != 0));
@@ -351,6 +412,8 @@ void vq_main_kernel(VqArgs a) {
         const double delta = 2.0 * (D + 2) * 0x1p-52 * (xs + cs) * (xs + cs);
         const double scale = cs * cs + 2.0 * xs * cs;
         T[rs] = (float)((2.0 * E + 2.0 * delta) * 1.0001 + 1.0e-6 * scale + 1e-30);
+        // one row set's loads at a time (both sets' would need twice the registers)
+        if (!VEC) __builtin_amdgcn_sched_barrier(0);
     }
     if (bad) atomicOr(&a.status->nonfinite, 1u);
 
@@ -364,15 +427,14 @@ void vq_main_kernel(VqArgs a) {
         cnt[rs] = 0;
     }
 
-    const int nchunks = a.Kpad / VQ_CHUNK;
-    // Chunk step q reads buffer q % 2 while the next chunk is copied into the
-    // other one.
+    constexpr int STEP = SUB * VQ_CHUNK;  // codewords per buffer
+    const int nsteps = (a.Kpad + STEP - 1) / STEP;
+    // Step q reads buffer q % 2 while the next one is copied into the other.
     auto chunk = [&](int q, const _Float16* cb_l, _Float16* other) {
-        const int c0 = q * VQ_CHUNK;
+        const int c0 = q * STEP;
         // the other buffer was last read before the barrier that ended the
-        // previous step: fill it with the next chunk while this one is
-        // processed
-        if (q + 1 < nchunks) prefetch(c0 + VQ_CHUNK, other);
+        // previous step: fill it while this one is processed
+        if (q + 1 < nsteps) prefetch(c0 + STEP, other);
         // scores of one 32-codeword tile for the wave's row sets; K steps
         // outer, row sets inner: consecutive MFMAs are independent.  Lane l
         // reads unit 2 ks + (l / 32) of codeword tile * 32 + l % 32: 512
@@ -382,7 +444,8 @@ void vq_main_kernel(VqArgs a) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
                 areg[ks] = *(const f16x8*)((const char*)cb_l +
-                                            (size_t)(((2 * ks + half) * VQ_CHUNK) + tile * 32 + (lane & 31)) * 16);
+                                            (size_t)((tile / 2) * VQ_CHUNK * UNITS + ((2 * ks + half) * VQ_CHUNK) +
+                                                     (tile % 2) * 32 + (lane & 31)) * 16);
 #pragma unroll
             for (int rs = 0; rs < VQ_ROWSETS; ++rs) acc[rs] = f32x16{};
 #pragma unroll
@@ -434,23 +497,16 @@ void vq_main_kernel(VqArgs a) {
         };
         // software pipeline: the next tile's MFMAs are issued before this
         // tile's epilogue, so the matrix cores work while the VALU does
-        // (two accumulator sets, alternating)
-        constexpr int ntiles = VQ_CHUNK / 32;
+        // (two accumulator sets, alternating; a chunk is two tiles)
         f32x16 acc0[VQ_ROWSETS], acc1[VQ_ROWSETS];
+        const int nt = SUB == 1 ? VQ_CHUNK / 32 : min(STEP, a.Kpad - c0) / 32;
+        static_assert(VQ_CHUNK == 64, "two tiles per chunk");
         scores(0, acc0);
-        int tile = 0;
-        for (; tile + 2 < ntiles; tile += 2) {
+        for (int tile = 0; tile < nt; tile += 2) {
             scores(tile + 1, acc1);
             epilogue(tile, acc0);
-            scores(tile + 2, acc0);
+            if (SUB > 1 && tile + 2 < nt) scores(tile + 2, acc0);
             epilogue(tile + 1, acc1);
-        }
-        if (tile + 1 < ntiles) {
-            scores(tile + 1, acc1);
-            epilogue(tile, acc0);
-            epilogue(tile + 1, acc1);
-        } else {
-            epilogue(tile, acc0);
         }
         // the step's MFMAs are issued before the wait (the scheduler would
         // otherwise hoist the wait over them and expose the copy's latency)
@@ -462,11 +518,11 @@ void vq_main_kernel(VqArgs a) {
     __syncthreads();
     // step q reads buffer q % 2
     int q = 0;
-    for (; q + 1 < nchunks; q += 2) {
+    for (; q + 1 < nsteps; q += 2) {
         chunk(q, cbs0, cbs1);
         chunk(q + 1, cbs1, cbs0);
     }
-    if (q < nchunks) chunk(q, cbs0, cbs1);
+    if (q < nsteps) chunk(q, cbs0, cbs1);
 
     // ---- exact FP64 re-rank of the row's candidates (both lanes of the row)
 #pragma unroll
@@ -478,7 +534,7 @@ void vq_main_kernel(VqArgs a) {
         int32_t bj = 0x7fffffff;
         if (r < a.N && !ovf_row) {
             const float* xr = a.x + r * D;
-            const bool vec = a.xvec && a.cvec;  // float4 rows and codewords
+            const bool vec = VEC && a.cvec;  // float4 rows and codewords
             int e = 0;
             int jbase = cnt[rs] > 0 ? cand_t[wave][rs][0][lane] : 0;
             uint32_t bits = cnt[rs] > 0 ? cand_m[wave][rs][0][lane] : 0u;
@@ -517,8 +573,7 @@ void vq_main_kernel(VqArgs a) {
                 if (vec) {
                     exact_dist_vec2<KP / 4>(xr, c0, c1, D, &d0, &d1);
                 } else {
-                    d0 = exact_dist(xr, c0, D);
-                    d1 = exact_dist(xr, c1, D);
+                    exact_dist2(xr, c0, c1, D, &d0, &d1);
                 }
                 take(j0, d0);
                 take(j1, d1);
@@ -612,6 +667,28 @@ VqLayout vq_layout(int64_t N, int D, int K) {
     return L;
 }
 
+template <int KS>
+void vq_launch(const VqArgs& a, hipStream_t s) {
+    const unsigned cblocks = (unsigned)(a.Kpad / VQ_CB_THREADS);
+    static_assert(VQ_CHUNK % VQ_CB_THREADS == 0, "whole blocks of codewords");
+    hipLaunchKernelGGL(vq_norm_kernel<KS>, dim3(cblocks), dim3(VQ_CB_THREADS), 0, s, a);
+    hipLaunchKernelGGL(vq_prep_kernel<KS>, dim3(cblocks), dim3(VQ_CB_THREADS), 0, s, a);
+    if (a.N > 0) {
+        auto main_kernel = [&](auto vec) {
+            constexpr bool VEC = decltype(vec)::value;
+            if (a.N <= vq_few_rows(KS))
+                hipLaunchKernelGGL((vq_main_kernel<KS, VEC, 1, 4>), dim3((unsigned)((a.N + 127) / 128)),
+                                   dim3(VQ_THREADS), 0, s, a);
+            else
+                hipLaunchKernelGGL((vq_main_kernel<KS, VEC, 2, 1>), dim3((unsigned)((a.N + 255) / 256)),
+                                   dim3(VQ_THREADS), 0, s, a);
+        };
+        static_assert(VQ_WAVES == 4, "rows per workgroup: 32 per wave and row set");
+        if (a.xvec) main_kernel(std::true_type{});
+        else main_kernel(std::false_type{});
+    }
+}
+
 }  // namespace
 }  // namespace mgs
 
@@ -650,28 +727,15 @@ extern "C" int mgs_vq_assign(const float* d_x, int64_t N, int32_t D, const float
     a.KP = L.KP;
     a.xvec = (D % 4 == 0) && ((uintptr_t)d_x % 16 == 0);
     a.cvec = (D % 4 == 0) && ((uintptr_t)d_cb % 16 == 0);
-    int rc = mgs_fill<uint32_t>((uint32_t*)ws, 64, 0u, s);       // status word
+    // status word, norm maximum and fallback count (they lie side by side)
+    int rc = mgs_fill<uint32_t>((uint32_t*)ws, (int64_t)(L.cbp / sizeof(uint32_t)), 0u, s);
     if (rc) return rc;
-    rc = mgs_fill<uint32_t>(a.cmax_bits, 64, 0u, s);              // norm maximum + fallback count
-    if (rc) return rc;
-    hipLaunchKernelGGL(vq_norm_kernel, dim3((K + 255) / 256), dim3(256), 0, s, a);
-    const dim3 pgrid((L.Kpad + 255) / 256);
     switch (L.KS) {
-        case 1: hipLaunchKernelGGL(vq_prep_kernel<1>, pgrid, dim3(256), 0, s, a); break;
-        case 2: hipLaunchKernelGGL(vq_prep_kernel<2>, pgrid, dim3(256), 0, s, a); break;
-        case 3: hipLaunchKernelGGL(vq_prep_kernel<3>, pgrid, dim3(256), 0, s, a); break;
-        case 4: hipLaunchKernelGGL(vq_prep_kernel<4>, pgrid, dim3(256), 0, s, a); break;
-        default: hipLaunchKernelGGL(vq_prep_kernel<5>, pgrid, dim3(256), 0, s, a); break;
-    }
-    if (N > 0) {
-        const unsigned blocks = (unsigned)((N + VQ_ROWS - 1) / VQ_ROWS);
-        switch (L.KS) {
-            case 1: hipLaunchKernelGGL(vq_main_kernel<1>, dim3(blocks), dim3(VQ_THREADS), 0, s, a); break;
-            case 2: hipLaunchKernelGGL(vq_main_kernel<2>, dim3(blocks), dim3(VQ_THREADS), 0, s, a); break;
-            case 3: hipLaunchKernelGGL(vq_main_kernel<3>, dim3(blocks), dim3(VQ_THREADS), 0, s, a); break;
-            case 4: hipLaunchKernelGGL(vq_main_kernel<4>, dim3(blocks), dim3(VQ_THREADS), 0, s, a); break;
-            default: hipLaunchKernelGGL(vq_main_kernel<5>, dim3(blocks), dim3(VQ_THREADS), 0, s, a); break;
-        }
+        case 1: vq_launch<1>(a, s); break;
+        case 2: vq_launch<2>(a, s); break;
+        case 3: vq_launch<3>(a, s); break;
+        case 4: vq_launch<4>(a, s); break;
+        default: vq_launch<5>(a, s); break;
     }
     hipLaunchKernelGGL(vq_fallback_kernel, dim3(2048), dim3(256), 0, s, a);
     return mgs_last_launch();
