@@ -38,17 +38,19 @@
 // the root of 8 million leaves.  The inverse builds the lists bottom-up without
 // values and undoes the merges level by level from the root.
 //
-// What bounds it, at 5.3e6 x 20 on an MI355X: the leaf level (0.40 ms of 0.58)
+// What bounds it, at 5.3e6 x 20 on an MI355X: the leaf level (0.38 ms of 0.50)
 // reads and writes every attribute once (0.93 GB by the counters, 0.19 ms at
-// the rate of a copy) and adds the steps' FP64 and LDS work, half of which its
-// 16 wavefronts per CU do not hide (0.29 ms without the steps; with 12 per CU,
-// 4 wavefronts per block, 0.62 ms in all); the upper levels are chains of
-// about 20 steps each (0.17 ms).  Tiles of 128 leaves and 10 channels measured
-// 0.69 ms against 0.62, of 64 leaves and 20 channels 0.84: fewer steps per
-// channel, but twice and four times the nodes for the upper levels.  Run as one
-// launch per step over node values in HBM (42 dependent launches, rows of both
-// nodes fetched from all over the array) the forward took 1.95 ms at 5.3e6 x 20
-// and the inverse 0.58 ms at 1e6 x 20, which is 0.20 ms now.
+// the rate of a copy) and adds the structure's and the steps' instructions: its
+// vector units are busy 0.7 of the time, its LDS half of it.  A round of 64
+// (merge, channel) pairs is 26 vector instructions, 24 rounds per 256 leaves and
+// four channels.  With weights looked up inside the round, conditions as
+// branches and 40 instructions it took 0.46 ms.  Tiles of 128 leaves and 10 channels measured
+// 0.69 ms for the whole against 0.62 then, of 64 leaves and 20 channels 0.84:
+// fewer rounds per channel, but twice and four times the nodes for the upper
+// levels, which are chains of about 20 steps each (0.12 ms).  Run as one launch
+// per step over node values in HBM (42 dependent launches, rows of both nodes
+// fetched from all over the array) the forward took 1.95 ms at 5.3e6 x 20 and the
+// inverse 0.58 ms at 1e6 x 20, which is 0.18 ms now.
 #include <algorithm>
 #include <cstring>
 
@@ -68,6 +70,8 @@ constexpr int RH_CH = 4;                             // channels in LDS at a tim
 constexpr int RH_UCH = 4;                            // the same at the upper levels
 constexpr int RH_VS = RH_TILE + 1;                   // row stride of the values (channels in different banks)
 constexpr int RH_GROUP = 16;                         // lists that an upper level joins
+constexpr int RH_UPPER_MIN = 256;                     // threads of a group's block at least
+constexpr int RH_UPPER_MAX = 512;                     // and at most
 constexpr int RH_CAP1 = 256;                          // nodes of a group in LDS at the first upper level,
 constexpr int RH_CAP2 = 768;                          // and above it (few groups, lists of more nodes)
 constexpr int RH_LEVELS = 5;                         // leaf level and up to four above it
@@ -231,26 +235,121 @@ __global__ __launch_bounds__(RH_SCAN_THREADS) void raht_scan_kernel(RahtArgs a) 
     if (threadIdx.x == 0) a.tot[blockIdx.x] = total;
 }
 
-// n1 / s and n2 / s, correctly rounded, with y = RN(1 / s): RN(n y) is within
-// 1.5 ulp, one correction by the exact FMA remainder makes it faithful and a
-// second one the correctly rounded quotient (Markstein's theorem), five
-// operations instead of the division's dozen.  Zeros, non-finite values and
-// magnitudes whose remainders could leave the normal range take the division.
-__device__ __forceinline__ void quotients(double n1, double n2, double s, double y, double& q1, double& q2) {
-    q1 = n1 * y;
-    q2 = n2 * y;
-    const bool odd = !(fabs(q1) > 0x1p-900 && fabs(q1) < 0x1p900 && fabs(q2) > 0x1p-900 && fabs(q2) < 0x1p900);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        q1 = __builtin_fma(__builtin_fma(-s, q1, n1), y, q1);
-        q2 = __builtin_fma(__builtin_fma(-s, q2, n2), y, q2);
+// What a merge needs: the roots of both weights, and 1 / sqrt(w1 + w2) as the
+// sum of yh (rounded toward zero, so that yl >= 0) and yl.
+struct RahtWeights {
+    double s1, s2, yh, yl;
+};
+__device__ __forceinline__ double2 reciprocal(double s) {
+    double yh = 1.0 / s;
+    double r = __builtin_fma(-s, yh, 1.0);  // exact
+    if (r < 0.0) {
+        yh = __longlong_as_double(__double_as_longlong(yh) - 1);
+        r = __builtin_fma(-s, yh, 1.0);
     }
+    return make_double2(yh, r / s);
+}
+
+// n1 / s and n2 / s, s = sqrt(w1 + w2).  n yh + n yl is within 2^-104 of the
+// quotient before its one rounding: the division's result (a last bit could
+// differ where the quotient lies that close to the middle of two doubles, one in
+// 2^50), in two operations instead of its dozen, zeros with their sign included
+// (both terms have n's).  Infinities, whose products with a yl of 0 are none,
+// and what they could come from take the division (the roots give the weights).
+// With two corrections by the FMA remainder (Markstein) in place of yl, five
+// operations per quotient, the leaf level at 5.3e6 x 20 took 426 us, now 381.
+__device__ __forceinline__ void quotients(double n1, double n2, const RahtWeights& w, double& q1, double& q2) {
+    q1 = __builtin_fma(n1, w.yh, n1 * w.yl);
+    q2 = __builtin_fma(n2, w.yh, n2 * w.yl);
+    const bool odd = !(fmax(fabs(n1), fabs(n2)) < 0x1p900);
     if (__builtin_amdgcn_ballot_w64(odd)) {  // (rare; the empty asm keeps it a branch)
         asm volatile("" : "+v"(n1), "+v"(n2));
         if (odd) {
+            const double s = sqrt(__builtin_rint(w.s1 * w.s1) + __builtin_rint(w.s2 * w.s2));
             q1 = n1 / s;
             q2 = n2 / s;
         }
+    }
+}
+
+// The steps of one wavefront on its channels, as rounds of up to 64 (merge,
+// channel) pairs, channel fastest; a step of more merges takes several.  A
+// round waits for its values alone: its weights were read a round ahead, its
+// nodes two, and what addresses them is made at the end of the round before.
+// Lanes without a pair repeat the round's last merge and write nothing.  Lane b
+// of mstart and msize: first merge of step b, number of them.  nodes(q): the
+// merge's packed nodes; where(q, nodes): the place of its weights, weights(place)
+// reads them; slots(nodes, channel, first, second): the places of its values.
+typedef __attribute__((address_space(3))) double lds_double;
+template <int MODE, class N, class P, class W, class S>
+__device__ __forceinline__ void run_steps(uint64_t todo, int mstart, int msize, int nch, int lane, double* val, N nodes,
+                                          P where, W weights, S slots) {
+    if (!todo) return;
+    const int per = MGS_WAVE / nch;  // merges of a round
+    const int q0 = lane / nch, cc = lane - q0 * nch;
+    struct Round {
+        int m0, m;  // first merge, merges left of its step (past the last round: 1, 0)
+    };
+    auto next = [&](Round r) {
+        r.m0 += per;
+        r.m -= per;
+        if (r.m <= 0) {
+            r = Round{1, 0};
+            if (todo) {
+                const int b = MODE == RH_FORWARD ? __builtin_ctzll(todo) : 63 - __builtin_clzll(todo);
+                todo &= ~(1ull << b);
+                r.m0 = __builtin_amdgcn_readlane(mstart, b);
+                r.m = __builtin_amdgcn_readlane(msize, b);
+            }
+        }
+        return r;
+    };
+    auto merge_of = [&](Round r) { return r.m0 + min(q0, r.m - 1); };
+    Round ra = next(Round{0, 0}), rb = next(ra);
+    uint32_t nb = nodes(merge_of(ra));
+    lds_double* const v = (lds_double*)val;
+    lds_double *pa, *pb;
+    // (the empty asm keeps the addresses from being made again where they are used)
+    auto slots_of = [&](uint32_t n) {
+        int ia, ib;
+        slots(n, cc, ia, ib);
+        pa = v + ia;
+        pb = v + ib;
+        asm volatile("" : "+v"(pa), "+v"(pb));
+    };
+    slots_of(nb);
+    RahtWeights wa = weights(where(merge_of(ra), nb)), wb{};
+    nb = nodes(merge_of(rb));
+    uint2 at = where(merge_of(rb), nb);
+    auto round = [&](const RahtWeights& now, RahtWeights& then) {
+        lds_double *const va = pa, *const vb = pb;
+        const double x1 = *va, x2 = *vb;
+        then = weights(at);
+        const Round rc = next(rb);
+        const uint32_t nc = nodes(merge_of(rc));
+        double lo, hi;
+        if (MODE == RH_FORWARD)
+            quotients(now.s1 * x1 + now.s2 * x2, now.s1 * x2 - now.s2 * x1, now, lo, hi);
+        else
+            quotients(now.s1 * x1 - now.s2 * x2, now.s2 * x1 + now.s1 * x2, now, lo, hi);
+        const bool mine = q0 < min(ra.m, per);
+        ra = rb;
+        rb = rc;
+        slots_of(nb);
+        at = where(merge_of(rc), nc);  // (before the stores, which it would wait for)
+        asm volatile("" : "+v"(at.x), "+v"(at.y));
+        nb = nc;
+        if (mine) {
+            *va = lo;
+            *vb = hi;
+        }
+        wave_order();
+    };
+    for (;;) {
+        round(wa, wb);
+        if (ra.m <= 0) break;
+        round(wb, wa);
+        if (ra.m <= 0) break;
     }
 }
 
@@ -271,12 +370,20 @@ unsigned xcd_grid(int64_t nblk) { return (unsigned)((nblk + RH_XCDS - 1) / RH_XC
 template <int MODE>
 __global__ __launch_bounds__(RH_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 void raht_leaf_kernel(RahtArgs a) {
-    __shared__ double val[RH_WAVES][RH_CH * RH_VS];
-    __shared__ double sq[RH_TILE], inv[RH_TILE];  // sqrt(w) and RN(1 / sqrt(w)) at w - 1
-    __shared__ int32_t base[RH_STEPS];            // first AC index of each step in this block
-    // the tile's merges in step order: first node's slot, second node's, and
-    // their weights less one, a byte each
-    __shared__ uint32_t pk[RH_WAVES][RH_TILE];
+    __shared__ struct {
+        double2 inv[RH_TILE];  // 1 / sqrt(w) as a sum and sqrt(w), at w - 1 (first: their offsets fit the loads')
+        double sq[RH_TILE];
+        // the tile's merges in step order: first node's slot, second node's, and
+        // their weights less one, a byte each
+        uint32_t pk[RH_WAVES][RH_TILE];
+        int32_t base[RH_STEPS];  // first AC index of each step in this block
+        double val[RH_WAVES][RH_CH * RH_VS];
+    } lds;
+    auto& sq = lds.sq;
+    auto& inv = lds.inv;
+    auto& pk = lds.pk;
+    auto& base = lds.base;
+    auto& val = lds.val;
     const int tid = threadIdx.x;
     const int lane = tid & (MGS_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / MGS_WAVE);
     uint64_t* cd = (uint64_t*)val[wave];                               // [RH_TILE]
@@ -293,7 +400,7 @@ void raht_leaf_kernel(RahtArgs a) {
     if (MODE != RH_STRUCTURE)
         for (int k = tid; k < RH_TILE; k += RH_THREADS) {
             sq[k] = sqrt((double)(k + 1));
-            inv[k] = 1.0 / sq[k];
+            inv[k] = reciprocal(sq[k]);
         }
     hist(wave)[lane] = 0u;
     mcnt[lane] = 0u;
@@ -425,8 +532,15 @@ void raht_leaf_kernel(RahtArgs a) {
         second[e] = q < nm ? (int)((pk[wave][q] >> 8) & 255u) : 0;
         column[e] = q < nm ? 1 + ac[second[e] - 1] : 0;
     }
-    // ---- values, RH_CH channels at a time
+    // ---- values, RH_CH channels at a time; the rows of the nodes that are left
+    // by lanes over (node, channel), whole lines at a time
     double* v = val[wave];
+    constexpr int ROWS = MGS_WAVE / RH_CH;
+    const int node_of = lane / RH_CH, ch_of = lane % RH_CH;
+    auto first_leaf = [&](int node) {  // of every lane's node
+        const int j0 = __shfl(node0, node & (MGS_WAVE - 1)), j1 = __shfl(node1, node & (MGS_WAVE - 1));
+        return node < MGS_WAVE ? j0 : j1;
+    };
     for (int k = 0; k < nchunk; ++k) {
         const int k0 = chunk_first(a.C, nchunk, k), nch = chunk_size(a.C, nchunk, k);
         wave_order();
@@ -440,102 +554,44 @@ void raht_leaf_kernel(RahtArgs a) {
             // each merge's coefficient in the slot of its second node, the
             // nodes' values in theirs (all loads issued before the first is used)
             float hx[RH_CH][RH_ROUNDS];
-            double rv[RH_CH][2];
 #pragma unroll
             for (int cc = 0; cc < RH_CH; ++cc) {
                 const int ch = k0 + min(cc, nch - 1);
 #pragma unroll
                 for (int e = 0; e < RH_ROUNDS; ++e) hx[cc][e] = a.coef_in[(int64_t)ch * a.ld + column[e]];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int node = t * MGS_WAVE + lane;
-                    rv[cc][t] = 0.0;
-                    if (node < live)
-                        rv[cc][t] = a.top == 0 ? (double)a.coef_in[(int64_t)ch * a.ld]
-                                               : a.lev[0].rows[(tile * a.stride + node) * a.C + ch];
-                }
             }
+            auto row = [&](int t) {
+                const int node = min(t + node_of, live - 1), ch = k0 + min(ch_of, nch - 1);
+                return a.top == 0 ? (double)a.coef_in[(int64_t)ch * a.ld]
+                                  : a.lev[0].rows[(tile * a.stride + node) * a.C + ch];
+            };
+            auto put = [&](int t, double r) {
+                const int j = first_leaf(t + node_of);
+                if (t + node_of < live) v[ch_of * RH_VS + j] = r;
+            };
+            const double r0 = row(0);
 #pragma unroll
-            for (int cc = 0; cc < RH_CH; ++cc) {
+            for (int cc = 0; cc < RH_CH; ++cc)
 #pragma unroll
                 for (int e = 0; e < RH_ROUNDS; ++e)
                     if (second[e]) v[cc * RH_VS + second[e]] = (double)hx[cc][e];
-                if (lane < live) v[cc * RH_VS + node0] = rv[cc][0];
-                if (lane + MGS_WAVE < live) v[cc * RH_VS + node1] = rv[cc][1];
-            }
+            put(0, r0);
+            for (int t = ROWS; t < live; t += ROWS) put(t, row(t));
         }
         wave_order();
-        // ---- the steps.  Lanes over (merge, channel) pairs, channel fastest;
-        // the first 64 pairs of the next step get their weights while this
-        // step's values are on their way (only the values depend on it).
-        struct Pair {
-            int va, vb;
-            double s1, s2, sw, y;
+        auto nodes = [&](int q) { return pk[wave][q]; };
+        // byte offsets of sqrt(w1) and sqrt(w2); their sum leads to one below w1 + w2
+        auto where = [&](int, uint32_t w) { return make_uint2((w >> 13) & (255u << 3), (w >> 21) & (255u << 3)); };
+        auto weights = [&](uint2 o) {
+            auto at = [](const double* t, uint32_t bytes) { return *(const double*)((const char*)t + bytes); };
+            const double2 y = *(const double2*)((const char*)(inv + 1) + 2 * (o.x + o.y));
+            return RahtWeights{at(sq, o.x), at(sq, o.y), y.x, y.y};
         };
-        auto weights = [&](int q, int cc) {
-            const uint32_t w = pk[wave][q];
-            const int w1 = (int)((w >> 16) & 255u), w2 = (int)(w >> 24);
-            Pair r;
-            r.va = cc * RH_VS + (int)(w & 255u);
-            r.vb = cc * RH_VS + (int)((w >> 8) & 255u);
-            r.s1 = sq[w1];
-            r.s2 = sq[w2];
-            r.sw = sq[w1 + w2 + 1];
-            r.y = inv[w1 + w2 + 1];
-            return r;
+        auto slots = [&](uint32_t w, int cc, int& ia, int& ib) {
+            ia = cc * RH_VS + (int)(w & 255u);
+            ib = cc * RH_VS + (int)((w >> 8) & 255u);
         };
-        auto merge = [&](const Pair& r) {
-            const double x1 = v[r.va], x2 = v[r.vb];
-            double lo, hi;
-            if (MODE == RH_FORWARD)
-                quotients(r.s1 * x1 + r.s2 * x2, r.s1 * x2 - r.s2 * x1, r.sw, r.y, lo, hi);
-            else
-                quotients(r.s1 * x1 - r.s2 * x2, r.s2 * x1 + r.s1 * x2, r.sw, r.y, lo, hi);
-            v[r.va] = lo;
-            v[r.vb] = hi;
-        };
-        const int q0 = lane / nch, cc0 = lane - q0 * nch;    // the lane's first pair
-        const int dq = MGS_WAVE / nch, dc = MGS_WAVE - dq * nch;  // and what 64 pairs on add to it
-        uint64_t todo = steps;
-        int m0 = 0, m = 0;
-        auto next_step = [&]() {
-            const int b = MODE == RH_FORWARD ? __builtin_ctzll(todo) : 63 - __builtin_clzll(todo);
-            todo &= ~(1ull << b);
-            m0 = __builtin_amdgcn_readlane(mstart, b);
-            m = __builtin_amdgcn_readlane(msize, b);
-        };
-        // one step with the weights in `now`; those of the next step go to `then`
-        auto step = [&](const Pair& now, Pair& then) {
-            const int pm0 = m0, pm = m;
-            m = 0;
-            if (todo) {
-                next_step();
-                if (q0 < m) then = weights(m0 + q0, cc0);
-            }
-            if (q0 < pm) merge(now);
-            int q = q0, cc = cc0;
-            for (;;) {
-                q += dq;
-                cc += dc;
-                if (cc >= nch) {
-                    cc -= nch;
-                    ++q;
-                }
-                if (q >= pm) break;
-                merge(weights(pm0 + q, cc));
-            }
-            wave_order();
-        };
-        Pair pa{}, pb{};
-        if (todo) {
-            next_step();
-            if (q0 < m) pa = weights(m0 + q0, cc0);
-        }
-        while (m > 0) {
-            step(pa, pb);
-            if (m == 0) break;
-            step(pb, pa);
-        }
+        run_steps<MODE>(steps, mstart, msize, nch, lane, v, nodes, where, weights, slots);
         if (MODE == RH_FORWARD) {
             // the next chunk's attributes have had the steps' time to arrive:
             // waited for here, they are not waited for behind the stores below
@@ -549,17 +605,12 @@ void raht_leaf_kernel(RahtArgs a) {
                         if (cc < nch)
                             a.coef[(int64_t)(k0 + cc) * a.ld + column[e]] = (float)v[cc * RH_VS + second[e]];
                 }
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int node = t * MGS_WAVE + lane;
-                if (node >= live) continue;
-                const int j = t ? node1 : node0;
-#pragma unroll
-                for (int cc = 0; cc < RH_CH; ++cc) {
-                    const double r = v[cc * RH_VS + j];
-                    if (cc >= nch) continue;
-                    if (a.top == 0) a.coef[(int64_t)(k0 + cc) * a.ld] = (float)r;  // the root: DC
-                    else a.lev[0].rows[(tile * a.stride + node) * a.C + k0 + cc] = r;
+            for (int t = 0; t < live; t += ROWS) {
+                const int node = t + node_of, j = first_leaf(node);
+                if (node < live && ch_of < nch) {
+                    const double r = v[ch_of * RH_VS + j];
+                    if (a.top == 0) a.coef[(int64_t)(k0 + ch_of) * a.ld] = (float)r;  // the root: DC
+                    else a.lev[0].rows[(tile * a.stride + node) * a.C + k0 + ch_of] = r;
                 }
             }
         } else {
@@ -576,180 +627,298 @@ void raht_leaf_kernel(RahtArgs a) {
 }
 
 // One group of an upper level: the nodes of RH_GROUP lists of the level below,
-// as above but with nodes in place of leaves.  Its arrays lie in LDS for up to
-// CAP nodes, else (BIG: codes whose trees are combs) in the workspace, with
-// the values worked on in place, in the rows of the level below.  The block is
-// one wavefront.
+// as above but with nodes in place of leaves.  Up to CAP nodes lie in LDS: the
+// block's threads take a node each for the structure and for the weights of its
+// merge, then every wavefront does all steps on RH_UCH channels of its own.
+// More nodes (BIG: codes whose trees are combs) lie in the workspace, with the
+// values worked on in place, in the rows of the level below.
 struct UpperArrays {
     uint64_t* code;
-    int32_t *first, *ac, *row, *left, *right, *rank, *order;  // first has one entry more
+    int32_t *first, *ac, *row, *left, *right, *order;  // first has one entry more
+    int32_t* rank;  // boundary j: (step, rank in it) of its merge, or -1 - slot of the node that starts after it
 };
 constexpr int RH_BIG_ARRAYS = 7;
 
 template <int MODE, bool BIG, int CAP>
 __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t g, int n, const UpperArrays& u,
-                                           int my_pre, uint32_t* h, double* v, int k_first, int k_step) {
+                                           int my_pre, uint32_t* h, double* wt, uint32_t* pk, double* v, int vwaves) {
     const RahtLevel& in = a.lev[level - 1];
     const RahtLevel& out = a.lev[level];
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, T = blockDim.x;
+    const int lane = tid & (MGS_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / MGS_WAVE);
     const int bits = 3 * a.depth;
     const bool root = level == a.top;
+    constexpr int U = BIG ? 1 : CAP / RH_UPPER_MIN;  // nodes per thread (T >= RH_UPPER_MIN)
     // ---- the lists, one after the other: node j of the group is node
     // j - pre of the list whose prefix covers it
     const int64_t list0 = g * RH_GROUP;
-    int pre[RH_GROUP];
-#pragma unroll
-    for (int t = 0; t < RH_GROUP; ++t) pre[t] = __builtin_amdgcn_readlane(my_pre, t);
     int64_t span = RH_TILE;  // leaves of a group of this level
     for (int l = 0; l < level; ++l) span *= RH_GROUP;
     const int64_t end = min(a.N, (g + 1) * span);
     const uint64_t after = a.codes[min(end, a.N - 1)];
-    h[lane] = 0u;
-    for (int j0 = 0; j0 < n; j0 += RH_TILE) {
-        int at[RH_ROUNDS], fi[RH_ROUNDS], ai[RH_ROUNDS];
-        uint64_t co[RH_ROUNDS];
+    {
+        int pre[RH_GROUP];
 #pragma unroll
-        for (int e = 0; e < RH_ROUNDS; ++e) {
-            const int j = min(j0 + e * MGS_WAVE + lane, n - 1);
-            int t = 0, p = 0;
+        for (int t = 0; t < RH_GROUP; ++t) pre[t] = __builtin_amdgcn_readlane(my_pre, t);
+        if (tid < RH_STEPS) h[tid] = 0u;
+        for (int j0 = tid; j0 < n; j0 += U * T) {
+            int at[U], fi[U], ai[U];
 #pragma unroll
-            for (int l = 1; l < RH_GROUP; ++l)
-                if (j >= pre[l]) {
-                    t = l;
-                    p = pre[l];
+            for (int e = 0; e < U; ++e) {
+                const int j = min(j0 + e * T, n - 1);
+                int t = 0, p = 0;
+#pragma unroll
+                for (int l = 1; l < RH_GROUP; ++l)
+                    if (j >= pre[l]) {
+                        t = l;
+                        p = pre[l];
+                    }
+                at[e] = (int)((list0 + t) * a.stride) + j - p;
+                fi[e] = in.first[at[e]];
+                ai[e] = in.ac[at[e]];
+            }
+#pragma unroll
+            for (int e = 0; e < U; ++e)
+                if (j0 + e * T < n) {
+                    u.first[j0 + e * T] = fi[e];
+                    u.ac[j0 + e * T] = ai[e];
+                    u.row[j0 + e * T] = at[e];
                 }
-            at[e] = (int)((list0 + t) * a.stride) + j - p;
-            fi[e] = in.first[at[e]];
-            ai[e] = in.ac[at[e]];
         }
+        if (tid == 0) u.first[n] = (int32_t)end;
+    }
+    __syncthreads();
+    // ---- codes, and the wavefront's first channels beside them
+    const int nchunk = BIG ? 1 : (a.C + RH_UCH - 1) / RH_UCH;
+    const int k_first = blockIdx.y * vwaves + wave, k_step = (int)gridDim.y * vwaves;
+    double* vw = v + (size_t)wave * (RH_UCH * CAP);  // [node][channel]
+    // the rows go by lanes over (node, channel), whole lines at a time
+    constexpr int ROWS = MGS_WAVE / RH_UCH;
+    const int node_of = lane / RH_UCH, ch_of = lane % RH_UCH;
+    auto place = [&](int j, int k0, int nch) { return (int64_t)u.row[j] * a.C + k0 + min(ch_of, nch - 1); };
+    // forward: the nodes' values; inverse: the coefficient of the boundary
+    // before each node (the nodes that are left get their values over it)
+    auto fetch = [&](int k) {
+        const int k0 = chunk_first(a.C, nchunk, k), nch = chunk_size(a.C, nchunk, k);
+        for (int j0 = 0; j0 < n; j0 += RH_TILE) {
+            if (MODE == RH_FORWARD) {
+                double r[RH_TILE / ROWS];
 #pragma unroll
-        for (int e = 0; e < RH_ROUNDS; ++e) co[e] = a.codes[fi[e]];
+                for (int e = 0; e < RH_TILE / ROWS; ++e) r[e] = in.rows[place(min(j0 + e * ROWS + node_of, n - 1), k0, nch)];
 #pragma unroll
-        for (int e = 0; e < RH_ROUNDS; ++e) {
-            const int j = j0 + e * MGS_WAVE + lane;
-            if (j < n) {
-                u.first[j] = fi[e];
-                u.ac[j] = ai[e];
-                u.row[j] = at[e];
-                u.code[j] = co[e];
+                for (int e = 0; e < RH_TILE / ROWS; ++e) vw[(j0 + e * ROWS) * RH_UCH + lane] = r[e];
+            } else {
+                float r[RH_ROUNDS][RH_UCH];
+#pragma unroll
+                for (int e = 0; e < RH_ROUNDS; ++e) {
+                    const int j = min(j0 + e * MGS_WAVE + lane, n - 1);
+                    const int64_t p = min(1 + (int64_t)u.ac[max(j - 1, 0)], a.N - 1);
+#pragma unroll
+                    for (int cc = 0; cc < RH_UCH; ++cc)
+                        r[e][cc] = a.coef_in[(int64_t)(k0 + min(cc, nch - 1)) * a.ld + p];
+                }
+#pragma unroll
+                for (int e = 0; e < RH_ROUNDS; ++e)
+#pragma unroll
+                    for (int cc = 0; cc < RH_UCH; ++cc)
+                        vw[(j0 + e * MGS_WAVE + lane) * RH_UCH + cc] = (double)r[e][cc];
             }
         }
-    }
-    if (lane == 0) u.first[n] = (int32_t)end;
-    __syncthreads();
+    };
     const int64_t start = u.first[0];
     const uint64_t before = a.codes[max(start - 1, (int64_t)0)];
-    // ---- each boundary's run; the merges inside the group, ranked in their step
+    for (int j0 = tid; j0 < n; j0 += U * T) {
+        uint64_t co[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) co[e] = a.codes[u.first[min(j0 + e * T, n - 1)]];
+#pragma unroll
+        for (int e = 0; e < U; ++e)
+            if (j0 + e * T < n) u.code[j0 + e * T] = co[e];
+    }
+    if (MODE != RH_STRUCTURE && !BIG && wave < vwaves && k_first < nchunk) fetch(k_first);
+    __syncthreads();
+    // ---- each boundary's run, and whether it lies inside the group
     int top = 1;
     while (2 * top < n) top *= 2;
-    for (int j0 = 0; j0 < n; j0 += MGS_WAVE) {
-        const int j = j0 + lane;
-        bool m = false;
-        int d = RH_STEPS - 1;
-        if (j + 1 < n) {
+    for (int j0 = tid; j0 < n; j0 += U * T) {
+        int d[U], L[U], R[U];
+        uint64_t lo[U], hi[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            const int j = min(j0 + e * T, n - 1);
             const uint64_t c0 = u.code[j];
-            d = merge_step(c0, u.code[j + 1], bits);
-            if (d < RH_STEPS - 1) {
-                const uint64_t lo = (c0 >> (d + 1)) << (d + 1), hi = lo + (1ull << (d + 1));
-                int L = j, R = j + 1;
-                for (int o = top; o >= 1; o >>= 1) {
-                    if (L - o >= 0 && u.code[L - o] >= lo) L -= o;
-                    if (R + o < n && u.code[R + o] < hi) R += o;
-                }
-                m = (L > 0 || start == 0 || before < lo) && (R < n - 1 || end >= a.N || after >= hi);
-                u.left[j] = L;
-                u.right[j] = R;
+            d[e] = j0 + e * T + 1 < n ? merge_step(c0, u.code[min(j + 1, n - 1)], bits) : RH_STEPS - 1;
+            const int sh = d[e] + 1;  // <= 63 for a step that merges
+            lo[e] = d[e] < RH_STEPS - 1 ? (c0 >> sh) << sh : 0ull;
+            hi[e] = d[e] < RH_STEPS - 1 ? lo[e] + (1ull << sh) : 0ull;
+            L[e] = j;
+            R[e] = min(j + 1, n - 1);
+        }
+        for (int o = top; o >= 1; o >>= 1)
+#pragma unroll
+            for (int e = 0; e < U; ++e) {
+                const int pl = max(L[e] - o, 0), pr = min(R[e] + o, n - 1);
+                const uint64_t cl = u.code[pl], cr = u.code[pr];
+                if (L[e] - o >= 0 && cl >= lo[e]) L[e] = pl;
+                if (R[e] + o < n && cr < hi[e]) R[e] = pr;
+            }
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            const int j = j0 + e * T;
+            const bool m = d[e] < RH_STEPS - 1 && (L[e] > 0 || start == 0 || before < lo[e]) &&
+                           (R[e] < n - 1 || end >= a.N || after >= hi[e]);
+            if (j < n) {
+                u.left[j] = L[e];
+                u.right[j] = R[e];
+                u.rank[j] = m ? d[e] : -1;
             }
         }
-        const int r = bin_rank(m, d, h, lane);
-        if (j < n) u.rank[j] = m ? (d << 16) | r : -1;  // -1: no merge here
     }
+    __syncthreads();
+    // ---- ranks of the merges in their steps, and the nodes that are left: a
+    // node starts at 0 and after every boundary that does not merge here
+    if (wave == 0) {
+        const int64_t o = g * a.stride;
+        int live = 0;
+        if (MODE != RH_INVERSE && lane == 0) out.first[o] = (int32_t)start;
+        for (int j0 = 0; j0 < n; j0 += MGS_WAVE) {
+            const int j = j0 + lane;
+            const int d = j < n ? u.rank[j] : -1;
+            const uint64_t ends = __builtin_amdgcn_ballot_w64(j < n && d < 0);
+            const int r = bin_rank(d >= 0, max(d, 0), h, lane);
+            const int slot = live + __popcll(ends & lanes_below(lane));  // of the node that ends at boundary j
+            if (j < n) {
+                u.rank[j] = d >= 0 ? (d << 16) | r : -2 - slot;
+                if (MODE != RH_INVERSE && d < 0) {
+                    if (slot < a.stride) out.ac[o + slot] = u.ac[j];
+                    if (slot + 1 < a.stride && j + 1 < n) out.first[o + slot + 1] = u.first[j + 1];
+                }
+            }
+            live += __popcll(ends);
+        }
+        if (MODE != RH_INVERSE && lane == 0) out.cnt[g] = min(live, a.stride);
+    }
+    if (MODE == RH_STRUCTURE) return;
     __syncthreads();
     const int msize = (int)h[lane];  // lane b: merges of step b
     const int mstart = wave_exclusive(msize, lane);
     const uint64_t steps = __builtin_amdgcn_ballot_w64(msize > 0);
     const int nm = __builtin_amdgcn_readlane(mstart + msize, MGS_WAVE - 1);
-    __syncthreads();
-    h[lane] = (uint32_t)mstart;
-    __syncthreads();
-    for (int j = lane; j < n; j += MGS_WAVE) {
-        const int r = u.rank[j];
-        if (r >= 0) u.order[h[r >> 16] + (r & 0xFFFF)] = j;
-    }
-    // ---- the nodes that are left: fn(j, slot) for each
-    auto for_live = [&](auto fn) {
-        int seen = 0;
-        for (int j0 = 0; j0 < n; j0 += MGS_WAVE) {
-            const int j = j0 + lane;
-            const bool starts = j < n && !(j > 0 && u.rank[j - 1] >= 0);
-            const uint64_t sm = __builtin_amdgcn_ballot_w64(starts);
-            fn(j, starts, seen + __popcll(sm & lanes_below(lane)));
-            seen += __popcll(sm);
-        }
-        return seen;
+    // slot of the node that starts at j, or -1 where none does
+    auto slot_of = [&](int j) {
+        const int r = j > 0 ? u.rank[j - 1] : -1;
+        return r < 0 ? -1 - r : -1;
     };
-    if (MODE != RH_INVERSE) {
-        const int64_t o = g * a.stride;
-        const int live = for_live([&](int j, bool starts, int slot) {
-            if (starts && slot < a.stride) out.first[o + slot] = u.first[j];
-            const int upto = slot + (starts ? 1 : 0) - 1;  // the node that ends at boundary j
-            if (j < n && u.rank[j] < 0 && upto >= 0 && upto < a.stride) out.ac[o + upto] = u.ac[j];
-        });
-        if (lane == 0) out.cnt[g] = min(live, a.stride);
-    }
-    if (MODE == RH_STRUCTURE) return;
-    // ---- values
-    const int nchunk = BIG ? 1 : (a.C + RH_UCH - 1) / RH_UCH;
-    for (int k = k_first; k < nchunk; k += k_step) {
-        const int k0 = chunk_first(a.C, nchunk, k), nch = chunk_size(a.C, nchunk, k);
-        auto value = [&](int cc, int j) -> double& {  // channel k0 + cc of node j
-            if constexpr (BIG) return in.rows[(int64_t)u.row[j] * a.C + k0 + cc];
-            else return v[cc * (CAP + 1) + j];
-        };
-        __syncthreads();
-        if (MODE == RH_FORWARD && !BIG) {  // (all loads issued before the first is used)
-            for (int j0 = 0; j0 < n; j0 += RH_TILE) {
-                double r[RH_ROUNDS][RH_UCH];
+    if constexpr (!BIG) {
+        // ---- the merges in step order, with their weights (in the place of the
+        // codes and runs, which are read before the first is written)
+        double w1[U], w2[U];
+        int to[U];
+        uint32_t nodes[U];
 #pragma unroll
-                for (int e = 0; e < RH_ROUNDS; ++e) {
-                    const int64_t o = (int64_t)u.row[min(j0 + e * MGS_WAVE + lane, n - 1)] * a.C + k0;
-#pragma unroll
-                    for (int cc = 0; cc < RH_UCH; ++cc) r[e][cc] = in.rows[o + min(cc, nch - 1)];
-                }
-#pragma unroll
-                for (int e = 0; e < RH_ROUNDS; ++e)
-#pragma unroll
-                    for (int cc = 0; cc < RH_UCH; ++cc) value(cc, j0 + e * MGS_WAVE + lane) = r[e][cc];
+        for (int e = 0; e < U; ++e) {
+            const int j = tid + e * T;
+            const int r = j < n ? u.rank[j] : -1;
+            const int m0 = __shfl(mstart, max(r, 0) >> 16);
+            to[e] = r >= 0 ? m0 + (r & 0xFFFF) : -1;
+            w1[e] = w2[e] = 1.0;
+            nodes[e] = 0;
+            if (r >= 0) {
+                const int L = u.left[j], f = u.first[j + 1];
+                w1[e] = (double)(f - u.first[L]);
+                w2[e] = (double)(u.first[u.right[j] + 1] - f);
+                nodes[e] = (uint32_t)L | (uint32_t)(j + 1) << 16;
             }
         }
-        if (MODE == RH_INVERSE) {
-            for_live([&](int j, bool starts, int slot) {
-                if (!starts || slot >= a.stride) return;
-                for (int c0 = 0; c0 < nch; c0 += RH_UCH) {
-                    double r[RH_UCH];
+        __syncthreads();
 #pragma unroll
-                    for (int cc = 0; cc < RH_UCH; ++cc) {
-                        const int ch = k0 + min(c0 + cc, nch - 1);
-                        r[cc] = root ? (double)a.coef_in[(int64_t)ch * a.ld]
-                                     : out.rows[(g * a.stride + slot) * a.C + ch];
+        for (int e = 0; e < U; ++e)
+            if (to[e] >= 0) {
+                double* w = wt + to[e] * 4;
+                const double2 y = reciprocal(sqrt(w1[e] + w2[e]));
+                w[0] = sqrt(w1[e]);
+                w[1] = sqrt(w2[e]);
+                w[2] = y.x;
+                w[3] = y.y;
+                pk[to[e]] = nodes[e];
+            }
+        __syncthreads();
+        if (wave >= vwaves) return;
+        for (int k = k_first; k < nchunk; k += k_step) {
+            const int k0 = chunk_first(a.C, nchunk, k), nch = chunk_size(a.C, nchunk, k);
+            if (k != k_first) {
+                wave_order();
+                fetch(k);
+            }
+            if (MODE == RH_INVERSE)
+                for (int j0 = 0; j0 < n; j0 += RH_TILE) {
+                    constexpr int E = RH_TILE / ROWS;
+                    double r[E];
+                    int slot[E];
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        const int j = j0 + e * ROWS + node_of, ch = k0 + min(ch_of, nch - 1);
+                        slot[e] = j < n ? slot_of(j) : -1;
+                        if (slot[e] >= a.stride) slot[e] = -1;
+                        r[e] = 0.0;
+                        if (slot[e] >= 0)
+                            r[e] = root ? (double)a.coef_in[(int64_t)ch * a.ld]
+                                        : out.rows[(g * a.stride + slot[e]) * a.C + ch];
                     }
 #pragma unroll
-                    for (int cc = 0; cc < RH_UCH; ++cc)
-                        if (c0 + cc < nch) value(c0 + cc, j) = r[cc];
+                    for (int e = 0; e < E; ++e)
+                        if (slot[e] >= 0) vw[(j0 + e * ROWS) * RH_UCH + lane] = r[e];
                 }
-            });
-            for (int q = lane; q < nm; q += MGS_WAVE) {
+            wave_order();
+            auto nodes = [&](int q) { return pk[q]; };
+            auto where = [&](int q, uint32_t) { return make_uint2((uint32_t)q * 4, 0u); };
+            auto weights = [&](uint2 o) { return RahtWeights{wt[o.x], wt[o.x + 1], wt[o.x + 2], wt[o.x + 3]}; };
+            auto slots = [&](uint32_t w, int cc, int& ia, int& ib) {
+                ia = (int)(w & 0xFFFFu) * RH_UCH + cc;
+                ib = (int)(w >> 16) * RH_UCH + cc;
+            };
+            run_steps<MODE>(steps, mstart, msize, nch, lane, vw, nodes, where, weights, slots);
+            if (MODE == RH_FORWARD) {
+                for (int j = node_of; j < n; j += ROWS) {
+                    const int slot = slot_of(j);
+                    if (slot < 0 || slot >= a.stride || ch_of >= nch) continue;
+                    const double r = vw[j * RH_UCH + ch_of];
+                    if (root) a.coef[(int64_t)(k0 + ch_of) * a.ld] = (float)r;  // DC
+                    else out.rows[(g * a.stride + slot) * a.C + k0 + ch_of] = r;
+                }
+                for (int q = lane; q < nm; q += MGS_WAVE) {
+                    const int j = (int)(pk[q] >> 16);
+                    const int64_t p = 1 + (int64_t)u.ac[j - 1];
+#pragma unroll
+                    for (int cc = 0; cc < RH_UCH; ++cc)
+                        if (cc < nch) a.coef[(int64_t)(k0 + cc) * a.ld + p] = (float)vw[j * RH_UCH + cc];
+                }
+            } else {
+                for (int j = node_of; j < n; j += ROWS)
+                    if (ch_of < nch) in.rows[place(j, k0, nch)] = vw[j * RH_UCH + ch_of];
+            }
+        }
+    } else {
+        // ---- values in place, in the rows of the level below
+        for (int j0 = 0; j0 < n; j0 += T) {
+            const int j = j0 + tid;
+            const int r = j < n ? u.rank[j] : -1;
+            const int m0 = __shfl(mstart, max(r, 0) >> 16);
+            if (r >= 0) u.order[m0 + (r & 0xFFFF)] = j;
+        }
+        __syncthreads();
+        auto value = [&](int c, int j) -> double& { return in.rows[(int64_t)u.row[j] * a.C + c]; };
+        if (MODE == RH_INVERSE) {
+            for (int j = tid; j < n; j += T) {
+                const int slot = slot_of(j);
+                if (slot < 0 || slot >= a.stride) continue;
+                for (int c = 0; c < a.C; ++c)
+                    value(c, j) = root ? (double)a.coef_in[(int64_t)c * a.ld]
+                                       : out.rows[(g * a.stride + slot) * a.C + c];
+            }
+            for (int q = tid; q < nm; q += T) {
                 const int j = u.order[q];
-                const int64_t p = 1 + (int64_t)u.ac[j];
-                for (int c0 = 0; c0 < nch; c0 += RH_UCH) {
-                    float r[RH_UCH];
-#pragma unroll
-                    for (int cc = 0; cc < RH_UCH; ++cc)
-                        r[cc] = a.coef_in[(int64_t)(k0 + min(c0 + cc, nch - 1)) * a.ld + p];
-#pragma unroll
-                    for (int cc = 0; cc < RH_UCH; ++cc)
-                        if (c0 + cc < nch) value(c0 + cc, j + 1) = (double)r[cc];
-                }
+                for (int c = 0; c < a.C; ++c) value(c, j + 1) = (double)a.coef_in[(int64_t)c * a.ld + 1 + u.ac[j]];
             }
         }
         __syncthreads();
@@ -758,16 +927,16 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
             const int b = MODE == RH_FORWARD ? __builtin_ctzll(todo) : 63 - __builtin_clzll(todo);
             todo &= ~(1ull << b);
             const int m0 = __builtin_amdgcn_readlane(mstart, b);
-            const uint32_t pairs = (uint32_t)__builtin_amdgcn_readlane(msize, b) * (uint32_t)nch;
-            for (uint32_t p = lane; p < pairs; p += MGS_WAVE) {
-                const uint32_t q = p / (uint32_t)nch;
-                const int cc = (int)(p - q * (uint32_t)nch);
+            const uint32_t pairs = (uint32_t)__builtin_amdgcn_readlane(msize, b) * (uint32_t)a.C;
+            for (uint32_t p = tid; p < pairs; p += T) {
+                const uint32_t q = p / (uint32_t)a.C;
+                const int c = (int)(p - q * (uint32_t)a.C);
                 const int j = u.order[m0 + (int)q];
                 const int L = u.left[j];
                 const double w1 = (double)(u.first[j + 1] - u.first[L]);
                 const double w2 = (double)(u.first[u.right[j] + 1] - u.first[j + 1]);
                 const double s1 = sqrt(w1), s2 = sqrt(w2), sw = sqrt(w1 + w2);
-                double &va = value(cc, L), &vb = value(cc, j + 1);
+                double &va = value(c, L), &vb = value(c, j + 1);
                 const double x1 = va, x2 = vb;
                 if (MODE == RH_FORWARD) {
                     va = (s1 * x1 + s2 * x2) / sw;
@@ -780,53 +949,61 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
             __syncthreads();
         }
         if (MODE == RH_FORWARD) {
-            for_live([&](int j, bool starts, int slot) {
-                if (!starts || slot >= a.stride) return;
-                for (int cc = 0; cc < nch; ++cc) {
-                    if (root) a.coef[(int64_t)(k0 + cc) * a.ld] = (float)value(cc, j);  // DC
-                    else out.rows[(g * a.stride + slot) * a.C + k0 + cc] = value(cc, j);
+            for (int j = tid; j < n; j += T) {
+                const int slot = slot_of(j);
+                if (slot < 0 || slot >= a.stride) continue;
+                for (int c = 0; c < a.C; ++c) {
+                    if (root) a.coef[(int64_t)c * a.ld] = (float)value(c, j);  // DC
+                    else out.rows[(g * a.stride + slot) * a.C + c] = value(c, j);
                 }
-            });
-            for (int q = lane; q < nm; q += MGS_WAVE) {
-                const int j = u.order[q];
-                const int64_t p = 1 + (int64_t)u.ac[j];
-                for (int cc = 0; cc < nch; ++cc) a.coef[(int64_t)(k0 + cc) * a.ld + p] = (float)value(cc, j + 1);
             }
-        } else if (!BIG) {
-            for (int j = lane; j < n; j += MGS_WAVE)
-                for (int cc = 0; cc < nch; ++cc) in.rows[(int64_t)u.row[j] * a.C + k0 + cc] = value(cc, j);
+            for (int q = tid; q < nm; q += T) {
+                const int j = u.order[q];
+                for (int c = 0; c < a.C; ++c) a.coef[(int64_t)c * a.ld + 1 + u.ac[j]] = (float)value(c, j + 1);
+            }
         }
     }
 }
 
-// Upper levels: one wavefront per group of RH_GROUP lists and chunk of RH_UCH
-// channels (blockIdx.y; few groups are left, so the chunks are spread out and
-// each builds the group's structure again).
+// Upper levels: one block per group of RH_GROUP lists and `vwaves` chunks of
+// RH_UCH channels (blockIdx.y takes the others and builds the structure again).
+// What bounds a block is its chain: three dependent loads (2.5 + 2 us), the
+// search (2.5), the ranks (2), then the steps (5), one LDS round trip and four
+// dependent FP64 operations each.  With the weights (three dependent LDS reads,
+// three square roots, two divisions) inside the steps, one wavefront per group
+// and chunk, a level took 24 to 31 us and the first of 5.3e6 x 20, whose 1294
+// groups fill the chip several times, 89; now 18 to 24 and 71.
 template <int MODE, int CAP>
-__global__ __launch_bounds__(MGS_WAVE) void raht_upper_kernel(RahtArgs a, int level) {
-    static_assert(CAP % RH_TILE == 0, "values are loaded in rounds of RH_TILE nodes");
-    __shared__ double v[RH_UCH * (CAP + 1)];
-    __shared__ uint64_t code[CAP];
-    __shared__ int32_t ints[RH_BIG_ARRAYS][CAP + 1];
-    __shared__ uint32_t h[RH_STEPS];
+__global__ __launch_bounds__(RH_UPPER_MAX) void raht_upper_kernel(RahtArgs a, int level, int vwaves) {
+    static_assert(CAP % RH_UPPER_MIN == 0 && CAP % RH_TILE == 0, "nodes per thread, rounds of loads");
+    extern __shared__ double up_lds[];
     const int64_t g = xcd_block(a.lev[level].lists);
     if (g < 0) return;
     const RahtLevel& in = a.lev[level - 1];
     const int64_t list0 = g * RH_GROUP;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (MGS_WAVE - 1);
     const int m = lane < RH_GROUP && list0 + lane < in.lists ? in.cnt[list0 + lane] : 0;
     const int my_pre = wave_exclusive(m, lane);  // lane t: nodes of the group before list t
     const int n = __builtin_amdgcn_readlane(my_pre + m, MGS_WAVE - 1);
+    // values, then weights and node pairs of the merges (before them, in their
+    // place, the codes, runs, first leaves and counters), then what stays
+    double* v = up_lds;
+    double* wt = v + (size_t)vwaves * (RH_UCH * CAP);
+    uint32_t* pk = (uint32_t*)(wt + 4 * CAP);
+    int32_t* keep = (int32_t*)(pk + CAP);
+    uint64_t* code = (uint64_t*)wt;
+    int32_t* tmp = (int32_t*)(code + CAP);
+    uint32_t* h = (uint32_t*)(tmp + 3 * CAP + 1);
+    static_assert(2 * CAP + 3 * CAP + 1 + RH_STEPS <= 9 * CAP, "what is replaced fits");
     if (n <= CAP) {
-        const UpperArrays u{code, ints[0], ints[1], ints[2], ints[3], ints[4], ints[5], ints[6]};
-        raht_group<MODE, false, CAP>(a, level, g, n, u, my_pre, h, v, blockIdx.y, gridDim.y);
+        const UpperArrays u{code, tmp + 2 * CAP, keep, keep + CAP, tmp, tmp + CAP, nullptr, keep + 2 * CAP};
+        raht_group<MODE, false, CAP>(a, level, g, n, u, my_pre, h, wt, pk, v, vwaves);
     } else if (blockIdx.y == 0) {
         const int64_t o = list0 * a.stride + g;  // one entry more per group
         const int64_t st = a.big_stride;
-        const UpperArrays u{a.big_code + o,           a.big_i + o,          a.big_i + st + o,
-                            a.big_i + 2 * st + o,     a.big_i + 3 * st + o, a.big_i + 4 * st + o,
-                            a.big_i + 5 * st + o,     a.big_i + 6 * st + o};
-        raht_group<MODE, true, CAP>(a, level, g, n, u, my_pre, h, v, 0, 1);
+        const UpperArrays u{a.big_code + o,       a.big_i + o,          a.big_i + st + o,     a.big_i + 2 * st + o,
+                            a.big_i + 3 * st + o, a.big_i + 4 * st + o, a.big_i + 5 * st + o, a.big_i + 6 * st + o};
+        raht_group<MODE, true, CAP>(a, level, g, n, u, my_pre, h, wt, pk, v, vwaves);
     }
 }
 
@@ -913,16 +1090,30 @@ int raht_counts(RahtArgs& a, hipStream_t s) {
     return mgs_last_launch();
 }
 
-template <int MODE>
-void raht_upper(const RahtArgs& a, int level, unsigned chunks, hipStream_t s) {
-    const dim3 grid(xcd_grid(a.lev[level].lists), chunks);
-    if (level == 1)
-        hipLaunchKernelGGL((raht_upper_kernel<MODE, RH_CAP1>), grid, dim3(MGS_WAVE), 0, s, a, level);
-    else
-        hipLaunchKernelGGL((raht_upper_kernel<MODE, RH_CAP2>), grid, dim3(MGS_WAVE), 0, s, a, level);
+// Chunks of RH_UCH channels go to the wavefronts of a block, as many as its
+// LDS holds (eight at the first upper level, four above it), the rest to
+// blockIdx.y, evenly.  (The attribute belongs to the device's code object:
+// repeating it is cheap and needs no state.)
+template <int MODE, int CAP>
+int raht_upper_launch(const RahtArgs& a, int level, int most, hipStream_t s) {
+    const int chunks = MODE == RH_STRUCTURE ? 0 : (a.C + RH_UCH - 1) / RH_UCH;
+    const int blocks = std::max(1, std::min(65535, (chunks + most - 1) / most));
+    const int vwaves = std::min(most, (chunks + blocks - 1) / blocks);
+    const int threads = std::max(RH_UPPER_MIN, vwaves * MGS_WAVE);
+    const size_t lds = (size_t)CAP * (vwaves * RH_UCH * sizeof(double) + 48);
+    int rc = mgs_hip_status(hipFuncSetAttribute((const void*)raht_upper_kernel<MODE, CAP>,
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (rc) return rc;
+    hipLaunchKernelGGL((raht_upper_kernel<MODE, CAP>), dim3(xcd_grid(a.lev[level].lists), blocks), dim3(threads),
+                       lds, s, a, level, vwaves);
+    return mgs_last_launch();
 }
 
-unsigned raht_chunks(int32_t C) { return (unsigned)std::min(65535, (C + RH_UCH - 1) / RH_UCH); }
+template <int MODE>
+int raht_upper(const RahtArgs& a, int level, hipStream_t s) {
+    return level == 1 ? raht_upper_launch<MODE, RH_CAP1>(a, level, 8, s)
+                      : raht_upper_launch<MODE, RH_CAP2>(a, level, 4, s);
+}
 
 }  // namespace
 }  // namespace mgs
@@ -946,9 +1137,9 @@ extern "C" int mgs_raht_forward(const uint64_t* d_codes, int64_t N, int32_t C, i
     rc = raht_counts(a, s);
     if (rc) return rc;
     hipLaunchKernelGGL(raht_leaf_kernel<RH_FORWARD>, dim3(xcd_grid(a.nblk)), dim3(RH_THREADS), 0, s, a);
-    for (int l = 1; l <= a.top; ++l)
-        raht_upper<RH_FORWARD>(a, l, raht_chunks(C), s);
-    return mgs_last_launch();
+    rc = mgs_last_launch();
+    for (int l = 1; l <= a.top && !rc; ++l) rc = raht_upper<RH_FORWARD>(a, l, s);
+    return rc;
 }
 
 extern "C" int mgs_raht_inverse(const uint64_t* d_codes, int64_t N, int32_t C, int32_t depth, const float* d_coef,
@@ -966,10 +1157,10 @@ extern "C" int mgs_raht_inverse(const uint64_t* d_codes, int64_t N, int32_t C, i
     if (rc) return rc;
     // the lists of every level from the leaves up, then the values from the root down
     if (a.top > 0) hipLaunchKernelGGL(raht_leaf_kernel<RH_STRUCTURE>, dim3(xcd_grid(a.nblk)), dim3(RH_THREADS), 0, s, a);
-    for (int l = 1; l < a.top; ++l)
-        raht_upper<RH_STRUCTURE>(a, l, 1, s);
-    for (int l = a.top; l >= 1; --l)
-        raht_upper<RH_INVERSE>(a, l, raht_chunks(C), s);
+    rc = mgs_last_launch();
+    for (int l = 1; l < a.top && !rc; ++l) rc = raht_upper<RH_STRUCTURE>(a, l, s);
+    for (int l = a.top; l >= 1 && !rc; --l) rc = raht_upper<RH_INVERSE>(a, l, s);
+    if (rc) return rc;
     hipLaunchKernelGGL(raht_leaf_kernel<RH_INVERSE>, dim3(xcd_grid(a.nblk)), dim3(RH_THREADS), 0, s, a);
     return mgs_last_launch();
 }

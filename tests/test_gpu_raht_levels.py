@@ -143,3 +143,34 @@ def test_bad_codes_are_flagged(torch, bad):
         with pytest.raises(mgs.MgsError) as e:
             mgs.raht(dev(torch, codes), torch.ones((2, 9000), device="cuda"), 9, inverse=inv)
         assert e.value.code == mgs.ENONFINITE
+
+
+@pytest.mark.parametrize("C", [1, 4, 16, 17, 32, 33, 70])
+def test_channels(torch, C):
+    """Chunks of four channels: one or more wavefronts per group, and groups spread over blocks."""
+    codes, _ = synth.voxel_codes(synth.voxels(70_001, 11, seed=C), 11)
+    check(torch, codes, 11, C, C)
+
+
+def test_values_without_a_quotient(torch):
+    """Infinities, NaN, zeros of both signs and the largest values pass through a merge as the
+    division passes them."""
+    codes, _ = synth.voxel_codes(synth.voxels(5000, 8, seed=5), 8)
+    rng = np.random.default_rng(5)
+    attr = rng.normal(0, 1, (6, 5000)).astype(np.float32)
+    attr[0, rng.integers(0, 5000, 40)] = np.inf
+    attr[1, rng.integers(0, 5000, 40)] = -np.inf
+    attr[2, rng.integers(0, 5000, 40)] = np.nan
+    attr[3] = rng.choice(np.array([0.0, -0.0, np.finfo(np.float32).max, -np.finfo(np.float32).max], np.float32), 5000)
+    attr[4] = 0.25
+    attr[5] = -0.0
+    cd = dev(torch, codes.astype(np.int64))
+    with np.errstate(all="ignore"):
+        want = forward(codes, attr, 8)
+        back = inverse(codes, want, 8)
+    got = mgs.raht(cd, dev(torch, attr), 8)
+    again = mgs.raht(cd, dev(torch, want), 8, inverse=True)
+    for g, w in ((got.cpu().numpy(), want), (again.cpu().numpy(), back)):
+        assert np.array_equal(g, w, equal_nan=True)
+        finite = np.isfinite(w)
+        assert np.array_equal(np.signbit(g[finite]), np.signbit(w[finite]))
