@@ -22,9 +22,11 @@ extern "C" const char* mgs_version(void) { return "libmgs 0.1 (gfx950)"; }
 extern "C" int mgs_status_fetch(const void* d_ws, void* stream) {
     if (!d_ws) return MGS_EWORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    if (hipStreamSynchronize(s) != hipSuccess) return MGS_EDEVICE;
+    // one wait: the copy follows the stream's work and returns when it is done
+    // (after a stream synchronisation a second one, 23 us against 16 behind a
+    // small kernel)
     uint32_t flag = 0;
-    if (hipMemcpy(&flag, d_ws, sizeof(flag), hipMemcpyDeviceToHost) != hipSuccess) return MGS_EDEVICE;
+    if (hipMemcpyWithStream(&flag, d_ws, sizeof(flag), hipMemcpyDeviceToHost, s) != hipSuccess) return MGS_EDEVICE;
     return flag ? MGS_ENONFINITE : MGS_OK;
 }
 

@@ -390,7 +390,7 @@ def vq_assign(x, cb, want_dist: bool = True, ws=None, stream=None, check: bool =
         ws = workspace(need, dev)
     idx = torch.empty(N, dtype=torch.int32, device=dev)
     dist = torch.empty(N, dtype=torch.float64, device=dev) if want_dist else None
-    nfb = torch.zeros(1, dtype=torch.int64, device=dev)
+    nfb = torch.empty(1, dtype=torch.int64, device=dev)  # every call writes it
     _check(lib().mgs_vq_assign(_dptr(x), N, D, _dptr(cb), K, _dptr(idx) if N else None,
                                _dptr(dist) if (dist is not None and N) else None, _dptr(nfb), _dptr(ws),
                                ws.numel(), _stream(stream)), "mgs_vq_assign")
