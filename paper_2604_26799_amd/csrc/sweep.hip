@@ -1023,11 +1023,6 @@ void sweep_kernel(SweepParams p) {
     }
 }
 
-// Copies one scene descriptor (a by-value kernel argument) into device memory.
-__global__ void scene_copy_kernel(SceneDesc sd, SceneDesc* dst) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = sd;
-}
-
 // Position of group g of a ratio with k kept Gaussians along the Gaussian
 // index: the middle of its run of kept positions as a fraction of k,
 // (2 g G + n) times inv = 1 / (2 k) (every position is computed the same
@@ -1045,7 +1040,7 @@ __device__ __forceinline__ double group_pos(int64_t k, int G, int g, double inv)
 // increase with g, so a binary search per ratio); order[rank] = r.  The keep
 // counts and group prefixes come from LDS copies (sk, sg): the searches are
 // chains of dependent reads.
-__device__ void tile_order(const SceneDesc* sc, const int64_t* sk, const int32_t* sg, int r) {
+__device__ __forceinline__ void tile_order(const SceneDesc* sc, const int64_t* sk, const int32_t* sg, int r) {
     const int T = sc->T, G = sc->G;
     int t = 0;
     while (t + 1 < T && sg[t + 1] <= r) ++t;
@@ -1068,56 +1063,62 @@ __device__ void tile_order(const SceneDesc* sc, const int64_t* sk, const int32_t
     sc->order[rank] = r;
 }
 
-// Empty slots (groups past ceil(k_t / G)) hold NaN; the debug histogram is
-// cleared; the status word is reset; every scene gets its tile order.
-__global__ void sweep_init_kernel(SceneDesc* __restrict__ scenes, int count,
-                                  mgs_status_block* status, double* lgtab, int lgtab_max, int K) {
-    if (blockIdx.x == 0 && threadIdx.x < 16) {
-        if (threadIdx.x == 0) status->nonfinite = 0u;
-        status->queue[threadIdx.x] = 0u;
-    }
-    // T(h) = h log2 h for every count a group can hold (FP64, 0 for h < 2),
-    // and the increments F[c] = R(T(c+1)) - R(T(c)) with R the rounding to the
-    // grid 2^-K: sums of increments telescope to R(T(h)) exactly, in any order
-    double* inc = lgtab + (lgtab_max + 1);
-    for (int h = blockIdx.x * blockDim.x + threadIdx.x; h <= lgtab_max; h += gridDim.x * blockDim.x) {
-        const double dh = (double)h, dh1 = (double)(h + 1);
-        const double t0 = h < 2 ? 0.0 : dh * log2(dh);
-        const double t1 = dh1 * log2(dh1);
-        lgtab[h] = t0;
-        inc[h] = grid_round(t1, K) - grid_round(t0, K);
+// One scene: its descriptor (a kernel argument) goes into device memory, its
+// empty slots (groups past ceil(k_t / G)) hold NaN, its debug histogram is
+// cleared and it gets its tile order.  The first scene's launch also resets the
+// status word and makes the tables.  (A launch that only copied the descriptor
+// cost 5 of the 59 us of a sweep of 20,000 x 11.)
+__global__ void sweep_init_kernel(SceneDesc sd, SceneDesc* __restrict__ dst, int first, mgs_status_block* status,
+                                  double* lgtab, int lgtab_max, int K) {
+    static_assert(sizeof(SceneDesc) % sizeof(uint32_t) == 0, "copied by words");
+    const SceneDesc* sc = &sd;
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < (int)(sizeof(SceneDesc) / sizeof(uint32_t)); i += blockDim.x)
+            ((uint32_t*)dst)[i] = ((const uint32_t*)sc)[i];
+    if (first) {
+        if (blockIdx.x == 0 && threadIdx.x < 16) {
+            if (threadIdx.x == 0) status->nonfinite = 0u;
+            status->queue[threadIdx.x] = 0u;
+        }
+        // T(h) = h log2 h for every count a group can hold (FP64, 0 for h < 2),
+        // and the increments F[c] = R(T(c+1)) - R(T(c)) with R the rounding to the
+        // grid 2^-K: sums of increments telescope to R(T(h)) exactly, in any order
+        double* inc = lgtab + (lgtab_max + 1);
+        for (int h = blockIdx.x * blockDim.x + threadIdx.x; h <= lgtab_max; h += gridDim.x * blockDim.x) {
+            const double dh = (double)h, dh1 = (double)(h + 1);
+            const double t0 = h < 2 ? 0.0 : dh * log2(dh);
+            const double t1 = dh1 * log2(dh1);
+            lgtab[h] = t0;
+            inc[h] = grid_round(t1, K) - grid_round(t0, K);
+        }
     }
     __shared__ int64_t sk[MGS_MAX_RATIOS];
     __shared__ int32_t sg[MGS_MAX_RATIOS + 1];
-    for (int s = 0; s < count; ++s) {
-        SceneDesc* sc = &scenes[s];
-        if ((int64_t)blockIdx.x * blockDim.x < sc->gpc) {  // (block-uniform) this block orders groups
-            __syncthreads();  // the previous scene's searches are done with sk, sg
-            for (int u = threadIdx.x; u <= sc->T; u += blockDim.x) {
-                if (u < sc->T) sk[u] = sc->k[u];
-                sg[u] = sc->gcum[u];
-            }
-            __syncthreads();
-            for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < sc->gpc; r += gridDim.x * blockDim.x)
-                tile_order(sc, sk, sg, r);
+    if ((int64_t)blockIdx.x * blockDim.x < sc->gpc) {  // (block-uniform) this block orders groups
+        for (int u = threadIdx.x; u <= sc->T; u += blockDim.x) {
+            if (u < sc->T) sk[u] = sc->k[u];
+            sg[u] = sc->gcum[u];
         }
-        const int64_t nslot = (int64_t)sc->T * sc->C * sc->gmaxn;
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nslot;
-             i += (int64_t)gridDim.x * blockDim.x) {
-            int t = (int)(i / ((int64_t)sc->C * sc->gmaxn));
-            int g = (int)(i % sc->gmaxn);
-            int ng = sc->gcum[t + 1] - sc->gcum[t];
-            if (g >= ng) {
-                for (int b = 0; b < sc->nb; ++b) {
-                    sc->err[i * sc->nb + b] = NAN;
-                    sc->bits[i * sc->nb + b] = NAN;
-                }
-                sc->gmin[i] = NAN;
-                sc->gmax[i] = NAN;
+        __syncthreads();
+        for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < sc->gpc; r += gridDim.x * blockDim.x)
+            tile_order(sc, sk, sg, r);
+    }
+    const int64_t nslot = (int64_t)sc->T * sc->C * sc->gmaxn;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nslot;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        int t = (int)(i / ((int64_t)sc->C * sc->gmaxn));
+        int g = (int)(i % sc->gmaxn);
+        int ng = sc->gcum[t + 1] - sc->gcum[t];
+        if (g >= ng) {
+            for (int b = 0; b < sc->nb; ++b) {
+                sc->err[i * sc->nb + b] = NAN;
+                sc->bits[i * sc->nb + b] = NAN;
             }
-            if (sc->hist)
-                for (int64_t b = 0; b < sc->hist_bins; ++b) sc->hist[i * sc->hist_bins + b] = 0u;
+            sc->gmin[i] = NAN;
+            sc->gmax[i] = NAN;
         }
+        if (sc->hist)
+            for (int64_t b = 0; b < sc->hist_bins; ++b) sc->hist[i * sc->hist_bins + b] = 0u;
     }
 }
 
@@ -1475,16 +1476,13 @@ int launch_sweep(const SweepParams& p, const Shape& sh, size_t lds,
 
 int launch_init(const SceneDesc* host_scenes, int count, SceneDesc* d_scenes,
                 mgs_status_block* status, double* lgtab, int lgtab_max, hipStream_t s) {
-    int64_t slots = 0;
     for (int i = 0; i < count; ++i) {
-        hipLaunchKernelGGL(scene_copy_kernel, dim3(1), dim3(64), 0, s, host_scenes[i], d_scenes + i);
-        slots = std::max(slots, (int64_t)host_scenes[i].T * host_scenes[i].C * host_scenes[i].gmaxn);
+        const int64_t slots = (int64_t)host_scenes[i].T * host_scenes[i].C * host_scenes[i].gmaxn;
+        int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((slots + 255) / 256, 2048));
+        if (i == 0) blocks = std::max<int64_t>(blocks, std::min<int64_t>((lgtab_max + 256) / 256, 2048));
+        hipLaunchKernelGGL(sweep_init_kernel, dim3((unsigned)blocks), dim3(256), 0, s, host_scenes[i], d_scenes + i,
+                           i == 0, status, lgtab, lgtab_max, increment_grid_bits(lgtab_max));
     }
-    int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((slots + 255) / 256, 2048));
-    blocks = std::max<int64_t>(blocks, (lgtab_max + 256) / 256);
-    blocks = std::min<int64_t>(blocks, 2048);
-    hipLaunchKernelGGL(sweep_init_kernel, dim3((unsigned)blocks), dim3(256), 0, s, d_scenes, count,
-                       status, lgtab, lgtab_max, increment_grid_bits(lgtab_max));
     return mgs_last_launch();
 }
 
