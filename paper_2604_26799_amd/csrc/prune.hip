@@ -19,9 +19,9 @@
 // for 64 keys), a scan per k turns the counts into positions, and the wavefront
 // writes its kept indices behind its own running position, without LDS or
 // barriers.  Ties across a threshold are counted beside the smaller keys, and
-// the scan gives them out in index order.  At 5.3e6 keys and 32 counts: 161 us,
+// the scan gives them out in index order.  At 5.3e6 keys and 32 counts: 156 us,
 // of which 75 us write the 356 MB of indices (4.7 TB/s) and the three passes
-// take 12, 25 and 16 us, bound by the latency of picking the digits; with
+// take 11, 21 and 14 us, bound by the latency of picking the digits; with
 // three more digits for the index, a select launch per digit and an LDS scan per
 // (chunk, count) in the write it was 356 us.
 //
@@ -234,13 +234,20 @@ __global__ __launch_bounds__(PR_THREADS) void prune_hist_kernel(PruneArgs a) {
         // finds its count's sum among the 1024 and then its bin among the 32
         constexpr int PER = PR_BINS0 / PR_THREADS;
         static_assert(PER == 32 && PR_THREADS == 1024, "two lookups by ballots");
-        const uint4* h4 = (const uint4*)(a.hist0 + tid * PER);
-        uint32_t mine = 0;
+        // (loads of consecutive pieces by consecutive lanes; eight lanes hold 32 bins)
+        const uint4* h4 = (const uint4*)a.hist0;
+        uint4 q[PER / 4];
+#pragma unroll
+        for (int j = 0; j < PER / 4; ++j) q[j] = h4[j * PR_THREADS + tid];
 #pragma unroll
         for (int j = 0; j < PER / 4; ++j) {
-            const uint4 q = h4[j];
-            mine += (q.x + q.y) + (q.z + q.w);
+            uint32_t sum = (q[j].x + q[j].y) + (q[j].z + q[j].w);
+#pragma unroll
+            for (int o = 1; o < PER / 4; o <<= 1) sum += (uint32_t)__shfl_xor((int)sum, o, MGS_WAVE);
+            if (tid % (PER / 4) == 0) s.sums[(j * PR_THREADS + tid) / (PER / 4)] = sum;
         }
+        __syncthreads();
+        const uint32_t mine = s.sums[tid];  // (each thread replaces its own)
         s.sums[tid] = block_exclusive(mine, s.part, lane, wave, nullptr) + mine;  // inclusive
         __syncthreads();
         for (int t = wave; t < a.T; t += PR_WAVES) {
@@ -280,19 +287,19 @@ __global__ __launch_bounds__(PR_THREADS) void prune_hist_kernel(PruneArgs a) {
     // ---- the first count with each prefix owns its histogram; owners with the
     // same first digit form a list (one wavefront, lane u: count u)
     if (wave == 0) {
+        // (every lane compares its own with all of them, read from LDS: a chain
+        // from count to count, a lane at a time, took 4 us)
         const uint32_t pre = my_k ? s.pre[lane] : 0u;
-        uint64_t owners = 0, same = 0;  // same: owners with this lane's first digit
+        const uint64_t any = __builtin_amdgcn_ballot_w64(my_k != 0u);
+        uint64_t equal = 0, digit = 0;  // the counts with this lane's prefix, first digit
+#pragma unroll 8
         for (int t = 0; t < a.T; ++t) {
-            const uint32_t pt = (uint32_t)__builtin_amdgcn_readlane((int)pre, t);
-            const uint64_t m = __builtin_amdgcn_ballot_w64(my_k && pre == pt);
-            if (m && __builtin_ctzll(m) == t) owners |= 1ull << t;
+            const uint32_t pt = s.pre[t];
+            equal |= (uint64_t)(pt == pre) << t;
+            digit |= (uint64_t)((pt >> PR_REST) == (pre >> PR_REST)) << t;
         }
-        const bool owner = (owners >> lane) & 1ull;
-        for (int t = 0; t < a.T; ++t) {
-            const uint32_t dt = (uint32_t)__builtin_amdgcn_readlane((int)pre, t) >> PR_REST;
-            const uint64_t m = __builtin_amdgcn_ballot_w64(owner && (pre >> PR_REST) == dt);
-            if (lane == t) same = m;
-        }
+        const bool owner = my_k && __builtin_ctzll(equal & any) == lane;
+        const uint64_t same = digit & __builtin_amdgcn_ballot_w64(owner);  // owners with this lane's first digit
         if (owner) {
             const uint64_t later = lane < 63 ? same >> (lane + 1) : 0ull;
             s.next[lane] = later ? (int8_t)(lane + 1 + __builtin_ctzll(later)) : (int8_t)-1;
