@@ -38,7 +38,7 @@
 // the root of 8 million leaves.  The inverse builds the lists bottom-up without
 // values and undoes the merges level by level from the root.
 //
-// What bounds it, at 5.3e6 x 20 on an MI355X: the leaf level (0.38 ms of 0.50)
+// What bounds it, at 5.3e6 x 20 on an MI355X: the leaf level (0.38 ms of 0.49)
 // reads and writes every attribute once (0.93 GB by the counters, 0.19 ms at
 // the rate of a copy) and adds the structure's and the steps' instructions: its
 // vector units are busy 0.7 of the time, its LDS half of it.  A round of 64
@@ -50,7 +50,7 @@
 // levels, which are chains of about 20 steps each (0.12 ms).  Run as one launch
 // per step over node values in HBM (42 dependent launches, rows of both nodes
 // fetched from all over the array) the forward took 1.95 ms at 5.3e6 x 20 and the
-// inverse 0.58 ms at 1e6 x 20, which is 0.18 ms now.
+// inverse 0.58 ms at 1e6 x 20, which is 0.17 ms now.
 #include <algorithm>
 #include <cstring>
 
@@ -72,6 +72,7 @@ constexpr int RH_VS = RH_TILE + 1;                   // row stride of the values
 constexpr int RH_GROUP = 16;                         // lists that an upper level joins
 constexpr int RH_UPPER_MIN = 256;                     // threads of a group's block at least
 constexpr int RH_UPPER_MAX = 512;                     // and at most
+constexpr int RH_UPPER_WAVES = RH_UPPER_MAX / MGS_WAVE;
 constexpr int RH_CAP1 = 256;                          // nodes of a group in LDS at the first upper level,
 constexpr int RH_CAP2 = 768;                          // and above it (few groups, lists of more nodes)
 constexpr int RH_LEVELS = 5;                         // leaf level and up to four above it
@@ -80,6 +81,7 @@ constexpr int RH_LEVELS = 5;                         // leaf level and up to fou
 struct RahtLevel {
     int32_t* cnt;     // [lists] nodes in the list
     int32_t* first;   // [lists][stride] first leaf of each node (a node reaches to the next one's first leaf)
+    uint64_t* code;   // [lists][stride] its code
     int32_t* ac;      // [lists][stride] AC index of the merge across the boundary after the node
     double* rows;     // [lists][stride][C] values
     int32_t lists;
@@ -97,6 +99,7 @@ struct RahtArgs {
     float* attr_out;       // inverse output [C][ld]
     int32_t* cnt;          // [RH_STEPS][nblk] boundaries per (step, block), then their exclusive prefix in the step
     int32_t* tot;          // [RH_STEPS] boundaries per step
+    uint32_t* bad;         // [nblk] codes of the block out of order or range
     // scratch of a group whose lists hold more than RH_TILE nodes, per node of the level below
     uint64_t* big_code;
     int32_t* big_i;        // [6][big_stride]
@@ -168,10 +171,10 @@ __device__ __forceinline__ int wave_exclusive(int v, int lane) {
 }
 
 // Boundaries of each step per block of RH_SPAN leaves (boundary i belongs to
-// the block of leaf i); raises the status flag for codes that do not increase
-// or do not lie below 2^(3 depth).
+// the block of leaf i), and whether codes do not increase or do not lie below
+// 2^(3 depth) (the scan raises the status flag, which needs no clearing then).
 __global__ __launch_bounds__(RH_THREADS) void raht_count_kernel(RahtArgs a) {
-    __shared__ uint32_t h[RH_WAVES][RH_STEPS];
+    __shared__ uint32_t h[RH_WAVES][RH_STEPS], flag[RH_WAVES];
     const int lane = threadIdx.x & (MGS_WAVE - 1), wave = threadIdx.x / MGS_WAVE;
     h[wave][lane] = 0u;
     wave_order();
@@ -192,8 +195,14 @@ __global__ __launch_bounds__(RH_THREADS) void raht_count_kernel(RahtArgs a) {
         bad |= (i < a.N && (c0[e] >> bits) != 0) || (valid && c1[e] <= c0[e]);
         bin_rank(valid, merge_step(c0[e], c1[e], bits), h[wave], lane);
     }
-    if (__builtin_amdgcn_ballot_w64(bad) && lane == 0) atomicOr(&a.status->nonfinite, 4u);
+    const bool any = __builtin_amdgcn_ballot_w64(bad) != 0ull;
+    if (lane == 0) flag[wave] = any;
     __syncthreads();
+    if (threadIdx.x == RH_STEPS) {
+        uint32_t f = 0;
+        for (int w = 0; w < RH_WAVES; ++w) f |= flag[w];
+        a.bad[blockIdx.x] = f;
+    }
     if (threadIdx.x < RH_STEPS) {
         uint32_t n = 0;
         for (int w = 0; w < RH_WAVES; ++w) n += h[w][threadIdx.x];
@@ -202,7 +211,8 @@ __global__ __launch_bounds__(RH_THREADS) void raht_count_kernel(RahtArgs a) {
 }
 
 // One block per step: exclusive prefix of its counts over the blocks, in place,
-// and its total (the leaf level adds the totals of the earlier steps).
+// and its total (the leaf level adds the totals of the earlier steps).  The first
+// one sets the status word.
 constexpr int RH_SCAN_THREADS = 1024;
 __global__ __launch_bounds__(RH_SCAN_THREADS) void raht_scan_kernel(RahtArgs a) {
     constexpr int PER = RH_MAX_BLOCKS / RH_SCAN_THREADS;
@@ -233,6 +243,12 @@ __global__ __launch_bounds__(RH_SCAN_THREADS) void raht_scan_kernel(RahtArgs a) 
             run += v[e];
         }
     if (threadIdx.x == 0) a.tot[blockIdx.x] = total;
+    if (blockIdx.x == 0) {
+        int any = 0;
+        for (int j = threadIdx.x; j < a.nblk; j += RH_SCAN_THREADS) any |= (int)a.bad[j];
+        any = __syncthreads_or(any);
+        if (threadIdx.x == 0) a.status->nonfinite = any ? 4u : 0u;
+    }
 }
 
 // What a merge needs: the roots of both weights, and 1 / sqrt(w1 + w2) as the
@@ -507,7 +523,10 @@ void raht_leaf_kernel(RahtArgs a) {
             if (starts) leaf_of[at] = (uint8_t)j;
             if (MODE != RH_INVERSE && tile < a.lev[0].lists) {
                 const int64_t o = tile * a.stride;
-                if (starts && at < a.stride) a.lev[0].first[o + at] = (int32_t)(s + j);
+                if (starts && at < a.stride) {
+                    a.lev[0].first[o + at] = (int32_t)(s + j);
+                    a.lev[0].code[o + at] = c[e];
+                }
                 // the node that ends at this boundary
                 const int upto = at + (int)starts - 1;
                 if (j < n && !((merged[e] >> lane) & 1ull) && upto >= 0 && upto < a.stride)
@@ -654,15 +673,16 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
     const int64_t list0 = g * RH_GROUP;
     int64_t span = RH_TILE;  // leaves of a group of this level
     for (int l = 0; l < level; ++l) span *= RH_GROUP;
-    const int64_t end = min(a.N, (g + 1) * span);
-    const uint64_t after = a.codes[min(end, a.N - 1)];
+    const int64_t start = g * span, end = min(a.N, (g + 1) * span);
+    const uint64_t before = a.codes[max(start - 1, (int64_t)0)], after = a.codes[min(end, a.N - 1)];
     {
         int pre[RH_GROUP];
 #pragma unroll
         for (int t = 0; t < RH_GROUP; ++t) pre[t] = __builtin_amdgcn_readlane(my_pre, t);
-        if (tid < RH_STEPS) h[tid] = 0u;
+        h[wave * RH_STEPS + lane] = 0u;
         for (int j0 = tid; j0 < n; j0 += U * T) {
             int at[U], fi[U], ai[U];
+            uint64_t co[U];
 #pragma unroll
             for (int e = 0; e < U; ++e) {
                 const int j = min(j0 + e * T, n - 1);
@@ -676,6 +696,7 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
                 at[e] = (int)((list0 + t) * a.stride) + j - p;
                 fi[e] = in.first[at[e]];
                 ai[e] = in.ac[at[e]];
+                co[e] = in.code[at[e]];
             }
 #pragma unroll
             for (int e = 0; e < U; ++e)
@@ -683,12 +704,13 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
                     u.first[j0 + e * T] = fi[e];
                     u.ac[j0 + e * T] = ai[e];
                     u.row[j0 + e * T] = at[e];
+                    u.code[j0 + e * T] = co[e];
                 }
         }
         if (tid == 0) u.first[n] = (int32_t)end;
     }
     __syncthreads();
-    // ---- codes, and the wavefront's first channels beside them
+    // ---- the wavefront's first channels (in flight during the search)
     const int nchunk = BIG ? 1 : (a.C + RH_UCH - 1) / RH_UCH;
     const int k_first = blockIdx.y * vwaves + wave, k_step = (int)gridDim.y * vwaves;
     double* vw = v + (size_t)wave * (RH_UCH * CAP);  // [node][channel]
@@ -725,18 +747,7 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
             }
         }
     };
-    const int64_t start = u.first[0];
-    const uint64_t before = a.codes[max(start - 1, (int64_t)0)];
-    for (int j0 = tid; j0 < n; j0 += U * T) {
-        uint64_t co[U];
-#pragma unroll
-        for (int e = 0; e < U; ++e) co[e] = a.codes[u.first[min(j0 + e * T, n - 1)]];
-#pragma unroll
-        for (int e = 0; e < U; ++e)
-            if (j0 + e * T < n) u.code[j0 + e * T] = co[e];
-    }
     if (MODE != RH_STRUCTURE && !BIG && wave < vwaves && k_first < nchunk) fetch(k_first);
-    __syncthreads();
     // ---- each boundary's run, and whether it lies inside the group
     int top = 1;
     while (2 * top < n) top *= 2;
@@ -776,31 +787,62 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
     }
     __syncthreads();
     // ---- ranks of the merges in their steps, and the nodes that are left: a
-    // node starts at 0 and after every boundary that does not merge here
-    if (wave == 0) {
-        const int64_t o = g * a.stride;
+    // node starts at 0 and after every boundary that does not merge here.  Each
+    // wavefront counts a piece of the boundaries by itself, then adds what the
+    // wavefronts before it counted.
+    {
+        const int nw = T / MGS_WAVE;
+        const int piece = ((n + MGS_WAVE - 1) / MGS_WAVE + nw - 1) / nw * MGS_WAVE;
+        const int p0 = wave * piece, p1 = min(n, p0 + piece);
+        uint32_t* hw = h + wave * RH_STEPS;
+        uint32_t* ended = h + RH_UPPER_WAVES * RH_STEPS;
         int live = 0;
-        if (MODE != RH_INVERSE && lane == 0) out.first[o] = (int32_t)start;
-        for (int j0 = 0; j0 < n; j0 += MGS_WAVE) {
+        for (int j0 = p0; j0 < p1; j0 += MGS_WAVE) {
             const int j = j0 + lane;
-            const int d = j < n ? u.rank[j] : -1;
-            const uint64_t ends = __builtin_amdgcn_ballot_w64(j < n && d < 0);
-            const int r = bin_rank(d >= 0, max(d, 0), h, lane);
+            const int d = j < p1 ? u.rank[j] : -1;
+            const uint64_t ends = __builtin_amdgcn_ballot_w64(j < p1 && d < 0);
+            const int r = bin_rank(d >= 0, max(d, 0), hw, lane);
             const int slot = live + __popcll(ends & lanes_below(lane));  // of the node that ends at boundary j
-            if (j < n) {
-                u.rank[j] = d >= 0 ? (d << 16) | r : -2 - slot;
-                if (MODE != RH_INVERSE && d < 0) {
-                    if (slot < a.stride) out.ac[o + slot] = u.ac[j];
-                    if (slot + 1 < a.stride && j + 1 < n) out.first[o + slot + 1] = u.first[j + 1];
-                }
-            }
+            if (j < p1) u.rank[j] = d >= 0 ? (d << 16) | r : -2 - slot;
             live += __popcll(ends);
         }
-        if (MODE != RH_INVERSE && lane == 0) out.cnt[g] = min(live, a.stride);
+        if (lane == 0) ended[wave] = (uint32_t)live;
+        __syncthreads();
+        int before_bin = 0, before_ends = 0, all_ends = 0;  // lane b: merges of step b before the piece
+        for (int w = 0; w < nw; ++w) {
+            if (w < wave) {
+                before_bin += (int)h[w * RH_STEPS + lane];
+                before_ends += (int)ended[w];
+            }
+            all_ends += (int)ended[w];
+        }
+        const int64_t o = g * a.stride;
+        for (int j0 = p0; j0 < p1; j0 += MGS_WAVE) {
+            const int j = j0 + lane;
+            const int r = j < p1 ? u.rank[j] : -1;
+            const int more = __shfl(before_bin, max(r, 0) >> 16);
+            if (j < p1) {
+                u.rank[j] = r >= 0 ? r + more : r - before_ends;
+                const int slot = -2 - r + before_ends;
+                if (MODE != RH_INVERSE && r < 0) {
+                    if (slot < a.stride) out.ac[o + slot] = u.ac[j];
+                    if (slot + 1 < a.stride && j + 1 < n) {
+                        out.first[o + slot + 1] = u.first[j + 1];
+                        out.code[o + slot + 1] = u.code[j + 1];
+                    }
+                }
+            }
+        }
+        if (MODE != RH_INVERSE && tid == 0) {
+            out.first[o] = (int32_t)start;
+            out.code[o] = u.code[0];
+            out.cnt[g] = min(all_ends, a.stride);
+        }
     }
     if (MODE == RH_STRUCTURE) return;
     __syncthreads();
-    const int msize = (int)h[lane];  // lane b: merges of step b
+    int msize = 0;
+    for (int w = 0; w < T / MGS_WAVE; ++w) msize += (int)h[w * RH_STEPS + lane];  // lane b: merges of step b
     const int mstart = wave_exclusive(msize, lane);
     const uint64_t steps = __builtin_amdgcn_ballot_w64(msize > 0);
     const int nm = __builtin_amdgcn_readlane(mstart + msize, MGS_WAVE - 1);
@@ -967,12 +1009,12 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
 
 // Upper levels: one block per group of RH_GROUP lists and `vwaves` chunks of
 // RH_UCH channels (blockIdx.y takes the others and builds the structure again).
-// What bounds a block is its chain: three dependent loads (2.5 + 2 us), the
-// search (2.5), the ranks (2), then the steps (5), one LDS round trip and four
-// dependent FP64 operations each.  With the weights (three dependent LDS reads,
-// three square roots, two divisions) inside the steps, one wavefront per group
-// and chunk, a level took 24 to 31 us and the first of 5.3e6 x 20, whose 1294
-// groups fill the chip several times, 89; now 18 to 24 and 71.
+// What bounds a block is its chain: two dependent loads (2 + 2 us), the search
+// (2), the ranks (1), the weights (1), then the steps (5), one LDS round trip and
+// four dependent FP64 operations each.  With the weights (three dependent LDS
+// reads, three square roots, two divisions) inside the steps, one wavefront per
+// group and chunk, a level took 24 to 31 us and the first of 5.3e6 x 20, whose
+// 1294 groups fill the chip several times, 89; now 18 to 23 and 66.
 template <int MODE, int CAP>
 __global__ __launch_bounds__(RH_UPPER_MAX) void raht_upper_kernel(RahtArgs a, int level, int vwaves) {
     static_assert(CAP % RH_UPPER_MIN == 0 && CAP % RH_TILE == 0, "nodes per thread, rounds of loads");
@@ -994,7 +1036,7 @@ __global__ __launch_bounds__(RH_UPPER_MAX) void raht_upper_kernel(RahtArgs a, in
     uint64_t* code = (uint64_t*)wt;
     int32_t* tmp = (int32_t*)(code + CAP);
     uint32_t* h = (uint32_t*)(tmp + 3 * CAP + 1);
-    static_assert(2 * CAP + 3 * CAP + 1 + RH_STEPS <= 9 * CAP, "what is replaced fits");
+    static_assert(2 * CAP + 3 * CAP + 1 + RH_UPPER_WAVES * (RH_STEPS + 1) <= 9 * CAP, "what is replaced fits");
     if (n <= CAP) {
         const UpperArrays u{code, tmp + 2 * CAP, keep, keep + CAP, tmp, tmp + CAP, nullptr, keep + 2 * CAP};
         raht_group<MODE, false, CAP>(a, level, g, n, u, my_pre, h, wt, pk, v, vwaves);
@@ -1008,8 +1050,8 @@ __global__ __launch_bounds__(RH_UPPER_MAX) void raht_upper_kernel(RahtArgs a, in
 }
 
 struct RahtLayout {
-    size_t cnt, tot, big_code, big_i, total;
-    size_t lcnt[RH_LEVELS], first[RH_LEVELS], ac[RH_LEVELS], rows[RH_LEVELS];
+    size_t cnt, tot, bad, big_code, big_i, total;
+    size_t lcnt[RH_LEVELS], first[RH_LEVELS], code[RH_LEVELS], ac[RH_LEVELS], rows[RH_LEVELS];
     int64_t lists[RH_LEVELS], big_stride;
     int64_t nblk;
     int stride, top;
@@ -1030,6 +1072,7 @@ RahtLayout raht_layout(int64_t N, int32_t C, int32_t depth) {
     };
     L.cnt = take(sizeof(int32_t) * RH_STEPS * (size_t)L.nblk);
     L.tot = take(sizeof(int32_t) * RH_STEPS);
+    L.bad = take(sizeof(uint32_t) * (size_t)L.nblk);
     int64_t lists = std::max<int64_t>(1, (N + RH_TILE - 1) / RH_TILE);
     L.big_stride = lists * L.stride + (lists + RH_GROUP - 1) / RH_GROUP + 1;
     for (int l = 0; l < RH_LEVELS; ++l) {
@@ -1038,6 +1081,7 @@ RahtLayout raht_layout(int64_t N, int32_t C, int32_t depth) {
         L.lcnt[l] = take(sizeof(int32_t) * (size_t)lists);
         L.first[l] = take(sizeof(int32_t) * (size_t)lists * L.stride);
         L.ac[l] = take(sizeof(int32_t) * (size_t)lists * L.stride);
+        L.code[l] = take(sizeof(uint64_t) * (size_t)lists * L.stride);
         if (lists == 1) break;  // the root: its value is the DC coefficient
         L.rows[l] = take(sizeof(double) * (size_t)lists * L.stride * (size_t)C);
         lists = (lists + RH_GROUP - 1) / RH_GROUP;
@@ -1064,6 +1108,7 @@ int raht_setup(RahtArgs& a, RahtLayout& L, const uint64_t* codes, int64_t N, int
     a.ld = ld;
     a.cnt = (int32_t*)(ws + L.cnt);
     a.tot = (int32_t*)(ws + L.tot);
+    a.bad = (uint32_t*)(ws + L.bad);
     a.big_code = (uint64_t*)(ws + L.big_code);
     a.big_i = (int32_t*)(ws + L.big_i);
     a.big_stride = L.big_stride;
@@ -1075,16 +1120,15 @@ int raht_setup(RahtArgs& a, RahtLayout& L, const uint64_t* codes, int64_t N, int
         a.lev[l].cnt = (int32_t*)(ws + L.lcnt[l]);
         a.lev[l].first = (int32_t*)(ws + L.first[l]);
         a.lev[l].ac = (int32_t*)(ws + L.ac[l]);
+        a.lev[l].code = (uint64_t*)(ws + L.code[l]);
         a.lev[l].rows = (double*)(ws + L.rows[l]);
         a.lev[l].lists = (int32_t)L.lists[l];
     }
     return MGS_OK;
 }
 
-// Status reset and the AC indices' counts.
+// The status word and the AC indices' counts.
 int raht_counts(RahtArgs& a, hipStream_t s) {
-    int rc = mgs_fill<uint32_t>((uint32_t*)a.status, 64, 0u, s);
-    if (rc) return rc;
     hipLaunchKernelGGL(raht_count_kernel, dim3(a.nblk), dim3(RH_THREADS), 0, s, a);
     hipLaunchKernelGGL(raht_scan_kernel, dim3(RH_STEPS), dim3(RH_SCAN_THREADS), 0, s, a);
     return mgs_last_launch();
