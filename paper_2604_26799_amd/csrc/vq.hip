@@ -36,7 +36,7 @@
 //      scored at least that previous minimum, so above the final threshold
 //      (the row minimum only falls), and cannot hold the winner.  Thresholds
 //      only fall, so each mask holds every codeword under the final
-//      threshold.  The row's candidates are then re-scored, two at a time,
+//      threshold.  The row's candidates are then re-scored, one per lane at a time,
 //      with the FP64 definition (same operation order) and the smallest
 //      (distance, index) wins.  Rows with more candidate tiles than slots go
 //      to an exact FP64 full scan.  Padding codewords (up to whole chunks)
@@ -69,6 +69,7 @@ constexpr int VQ_CHUNK = 64;                           // codewords per chunk of
 // form: 65,000 rows x 36 against 4096 70 / 89 us, 100,000 114 / 105; 65,000 x 45
 // against 1024 49 / 59; 32,000 x 64 against 512 44 / 61, 65,000 64 / 60.
 constexpr int64_t vq_few_rows(int KS) { return KS <= 4 ? 65536 : 32768; }
+constexpr int VQ_EXACT_BATCH = 3;                       // float4 groups of an exact distance loaded together
 constexpr int VQ_CAND = 8;                             // candidate tiles per lane and row set
 
 struct VqArgs {
@@ -196,75 +197,61 @@ __device__ __forceinline__ double exact_dist(const float* __restrict__ x, const 
     return s;
 }
 
-// The distances of one row to two codewords, each the same terms added in
-// the same order as above, from float4 loads: the row and both codewords are
-// read in batches of four float4 groups, a batch's loads all issued before its
-// first use (a group past D is read from the row's last group and ignored),
-// and the two sums are independent chains.  Needs D % 4 == 0 and 16-byte
+// The same from float4 loads in batches of VQ_EXACT_BATCH groups of row and
+// codeword, a batch's loads all issued before its first use (a group past D is
+// read from the row's last group and ignored).  Needs D % 4 == 0 and 16-byte
 // aligned rows.
 template <int NG>
-__device__ __forceinline__ void exact_dist_vec2(const float* __restrict__ x, const float* __restrict__ c0,
-                                                const float* __restrict__ c1, int D, double* d0, double* d1) {
-    double s0 = 0.0, s1 = 0.0;
+__device__ __forceinline__ double exact_dist_vec(const float* __restrict__ x, const float* __restrict__ c, int D) {
+    double s = 0.0;
 #pragma unroll
-    for (int g0 = 0; g0 < NG; g0 += 4) {
+    for (int g0 = 0; g0 < NG; g0 += VQ_EXACT_BATCH) {
         if (4 * g0 >= D) break;
-        float4 xv[4], av[4], bv[4];
+        float4 xv[VQ_EXACT_BATCH], cv[VQ_EXACT_BATCH];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < VQ_EXACT_BATCH; ++i) {
             const int k0 = 4 * (g0 + i) < D ? 4 * (g0 + i) : D - 4;
             xv[i] = *(const float4*)(x + k0);
-            av[i] = *(const float4*)(c0 + k0);
-            bv[i] = *(const float4*)(c1 + k0);
+            cv[i] = *(const float4*)(c + k0);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < VQ_EXACT_BATCH; ++i) {
             const float xe[4] = {xv[i].x, xv[i].y, xv[i].z, xv[i].w};
-            const float ae[4] = {av[i].x, av[i].y, av[i].z, av[i].w};
-            const float be[4] = {bv[i].x, bv[i].y, bv[i].z, bv[i].w};
+            const float ce[4] = {cv[i].x, cv[i].y, cv[i].z, cv[i].w};
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (4 * (g0 + i) + e < D) {
-                    const double xd = (double)xe[e];
-                    const double da = xd - (double)ae[e];
-                    const double db = xd - (double)be[e];
-                    s0 += da * da;
-                    s1 += db * db;
+                    const double d = (double)xe[e] - (double)ce[e];
+                    s += d * d;
                 }
         }
     }
-    *d0 = s0;
-    *d1 = s1;
+    return s;
 }
 
 // The same for any D and 4-byte alignment, from single loads in batches of 16
 // (values past D repeat the last one and are ignored).  With one load after the
 // other this was a chain of D round trips per candidate: 14 of the 61 us of the
 // main kernel at 10,007 x 45 against 1000.
-__device__ __forceinline__ void exact_dist2(const float* __restrict__ x, const float* __restrict__ c0,
-                                            const float* __restrict__ c1, int D, double* d0, double* d1) {
+__device__ __forceinline__ double exact_dist_batch(const float* __restrict__ x, const float* __restrict__ c, int D) {
     constexpr int NB = 16;
-    double s0 = 0.0, s1 = 0.0;
+    double s = 0.0;
     for (int k0 = 0; k0 < D; k0 += NB) {
-        float xv[NB], av[NB], bv[NB];
+        float xv[NB], cv[NB];
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             const int k = min(k0 + i, D - 1);
             xv[i] = x[k];
-            av[i] = c0[k];
-            bv[i] = c1[k];
+            cv[i] = c[k];
         }
 #pragma unroll
         for (int i = 0; i < NB; ++i)
             if (k0 + i < D) {
-                const double da = (double)xv[i] - (double)av[i];
-                const double db = (double)xv[i] - (double)bv[i];
-                s0 += da * da;
-                s1 += db * db;
+                const double d = (double)xv[i] - (double)cv[i];
+                s += d * d;
             }
     }
-    *d0 = s0;
-    *d1 = s1;
+    return s;
 }
 
 // VEC: D % 4 == 0 and x 16-byte aligned (rows load as float4).  VQ_ROWSETS: 32-row
@@ -532,12 +519,13 @@ void vq_main_kernel(VqArgs a) {
         const int ovf_row = ovf | __shfl_xor(ovf, 32, MGS_WAVE);
         double best = INFINITY;
         int32_t bj = 0x7fffffff;
-        if (r < a.N && !ovf_row) {
-            const float* xr = a.x + r * D;
+        {
+            const float* xr = a.x + (r < a.N ? r : 0) * D;
             const bool vec = VEC && a.cvec;  // float4 rows and codewords
+            const int n = r < a.N && !ovf_row ? cnt[rs] : 0;
             int e = 0;
-            int jbase = cnt[rs] > 0 ? cand_t[wave][rs][0][lane] : 0;
-            uint32_t bits = cnt[rs] > 0 ? cand_m[wave][rs][0][lane] : 0u;
+            int jbase = n > 0 ? cand_t[wave][rs][0][lane] : 0;
+            uint32_t bits = n > 0 ? cand_m[wave][rs][0][lane] : 0u;
             // the lane's next candidate codeword; false once none is left
             auto next = [&](int32_t& j) {
                 for (;;) {
@@ -548,36 +536,33 @@ void vq_main_kernel(VqArgs a) {
                         j = jbase + 8 * (i >> 2) + 4 * half + (i & 3);
                         if (j < K) return true;
                     }
-                    if (++e >= cnt[rs]) return false;
+                    if (++e >= n) return false;
                     jbase = cand_t[wave][rs][e][lane];
                     bits = cand_m[wave][rs][e][lane];
                 }
             };
-            auto take = [&](int32_t j, double d) {
-                if (d < best || (d == best && j < bj)) {
-                    best = d;
-                    bj = j;
+            // one candidate per lane and turn: a row has 1.1 of them on average,
+            // in one of its lanes, and a lane that has none left takes one of
+            // its row's other lane (two per lane and turn, the second mostly the
+            // first again: 3,000,000 x 36 against 4096 2 % slower)
+            for (;;) {
+                int32_t j = -1, give = -1;
+                bool have = next(j);
+                if (!__shfl_xor((int)have, 32, MGS_WAVE) && have && !next(give)) give = -1;
+                const int32_t got = __shfl_xor(give, 32, MGS_WAVE);
+                if (!have && got >= 0) {
+                    j = got;
+                    have = true;
                 }
-            };
-            // candidates in pairs (an odd last one is scored twice)
-            int32_t j0 = 0, j1 = 0;
-            bool more = next(j0);
-            while (more) {
-                if (!next(j1)) {
-                    j1 = j0;
-                    more = false;
+                if (!__builtin_amdgcn_ballot_w64(have)) break;
+                if (have) {
+                    const float* c = a.cb + (int64_t)j * D;
+                    const double d = vec ? exact_dist_vec<KP / 4>(xr, c, D) : exact_dist_batch(xr, c, D);
+                    if (d < best || (d == best && j < bj)) {
+                        best = d;
+                        bj = j;
+                    }
                 }
-                const float* c0 = a.cb + (int64_t)j0 * D;
-                const float* c1 = a.cb + (int64_t)j1 * D;
-                double d0, d1;
-                if (vec) {
-                    exact_dist_vec2<KP / 4>(xr, c0, c1, D, &d0, &d1);
-                } else {
-                    exact_dist2(xr, c0, c1, D, &d0, &d1);
-                }
-                take(j0, d0);
-                take(j1, d1);
-                if (more) more = next(j0);
             }
         }
         const double ob = __shfl_xor(best, 32, MGS_WAVE);
