@@ -1067,7 +1067,7 @@ __device__ __forceinline__ void tile_order(const SceneDesc* sc, const int64_t* s
 // empty slots (groups past ceil(k_t / G)) hold NaN, its debug histogram is
 // cleared and it gets its tile order.  The first scene's launch also resets the
 // status word and makes the tables.  (A launch that only copied the descriptor
-// cost 5 of the 59 us of a sweep of 20,000 x 11.)
+// cost 5 of the 59 us of a sweep of 50,000 x 11.)
 __global__ void sweep_init_kernel(SceneDesc sd, SceneDesc* __restrict__ dst, int first, mgs_status_block* status,
                                   double* lgtab, int lgtab_max, int K) {
     static_assert(sizeof(SceneDesc) % sizeof(uint32_t) == 0, "copied by words");
