@@ -65,7 +65,8 @@ constexpr int RH_ROUNDS = RH_TILE / MGS_WAVE;
 constexpr int RH_WAVES = 8;
 constexpr int RH_THREADS = RH_WAVES * MGS_WAVE;
 constexpr int RH_SPAN = RH_TILE * RH_WAVES;          // leaves per block of the counts
-constexpr int RH_MAX_BLOCKS = 4096;                  // N <= RH_SPAN * RH_MAX_BLOCKS
+constexpr int RH_MAX_SPANS = 4096;                   // N - 1 <= RH_SPAN * RH_MAX_SPANS
+constexpr int RH_MAX_BLOCKS = RH_MAX_SPANS + 1;       // blocks of RH_SPAN leaves
 constexpr int RH_CH = 4;                             // channels in LDS at a time (77 KB per block: two per CU)
 constexpr int RH_UCH = 4;                            // the same at the upper levels
 constexpr int RH_VS = RH_TILE + 1;                   // row stride of the values (channels in different banks)
@@ -92,9 +93,9 @@ struct RahtArgs {
     int64_t N;
     int32_t C;
     int32_t depth;
-    int64_t ld;
-    const float* attr;     // forward input [C][ld]
-    const float* coef_in;  // inverse input [C][ld]
+    int64_t ld, ld_in;     // of the output and of the input (which may lie in the workspace)
+    const float* attr;     // forward input [C][ld_in]
+    const float* coef_in;  // inverse input [C][ld_in]
     float* coef;           // forward output [C][ld]
     float* attr_out;       // inverse output [C][ld]
     int32_t* cnt;          // [RH_STEPS][nblk] boundaries per (step, block), then their exclusive prefix in the step
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(RH_THREADS) void raht_count_kernel(RahtArgs a) {
 // one sets the status word.
 constexpr int RH_SCAN_THREADS = 1024;
 __global__ __launch_bounds__(RH_SCAN_THREADS) void raht_scan_kernel(RahtArgs a) {
-    constexpr int PER = RH_MAX_BLOCKS / RH_SCAN_THREADS;
+    constexpr int PER = (RH_MAX_BLOCKS + RH_SCAN_THREADS - 1) / RH_SCAN_THREADS;
     constexpr int NW = RH_SCAN_THREADS / MGS_WAVE;
     __shared__ int wsum[NW];
     const int lane = threadIdx.x & (MGS_WAVE - 1), wave = threadIdx.x / MGS_WAVE;
@@ -434,7 +435,7 @@ void raht_leaf_kernel(RahtArgs a) {
         for (int cc = 0; cc < RH_CH; ++cc)
 #pragma unroll
             for (int e = 0; e < RH_ROUNDS; ++e)
-                x[cc][e] = a.attr[(int64_t)(k0 + min(cc, nch - 1)) * a.ld + min(s + e * MGS_WAVE + lane, a.N - 1)];
+                x[cc][e] = a.attr[(int64_t)(k0 + min(cc, nch - 1)) * a.ld_in + min(s + e * MGS_WAVE + lane, a.N - 1)];
     };
     if (MODE == RH_FORWARD) load_chunk(0);
     const uint64_t before = a.codes[max(min(s, a.N) - 1, (int64_t)0)];
@@ -577,11 +578,11 @@ void raht_leaf_kernel(RahtArgs a) {
             for (int cc = 0; cc < RH_CH; ++cc) {
                 const int ch = k0 + min(cc, nch - 1);
 #pragma unroll
-                for (int e = 0; e < RH_ROUNDS; ++e) hx[cc][e] = a.coef_in[(int64_t)ch * a.ld + column[e]];
+                for (int e = 0; e < RH_ROUNDS; ++e) hx[cc][e] = a.coef_in[(int64_t)ch * a.ld_in + column[e]];
             }
             auto row = [&](int t) {
                 const int node = min(t + node_of, live - 1), ch = k0 + min(ch_of, nch - 1);
-                return a.top == 0 ? (double)a.coef_in[(int64_t)ch * a.ld]
+                return a.top == 0 ? (double)a.coef_in[(int64_t)ch * a.ld_in]
                                   : a.lev[0].rows[(tile * a.stride + node) * a.C + ch];
             };
             auto put = [&](int t, double r) {
@@ -737,7 +738,7 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
                     const int64_t p = min(1 + (int64_t)u.ac[max(j - 1, 0)], a.N - 1);
 #pragma unroll
                     for (int cc = 0; cc < RH_UCH; ++cc)
-                        r[e][cc] = a.coef_in[(int64_t)(k0 + min(cc, nch - 1)) * a.ld + p];
+                        r[e][cc] = a.coef_in[(int64_t)(k0 + min(cc, nch - 1)) * a.ld_in + p];
                 }
 #pragma unroll
                 for (int e = 0; e < RH_ROUNDS; ++e)
@@ -904,7 +905,7 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
                         if (slot[e] >= a.stride) slot[e] = -1;
                         r[e] = 0.0;
                         if (slot[e] >= 0)
-                            r[e] = root ? (double)a.coef_in[(int64_t)ch * a.ld]
+                            r[e] = root ? (double)a.coef_in[(int64_t)ch * a.ld_in]
                                         : out.rows[(g * a.stride + slot[e]) * a.C + ch];
                     }
 #pragma unroll
@@ -955,12 +956,12 @@ __device__ __forceinline__ void raht_group(const RahtArgs& a, int level, int64_t
                 const int slot = slot_of(j);
                 if (slot < 0 || slot >= a.stride) continue;
                 for (int c = 0; c < a.C; ++c)
-                    value(c, j) = root ? (double)a.coef_in[(int64_t)c * a.ld]
+                    value(c, j) = root ? (double)a.coef_in[(int64_t)c * a.ld_in]
                                        : out.rows[(g * a.stride + slot) * a.C + c];
             }
             for (int q = tid; q < nm; q += T) {
                 const int j = u.order[q];
-                for (int c = 0; c < a.C; ++c) value(c, j + 1) = (double)a.coef_in[(int64_t)c * a.ld + 1 + u.ac[j]];
+                for (int c = 0; c < a.C; ++c) value(c, j + 1) = (double)a.coef_in[(int64_t)c * a.ld_in + 1 + u.ac[j]];
             }
         }
         __syncthreads();
@@ -1050,7 +1051,7 @@ __global__ __launch_bounds__(RH_UPPER_MAX) void raht_upper_kernel(RahtArgs a, in
 }
 
 struct RahtLayout {
-    size_t cnt, tot, bad, big_code, big_i, total;
+    size_t cnt, tot, bad, big_code, big_i, input, total;
     size_t lcnt[RH_LEVELS], first[RH_LEVELS], code[RH_LEVELS], ac[RH_LEVELS], rows[RH_LEVELS];
     int64_t lists[RH_LEVELS], big_stride;
     int64_t nblk;
@@ -1088,6 +1089,7 @@ RahtLayout raht_layout(int64_t N, int32_t C, int32_t depth) {
     }
     L.big_code = take(sizeof(uint64_t) * (size_t)L.big_stride);
     L.big_i = take(sizeof(int32_t) * RH_BIG_ARRAYS * (size_t)L.big_stride);
+    L.input = take(sizeof(float) * (size_t)N * (size_t)C);
     L.total = o;
     return L;
 }
@@ -1097,7 +1099,7 @@ int raht_setup(RahtArgs& a, RahtLayout& L, const uint64_t* codes, int64_t N, int
     if (N < 1 || N >= ((int64_t)1 << 31) || C < 1 || ld < N || depth < 1 || depth > 21 || !codes)
         return MGS_EINVAL;
     L = raht_layout(N, C, depth);
-    if (L.nblk > RH_MAX_BLOCKS) return MGS_EINVAL;
+    if (N - 1 > (int64_t)RH_SPAN * RH_MAX_SPANS) return MGS_EINVAL;
     if (!d_ws || ws_bytes < L.total) return MGS_EWORKSPACE;
     char* ws = (char*)d_ws;
     std::memset(&a, 0, sizeof(a));
@@ -1125,6 +1127,29 @@ int raht_setup(RahtArgs& a, RahtLayout& L, const uint64_t* codes, int64_t N, int
         a.lev[l].lists = (int32_t)L.lists[l];
     }
     return MGS_OK;
+}
+
+// A call in place (input and output overlap) works on a copy of its input: tiles
+// write coefficients to columns that other tiles have yet to read.
+__global__ void raht_copy_kernel(const float* __restrict__ src, int64_t ld, float* __restrict__ dst, int64_t N,
+                                 int64_t total) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t c = i / N;
+        dst[i] = src[c * ld + (i - c * N)];
+    }
+}
+const float* raht_input(RahtArgs& a, const RahtLayout& L, const float* in, const float* out, void* d_ws,
+                        hipStream_t s) {
+    const uintptr_t i0 = (uintptr_t)in, o0 = (uintptr_t)out;
+    const uintptr_t bytes = sizeof(float) * (uintptr_t)((a.C - 1) * a.ld + a.N);
+    a.ld_in = a.ld;
+    if (i0 >= o0 + bytes || o0 >= i0 + bytes) return in;
+    float* copy = (float*)((char*)d_ws + L.input);
+    const int64_t total = a.N * a.C;
+    a.ld_in = a.N;
+    hipLaunchKernelGGL(raht_copy_kernel, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 16384)), dim3(256), 0, s,
+                       in, a.ld, copy, a.N, total);
+    return copy;
 }
 
 // The status word and the AC indices' counts.
@@ -1176,7 +1201,7 @@ extern "C" int mgs_raht_forward(const uint64_t* d_codes, int64_t N, int32_t C, i
     if (rc) return rc;
     if (!d_attr || !d_coef) return MGS_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    a.attr = d_attr;
+    a.attr = raht_input(a, L, d_attr, d_coef, d_ws, s);
     a.coef = d_coef;
     rc = raht_counts(a, s);
     if (rc) return rc;
@@ -1195,7 +1220,7 @@ extern "C" int mgs_raht_inverse(const uint64_t* d_codes, int64_t N, int32_t C, i
     if (rc) return rc;
     if (!d_attr || !d_coef) return MGS_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    a.coef_in = d_coef;
+    a.coef_in = raht_input(a, L, d_coef, d_attr, d_ws, s);
     a.attr_out = d_attr;
     rc = raht_counts(a, s);
     if (rc) return rc;

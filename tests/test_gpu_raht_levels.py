@@ -174,3 +174,42 @@ def test_values_without_a_quotient(torch):
         assert np.array_equal(g, w, equal_nan=True)
         finite = np.isfinite(w)
         assert np.array_equal(np.signbit(g[finite]), np.signbit(w[finite]))
+
+
+def call(torch, name, codes, values, out, ld, depth, C):
+    n = codes.numel()
+    ws = mgs.workspace(mgs.lib().mgs_raht_ws_bytes(n, C, depth))
+    code = getattr(mgs.lib(), name)(codes.data_ptr(), n, C, depth, values, ld, out, ws.data_ptr(), ws.numel(),
+                                    torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return code
+
+
+@pytest.mark.parametrize("n,C,pad", [(300, 1, 0), (70_001, 5, 0), (70_001, 5, 7)])
+def test_in_place(torch, n, C, pad):
+    """Input and output in one buffer, also with a stride and one row further on."""
+    codes, _ = synth.voxel_codes(synth.voxels(n, 11, seed=n), 11)
+    cd, ld = dev(torch, codes.astype(np.int64)), n + pad
+    attr = np.random.default_rng(n).normal(0, 1, (C, ld)).astype(np.float32)
+    want = forward(codes, attr[:, :n], 11)
+    back = inverse(codes, want, 11)
+    buf = dev(torch, np.concatenate([attr, np.zeros((1, ld), np.float32)]))
+    step = 4 * ld if C > 1 else 0
+    assert call(torch, "mgs_raht_forward", cd, buf.data_ptr(), buf.data_ptr() + step, ld, 11, C) == 0
+    got = buf.cpu().numpy()[1 if step else 0:][:C]
+    assert np.array_equal(got[:, :n], want)
+    assert call(torch, "mgs_raht_inverse", cd, buf.data_ptr() + step, buf.data_ptr() + step, ld, 11, C) == 0
+    assert np.array_equal(buf.cpu().numpy()[1 if step else 0:][:C, :n], back)
+
+
+def test_largest(torch):
+    """The largest size that the counts hold, and one more."""
+    n = 2048 * 4096 + 1
+    codes = torch.arange(n + 1, device="cuda")
+    attr = torch.randn((1, n), generator=torch.Generator("cuda").manual_seed(0), device="cuda")
+    got = mgs.raht(codes[:n], attr, 8)
+    want = forward(np.arange(n, dtype=np.uint64), attr.cpu().numpy(), 8)
+    assert np.array_equal(got.cpu().numpy(), want)
+    with pytest.raises(mgs.MgsError) as e:
+        mgs.raht(codes, torch.zeros((1, n + 1), device="cuda"), 8)
+    assert e.value.code == mgs.EINVAL
