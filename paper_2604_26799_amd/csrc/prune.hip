@@ -26,7 +26,7 @@
 // (chunk, count) in the write it was 356 us.
 //
 // Inputs of up to 65,536 take one kernel: one workgroup per k holds all keys in
-// registers, selects the k-th in LDS and writes the kept set (36 us at n =
+// registers, selects the k-th in LDS and writes the kept set (30 us at n =
 // 50,000 and four counts; the launches of the general path take 52 us, and the
 // 17 of the earlier one took 81).
 #include <algorithm>
@@ -502,10 +502,11 @@ __device__ __forceinline__ uint32_t mask_position(uint64_t m, uint32_t base) {
 template <int ROUNDS>
 __device__ __forceinline__ void write_run(const uint32_t (&key)[ROUNDS], uint32_t th, bool tied, uint32_t rem,
                                           uint32_t base, uint32_t eq_taken, uint32_t k, int32_t* out, uint32_t i0,
-                                          int lane) {
+                                          int lane, int used = ROUNDS) {
     if (!tied) {
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
+            if (r >= used) continue;
             const bool keep = key[r] <= th;
             const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
             const uint32_t pos = mask_position(m, base);
@@ -513,7 +514,7 @@ __device__ __forceinline__ void write_run(const uint32_t (&key)[ROUNDS], uint32_
             base += (uint32_t)__popcll(m);
         }
     } else {
-        for (int r = 0; r < ROUNDS; ++r) {
+        for (int r = 0; r < used; ++r) {
             uint32_t kr = key[0];
 #pragma unroll
             for (int x = 1; x < ROUNDS; ++x)
@@ -568,19 +569,22 @@ __global__ __launch_bounds__(PR_THREADS) void prune_small_kernel(PruneArgs a) {
     __shared__ uint32_t part[PR_WAVES], found[3], below[PR_WAVES], equal[PR_WAVES], nlist;
     const int t = blockIdx.x, tid = threadIdx.x;
     const int lane = tid & (MGS_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / MGS_WAVE);
-    const uint32_t i0 = (uint32_t)wave * (MGS_WAVE * ROUNDS);
     const uint32_t n = (uint32_t)a.n;
+    // rounds in use, the same for every wavefront (a round of keys past the end
+    // would be one bin's, 64 additions to one address)
+    const int used = (int)((n + PR_THREADS - 1) / PR_THREADS);
+    const uint32_t i0 = (uint32_t)(wave * used) * MGS_WAVE;
     uint32_t key[ROUNDS];
     {
         float v[ROUNDS], nan = 0.0f;
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) v[r] = a.imp[min(i0 + r * MGS_WAVE + lane, n - 1u)];
+        for (int r = 0; r < ROUNDS; ++r) v[r] = r < used ? a.imp[min(i0 + r * MGS_WAVE + lane, n - 1u)] : 0.0f;
         // (past the end the largest key: it ranks behind every finite one, so
         // no pass has to leave it out)
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
             nan = __builtin_fmaf(v[r], 0.0f, nan);  // NaN once a value is not finite
-            key[r] = i0 + r * MGS_WAVE + lane < n ? desc_key(v[r]) : 0xFFFFFFFFu;
+            key[r] = r < used && i0 + r * MGS_WAVE + lane < n ? desc_key(v[r]) : 0xFFFFFFFFu;
         }
         // every block sees all keys: the first one sets the status word
         const int any = __syncthreads_or(__builtin_isnan(nan));
@@ -593,12 +597,16 @@ __global__ __launch_bounds__(PR_THREADS) void prune_small_kernel(PruneArgs a) {
     auto pick = [&](int fixed, int bits) {
         const int nbins = 1 << bits, per = nbins > PR_THREADS ? nbins / PR_THREADS : 1;
         __syncthreads();
-        uint32_t c[8], mine = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            c[j] = j < per && tid * per + j < nbins ? h[tid * per + j] : 0u;
-            mine += c[j];
+        uint32_t c[8] = {}, mine = 0;
+        if (per == 8) {  // (16-byte reads: single ones, 8 words apart, meet in eight banks)
+            const uint4 lo = ((const uint4*)h)[2 * tid], hi = ((const uint4*)h)[2 * tid + 1];
+            c[0] = lo.x; c[1] = lo.y; c[2] = lo.z; c[3] = lo.w;
+            c[4] = hi.x; c[5] = hi.y; c[6] = hi.z; c[7] = hi.w;
+        } else if (tid < nbins) {
+            c[0] = h[tid];
         }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) mine += c[j];
         uint32_t cum = block_exclusive(mine, part, lane, wave, nullptr);
         if (cum < rem && rem <= cum + mine) {
 #pragma unroll
@@ -621,17 +629,19 @@ __global__ __launch_bounds__(PR_THREADS) void prune_small_kernel(PruneArgs a) {
         __syncthreads();
     };
     constexpr int F1 = 32 - PR_SMALL_BITS[0], F2 = F1 - PR_SMALL_BITS[1];
+    static_assert((1 << PR_SMALL_BITS[0]) == 8 * PR_THREADS && PR_SMALL_BITS[1] <= 10 && PR_SMALL_BITS[2] <= 10, "bins per thread: 8 or 1");
     if (tid == 0) nlist = 0u;
     clear(PR_SMALL_BITS[0]);
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) atomicAdd(&h[key[r] >> F1], 1u);
+    for (int r = 0; r < ROUNDS; ++r)
+        if (r < used) atomicAdd(&h[key[r] >> F1], 1u);
     pick(32, PR_SMALL_BITS[0]);
     const bool listed = have <= PR_LIST;
     const uint32_t nl = have;
     if (listed) {
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r)
-            if ((key[r] >> F1) == (prefix >> F1)) list[atomicAdd(&nlist, 1u) & (PR_LIST - 1)] = key[r];
+            if (r < used && (key[r] >> F1) == (prefix >> F1)) list[atomicAdd(&nlist, 1u) & (PR_LIST - 1)] = key[r];
     }
     clear(PR_SMALL_BITS[1]);
     if (listed) {
@@ -640,7 +650,7 @@ __global__ __launch_bounds__(PR_THREADS) void prune_small_kernel(PruneArgs a) {
     } else {
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r)
-            if ((key[r] >> F1) == (prefix >> F1))
+            if (r < used && (key[r] >> F1) == (prefix >> F1))
                 atomicAdd(&h[(key[r] >> F2) & ((1u << PR_SMALL_BITS[1]) - 1u)], 1u);
     }
     pick(F1, PR_SMALL_BITS[1]);
@@ -651,7 +661,7 @@ __global__ __launch_bounds__(PR_THREADS) void prune_small_kernel(PruneArgs a) {
     } else {
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r)
-            if ((key[r] >> F2) == (prefix >> F2)) atomicAdd(&h[key[r] & ((1u << PR_SMALL_BITS[2]) - 1u)], 1u);
+            if (r < used && (key[r] >> F2) == (prefix >> F2)) atomicAdd(&h[key[r] & ((1u << PR_SMALL_BITS[2]) - 1u)], 1u);
     }
     pick(F2, PR_SMALL_BITS[2]);
     // ---- positions: keys below the threshold (and equal to it) in earlier wavefronts
@@ -659,10 +669,12 @@ __global__ __launch_bounds__(PR_THREADS) void prune_small_kernel(PruneArgs a) {
     uint32_t lt = 0, eq = 0;
     if (!tied) {
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) lt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[r] <= prefix));
+        for (int r = 0; r < ROUNDS; ++r)
+            if (r < used) lt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[r] <= prefix));
     } else {
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
+            if (r >= used) continue;
             lt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[r] < prefix));
             eq += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[r] == prefix));
         }
@@ -678,7 +690,7 @@ __global__ __launch_bounds__(PR_THREADS) void prune_small_kernel(PruneArgs a) {
         taken += equal[w];
     }
     taken = min(taken, rem);
-    write_run<ROUNDS>(key, prefix, tied, rem, base + (tied ? taken : 0u), taken, k, a.kept + a.koff[t], i0, lane);
+    write_run<ROUNDS>(key, prefix, tied, rem, base + (tied ? taken : 0u), taken, k, a.kept + a.koff[t], i0, lane, used);
 }
 
 // Workspace layout.
