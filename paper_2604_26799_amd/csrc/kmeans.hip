@@ -311,6 +311,12 @@ int km_key_bits(int32_t K) {
     return bits;
 }
 
+// The size never falls with B or K, so that a workspace taken for the largest
+// batch and codebook serves every smaller one: the table is sized for the most
+// tiles that a batch of up to B rows can have (the tiles in use go down where
+// the tile grows: 256 of 256 rows at 65,536, 205 of 320 at 65,537), and the
+// radix sort's part takes at least what the counting sort of KM_LDS_K centers
+// does.
 KmLayout km_layout(int64_t B, int32_t D, int32_t K) {
     KmLayout L;
     std::memset(&L, 0, sizeof(L));
@@ -324,13 +330,16 @@ KmLayout km_layout(int64_t B, int32_t D, int32_t K) {
     L.xb = take(sizeof(float) * b * D);
     L.assign = take(sizeof(int32_t) * b);
     L.pos_s = take(sizeof(int32_t) * b);
+    const size_t most = std::min<size_t>(KM_TILES, (b + KM_TILE_MIN - 1) / KM_TILE_MIN);  // tiles
     if (K <= KM_LDS_K) {
         const int64_t even = ((int64_t)b + KM_TILES - 1) / KM_TILES;
         L.tile = (int32_t)std::max<int64_t>(KM_TILE_MIN, (even + MGS_WAVE - 1) / MGS_WAVE * MGS_WAVE);
         L.T = (int32_t)(((int64_t)b + L.tile - 1) / L.tile);
-        L.table = take(sizeof(uint32_t) * (size_t)L.T * K);
+        L.table = take(sizeof(uint32_t) * most * (size_t)K);
         L.run = take(sizeof(uint2) * (size_t)K);
     } else {
+        const size_t counting = o + mgs_align_up(sizeof(uint32_t) * most * (size_t)KM_LDS_K, 256) +
+                                mgs_align_up(sizeof(uint2) * (size_t)KM_LDS_K, 256);
         L.keys = take(sizeof(uint32_t) * b);
         L.keys_s = take(sizeof(uint32_t) * b);
         L.pos = take(sizeof(int32_t) * b);
@@ -339,6 +348,7 @@ KmLayout km_layout(int64_t B, int32_t D, int32_t K) {
                                         (const int32_t*)nullptr, (int32_t*)nullptr, (unsigned)b, 0,
                                         km_key_bits(K));
         L.sort = take(std::max<size_t>(L.sort_bytes, 1));
+        o = std::max(o, counting);
     }
     L.vq = take(mgs_vq_assign_ws_bytes(B, D, K));
     L.total = o;

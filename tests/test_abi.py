@@ -178,6 +178,28 @@ def test_workspace_queries():
     assert L.mgs_quant_sweep_ws_bytes(ct.byref(nok)) >= L.mgs_quant_sweep_ws_bytes(ct.byref(big))
 
 
+def test_workspace_queries_never_fall():
+    """A workspace taken for the largest call of a program serves its smaller ones."""
+    L = mgs.lib()
+    rows = sorted({max(1, e + d) for e in (1, 256, 16384, 65536, 81920, 98304, 262144, 1 << 20) for d in (-1, 0, 1, 65)})
+    wide = sorted({max(1, e + d) for e in (1, 64, 4096, 16384, 65536) for d in (-1, 0, 1)})
+    for B in rows:
+        for D in (1, 36, 64):
+            sizes = [L.mgs_kmeans_step_ws_bytes(B, D, K) for K in wide]
+            assert sizes == sorted(sizes), (B, D)
+    for K in wide:
+        for D in (1, 36, 64):
+            sizes = [L.mgs_kmeans_step_ws_bytes(B, D, K) for B in rows]
+            assert sizes == sorted(sizes), (D, K)
+            sizes = [L.mgs_vq_assign_ws_bytes(B, D, K) for B in rows]
+            assert sizes == sorted(sizes), (D, K)
+    for n in (1, 20, 64):
+        sizes = [L.mgs_prune_select_ws_bytes(B, n) for B in rows]
+        assert sizes == sorted(sizes), n
+        sizes = [L.mgs_raht_ws_bytes(B, n, 14) for B in rows]
+        assert sizes == sorted(sizes), n
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     """The product path has no fallback: a missing library is an error."""
     monkeypatch.setattr(mgs, "_lib", None)

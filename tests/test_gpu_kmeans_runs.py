@@ -55,3 +55,29 @@ def test_run_lengths(torch, orc):
     own = rng.permutation(np.repeat(np.arange(len(lens)), lens))
     x = (cb[own] + rng.normal(0, 1, (own.size, 12))).astype(np.float32)
     check(torch, orc, x, cb, np.arange(len(lens), dtype=np.int64), rng.permutation(own.size))
+
+
+@pytest.mark.parametrize("B,K,B1,K1", [
+    (65536, 64, 65537, 64),     # the tile grows: fewer tiles, a smaller table in use
+    (300, 16384, 300, 16385),   # the last codebook of the counting sort, the first of the radix sort
+])
+def test_workspace_of_a_larger_call(torch, B, K, B1, K1):
+    """A workspace sized for a larger batch or codebook serves the smaller call."""
+    L = mgs.lib()
+    g = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randn(1000, 4, device="cuda", generator=g)
+    batch = torch.randint(0, 1000, (B,), device="cuda", generator=g)
+    ws = mgs.workspace(L.mgs_kmeans_step_ws_bytes(B1, 4, K1), x.device)
+    out = []
+    for held in (True, False):
+        cb = torch.randn(K, 4, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+        counts = torch.zeros(K, dtype=torch.int64, device="cuda")
+        if held:
+            assert L.mgs_kmeans_step(x.data_ptr(), 1000, 4, batch.data_ptr(), B, cb.data_ptr(), K,
+                                     counts.data_ptr(), None, ws.data_ptr(), ws.numel(),
+                                     torch.cuda.current_stream().cuda_stream) == mgs.OK
+            assert mgs.status(ws) == mgs.OK
+        else:
+            mgs.kmeans_step(x, cb, counts, batch)
+        out.append((cb, counts))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
