@@ -95,6 +95,13 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
     return v;
 }
 
+// LDS accesses of one wavefront complete in order: this only keeps the
+// compiler from moving them.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ bool finite_f32(float x) { return __builtin_isfinite(x); }
 
 // Fill kernel used instead of memset so the calls stay graph-capturable.

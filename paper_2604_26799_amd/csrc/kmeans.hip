@@ -201,12 +201,16 @@ __global__ __launch_bounds__(256) void km_scatter_kernel(KmArgs a) {
             __syncthreads();  // the places of the tile are there, or of the waves before
             if (wave != w) continue;
 #pragma unroll
-            for (int u = 0; u < KS_U; ++u)
-                if (key[u] < (uint32_t)a.K) {
-                    const uint32_t at = km_lds[key[u]];  // read by all of them before the first moves it on
-                    if (rank[u] == 0) km_lds[key[u]] = at + cnt[u];
-                    a.pos_s[(size_t)at + rank[u]] = (int32_t)(b + u * MGS_WAVE);
-                }
+            for (int u = 0; u < KS_U; ++u) {
+                // the place is read by all lanes of the center before the first
+                // of them moves it on, and that before the next rows' lanes read it
+                const bool valid = key[u] < (uint32_t)a.K;
+                const uint32_t at = valid ? km_lds[key[u]] : 0u;
+                wave_order();
+                if (valid && rank[u] == 0) km_lds[key[u]] = at + cnt[u];
+                wave_order();
+                if (valid) a.pos_s[(size_t)at + rank[u]] = (int32_t)(b + u * MGS_WAVE);
+            }
         }
     }
 }

@@ -136,13 +136,6 @@ __device__ __forceinline__ uint64_t same_bin(bool valid, int b) {
 
 __device__ __forceinline__ uint64_t lanes_below(int lane) { return lane == 0 ? 0ull : (~0ull >> (64 - lane)); }
 
-// LDS accesses of one wavefront complete in order: this only keeps the
-// compiler from moving them.
-__device__ __forceinline__ void wave_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Rank of this lane's item among the items of its bin so far (`h`: the
 // wavefront's counters, which take this round's items up).
 __device__ __forceinline__ int bin_rank(bool valid, int b, uint32_t* h, int lane) {

@@ -81,3 +81,16 @@ def test_workspace_of_a_larger_call(torch, B, K, B1, K1):
             mgs.kmeans_step(x, cb, counts, batch)
         out.append((cb, counts))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 64, 65])
+def test_places_shared_by_lanes(torch, orc, K):
+    """Wavefronts of 64 rows whose centers repeat in every pattern of lanes (all one center, two in
+    turn, 64 of them, ..), in one and in several steps of a wavefront: the rows of a center that meet
+    in a wavefront take consecutive places, in batch order."""
+    cb = (np.arange(K)[:, None] * np.full((1, 5), 40.0)).astype(np.float32)
+    rng = np.random.default_rng(K)
+    for B in (64, 1024, 5000):
+        own = np.concatenate([np.arange(B // 2) % K, np.repeat(np.arange(K), -(-B // K))])[:B]
+        x = (cb[own] + rng.normal(0, 1, (B, 5)) * np.float32(10.0) ** rng.integers(-6, 1, (B, 1))).astype(np.float32)
+        check(torch, orc, x, cb, np.zeros(K, np.int64), np.arange(B))
