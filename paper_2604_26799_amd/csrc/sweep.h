@@ -89,6 +89,15 @@ struct Shape {
     int persist = 0;  // 1: a persistent grid sized to the resident slots, tiles from per-XCD queues
 };
 
+// Static LDS of a kernel of nt threads that keeps the loss sums of sub * nt
+// (everything but the histogram words), with room for the alignment of its
+// parts: log and increment tables, loss and size sums, the reductions' words,
+// the flags, the tile index of the persistent grid.
+constexpr int static_lds_bytes(int nt, int sub) {
+    const int nw = nt / MGS_WAVE;
+    return 2 * 8 * LGTAB + 8 * MGS_MAX_BITS * nw * (sub + 1) + 3 * 4 * nw + 4 + 4 * MGS_MAX_ENTRIES + 8 + 256 + 16;
+}
+
 int fill_scene(const mgs_sweep_desc* d, const float* attr, const float* imp, const int32_t* kept,
                double* err, double* bits, float* gmin, float* gmax, uint32_t* hist, SceneDesc* sc);
 bool build_plan(const uint8_t* bl, int nb, int cap_words, int G, SweepParams* p);

@@ -1202,15 +1202,6 @@ int device_cus() {
     return cached;
 }
 
-// Static LDS of a kernel variant (everything but the histogram words), with
-// room for the tile index of the persistent grid and the 16-byte alignment
-// of the histogram words.
-static int static_lds_bytes(int nt) {
-    int nw = nt / MGS_WAVE;
-    return (int)(2 * sizeof(double) * LGTAB + 2 * sizeof(double) * MGS_MAX_BITS * nw + 4 * 4 * nw +
-                 2 * 4 * MGS_MAX_BITS + 4 * MGS_MAX_ENTRIES + sizeof(int64_t)) + 256 + 16;
-}
-
 #ifndef MGS_RTN_FACTOR
 #define MGS_RTN_FACTOR 0.0625
 #endif
@@ -1339,7 +1330,9 @@ bool build_plan(const uint8_t* bl, int nb, int cap_words, int G, SweepParams* p)
 int plan_for(const SceneDesc& sc, const Shape& sh, SweepParams* p, size_t* lds_bytes) {
     int devlds = device_lds_bytes();
     int cap = sh.lds_cap > 0 ? std::min(sh.lds_cap, devlds) : devlds;
-    int cap_words = (cap - static_lds_bytes(sh.nt)) / 4;
+    const Variant* v = find_variant(sh.nt, sh.ept, sc.G);
+    if (!v) return MGS_EINVAL;
+    int cap_words = (cap - static_lds_bytes(v->nt, v->sub)) / 4;
     // keep the capacity a power of two so bin windows tile 2^b evenly
     int pw = 1024;
     while (pw * 2 <= cap_words) pw *= 2;
