@@ -346,8 +346,8 @@ void vq_main_kernel(VqArgs a) {
                     if (k < D) {
                         if (r < a.N) {
                             bad |= (uint32_t)!finite_f32(e);
-                            n2 += e * e;
                             v = e * sg;
+                            n2 += v * v;
                             bg |= !(fabsf(v) < 32768.0f);
                         }
                     } else if (k == D || k == D + 1) {
@@ -376,8 +376,8 @@ void vq_main_kernel(VqArgs a) {
                     if (k < D) {
                         if (r < a.N) {
                             bad |= (uint32_t)!finite_f32(e);
-                            n2 += e * e;
                             v = e * sg;
+                            n2 += v * v;
                             bg |= !(fabsf(v) < 32768.0f);
                         }
                     } else if (k == D || k == D + 1) {
@@ -388,8 +388,10 @@ void vq_main_kernel(VqArgs a) {
         }
         n2 += __shfl_xor(n2, 32, MGS_WAVE);
         big[rs] = (bg | (__shfl_xor((int)bg, 32, MGS_WAVE) != 0));
-        // the bound in scaled units (sigma is a power of two)
-        const double xs = (double)sg * (sqrt((double)n2) * (1.0 + 1.0e-5) + 1e-30);
+        // the bound in scaled units (sigma is a power of two).  The squares are
+        // those of the scaled values, which FP32 holds at any scale of the data
+        // (of a row inside FP16; below 2^-75 they vanish, and 1e-18 covers that)
+        const double xs = sqrt((double)n2) * (1.0 + 1.0e-5) + 1e-18;
         const double cs = (double)sg * (double)cm;
         const double u = 0x1p-11, aa = 0x1p-14, rd = sqrt((double)D);
         const double g = (double)(D + 3) * 0x1p-23;
