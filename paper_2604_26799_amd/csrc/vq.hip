@@ -16,7 +16,8 @@
 //      keeps its running minimum without cross-lane work.  ||sigma c_j||^2
 //      enters as two extra K columns (its FP16 high and low parts) against
 //      constant 1s in X.  A row with a scaled value of 2^15 or more (outside
-//      FP16) goes to the exact scan of step 3.
+//      FP16) goes to the exact scan of step 3, and every row does when cmax
+//      is past FP32.
 //   2. Error bound per row, in scaled units (xs = sigma |x_i|, cs = sigma cmax):
 //        E_i = (2u+u^2) xs 2cs + a(1+u) sqrt(D)(2cs + xs) + D a^2 + 2u^2 cs^2 + 2a
 //              + g (2.02 xs cs + 1.01 cs^2)
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(VQ_CB_THREADS) void vq_norm_kernel(VqArgs a) {
                 n2 += (double)v[k] * (double)v[k];
             }
         if (bad) atomicOr(&a.status->nonfinite, 1u);
-        nrm = (float)sqrt(n2) * (1.0f + 1.0e-6f);
+        else nrm = (float)sqrt(n2) * (1.0f + 1.0e-6f);  // (infinite past FP32: every row takes the exact scan)
     }
     // the block's largest norm, then one atomic per block (thousands of
     // atomics on one address serialise)
@@ -387,7 +388,7 @@ void vq_main_kernel(VqArgs a) {
                 }
         }
         n2 += __shfl_xor(n2, 32, MGS_WAVE);
-        big[rs] = (bg | (__shfl_xor((int)bg, 32, MGS_WAVE) != 0));
+        big[rs] = (bg | (__shfl_xor((int)bg, 32, MGS_WAVE) != 0)) | !finite_f32(cm);
         // the bound in scaled units (sigma is a power of two).  The squares are
         // those of the scaled values, which FP32 holds at any scale of the data
         // (of a row inside FP16; below 2^-75 they vanish, and 1e-18 covers that)

@@ -1,5 +1,5 @@
-"""VQ assignment over the whole range of FP32: values whose squares underflow or overflow in FP32
-and subnormal values.  Indices and distances
+"""VQ assignment over the whole range of FP32: values whose squares underflow or overflow in FP32,
+subnormal values, and codebooks whose norms exceed the largest FP32 number.  Indices and distances
 equal the FP64 definition bit for bit."""
 import numpy as np
 import pytest
@@ -45,3 +45,14 @@ def test_rows_far_below_the_codebook(torch, orc, D):
     x = (rng.laplace(0, 1, (3000, D)) * 10.0 ** rng.uniform(-45, 0, (3000, 1))).astype(np.float32)
     x[::97] = 0.0
     check(torch, orc, x, rng.laplace(0, 1, (300, D)).astype(np.float32))
+
+
+@pytest.mark.parametrize("D", [36, 64])
+def test_codebook_norms_past_fp32(torch, orc, D):
+    rng = np.random.default_rng(D)
+    cb = (rng.uniform(-1, 1, (130, D)) * 3e38).astype(np.float32)
+    x = (rng.uniform(-1, 1, (500, D)) * 3e38).astype(np.float32)
+    x[:100] *= np.float32(1e-30)
+    x[100:200] *= np.float32(1e-37)  # (these rows are inside FP16 without a scale)
+    x[200:230] = 0.0
+    check(torch, orc, x, cb)
