@@ -71,6 +71,7 @@ constexpr int VQ_CHUNK = 64;                           // codewords per chunk of
 // against 1024 49 / 59; 32,000 x 64 against 512 44 / 61, 65,000 64 / 60.
 constexpr int64_t vq_few_rows(int KS) { return KS <= 4 ? 65536 : 32768; }
 constexpr int VQ_EXACT_BATCH = 3;                       // float4 groups of an exact distance loaded together
+constexpr int VQ_SHORT = 8;                             // longest row of the exact stage's short form
 constexpr int VQ_CAND = 8;                             // candidate tiles per lane and row set
 
 struct VqArgs {
@@ -255,6 +256,26 @@ __device__ __forceinline__ double exact_dist_batch(const float* __restrict__ x, 
     return s;
 }
 
+// The same for rows of up to VQ_SHORT values in registers (D is the same for
+// every lane: what is past it is branched over, not repeated).
+__device__ __forceinline__ void load_short(const float* __restrict__ p, int D, float (&v)[VQ_SHORT]) {
+#pragma unroll
+    for (int k = 0; k < VQ_SHORT; ++k) {
+        if (k == D) break;
+        v[k] = p[k];
+    }
+}
+__device__ __forceinline__ double exact_dist_short(const float (&x)[VQ_SHORT], const float (&c)[VQ_SHORT], int D) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < VQ_SHORT; ++k) {
+        if (k == D) break;
+        const double d = (double)x[k] - (double)c[k];
+        s += d * d;
+    }
+    return s;
+}
+
 // VEC: D % 4 == 0 and x 16-byte aligned (rows load as float4).  VQ_ROWSETS: 32-row
 // sets per wave.  SUB: chunks per LDS buffer.
 // Many rows: two row sets (an A load feeds twice as many MFMAs) and one chunk per
@@ -362,11 +383,13 @@ void vq_main_kernel(VqArgs a) {
             const int64_t rbase = row0 < a.N ? row0 : a.N - 1, rr = r < a.N ? r : a.N - 1;
             const float* xw = a.x + rbase * D;
             const uint32_t rel = (uint32_t)(rr - rbase) * (uint32_t)D;
-            float t[KS][8];
+            float t[KS][8] = {};
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) t[ks][i] = xw[rel + (uint32_t)min(16 * ks + 8 * half + i, D - 1)];
+                for (int i = 0; i < 8; ++i)
+                    if (KS > 1 || i < D)  // (short rows: none that no lane needs)
+                        t[ks][i] = xw[rel + (uint32_t)min(16 * ks + 8 * half + i, D - 1)];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -529,6 +552,12 @@ void vq_main_kernel(VqArgs a) {
             int e = 0;
             int jbase = n > 0 ? cand_t[wave][rs][0][lane] : 0;
             uint32_t bits = n > 0 ? cand_m[wave][rs][0][lane] : 0u;
+            auto take = [&](int32_t j, double d) {
+                if (d < best || (d == best && j < bj)) {
+                    best = d;
+                    bj = j;
+                }
+            };
             // the lane's next candidate codeword; false once none is left
             auto next = [&](int32_t& j) {
                 for (;;) {
@@ -544,26 +573,56 @@ void vq_main_kernel(VqArgs a) {
                     bits = cand_m[wave][rs][e][lane];
                 }
             };
-            // one candidate per lane and turn: a row has 1.1 of them on average,
-            // in one of its lanes, and a lane that has none left takes one of
-            // its row's other lane (two per lane and turn, the second mostly the
-            // first again: 3,000,000 x 36 against 4096 2 % slower)
-            for (;;) {
-                int32_t j = -1, give = -1;
-                bool have = next(j);
-                if (!__shfl_xor((int)have, 32, MGS_WAVE) && have && !next(give)) give = -1;
-                const int32_t got = __shfl_xor(give, 32, MGS_WAVE);
-                if (!have && got >= 0) {
-                    j = got;
-                    have = true;
+            if (KS == 1 && (VEC ? D == 4 : D <= VQ_SHORT)) {
+                // short rows: a codebook that fills so few dimensions leaves
+                // several candidates, so each lane takes its own, two at a time,
+                // and the row stays in registers.  1,000,000 rows, D = 1 against
+                // 64, 2 and 3 against 1000, 4 against 4096: 61, 186, 138 and 350
+                // us, in the form below 98, 266, 170 and 366.  Longer rows leave
+                // about one and are faster there (D = 9 against 1000 154, two at
+                // a time 158; D = 14 153 and 176).
+                auto load = [&](const float* p, bool quad, float(&v)[VQ_SHORT]) {
+                    if (VEC && quad) {
+                        const float4 q = *(const float4*)p;
+                        v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
+                    } else {
+                        load_short(p, D, v);
+                    }
+                };
+                float xv[VQ_SHORT] = {};
+                load(xr, true, xv);
+                int32_t j0 = 0, j1 = 0;
+                bool more = next(j0);
+                while (more) {
+                    if (!next(j1)) {  // (an odd last one is scored twice)
+                        j1 = j0;
+                        more = false;
+                    }
+                    float c0[VQ_SHORT] = {}, c1[VQ_SHORT] = {};
+                    load(a.cb + (int64_t)j0 * D, a.cvec, c0);
+                    load(a.cb + (int64_t)j1 * D, a.cvec, c1);
+                    take(j0, exact_dist_short(xv, c0, D));
+                    take(j1, exact_dist_short(xv, c1, D));
+                    if (more) more = next(j0);
                 }
-                if (!__builtin_amdgcn_ballot_w64(have)) break;
-                if (have) {
-                    const float* c = a.cb + (int64_t)j * D;
-                    const double d = vec ? exact_dist_vec<KP / 4>(xr, c, D) : exact_dist_batch(xr, c, D);
-                    if (d < best || (d == best && j < bj)) {
-                        best = d;
-                        bj = j;
+            } else {
+                // one candidate per lane and turn: a row has 1.1 of them on average,
+                // in one of its lanes, and a lane that has none left takes one of
+                // its row's other lane (two per lane and turn, the second mostly the
+                // first again: 3,000,000 x 36 against 4096 2 % slower)
+                for (;;) {
+                    int32_t j = -1, give = -1;
+                    bool have = next(j);
+                    if (!__shfl_xor((int)have, 32, MGS_WAVE) && have && !next(give)) give = -1;
+                    const int32_t got = __shfl_xor(give, 32, MGS_WAVE);
+                    if (!have && got >= 0) {
+                        j = got;
+                        have = true;
+                    }
+                    if (!__builtin_amdgcn_ballot_w64(have)) break;
+                    if (have) {
+                        const float* c = a.cb + (int64_t)j * D;
+                        take(j, vec ? exact_dist_vec<KP / 4>(xr, c, D) : exact_dist_batch(xr, c, D));
                     }
                 }
             }

@@ -53,3 +53,21 @@ def test_unaligned_rows(torch, orc):
         idx, dist, _ = mgs.vq_assign(gx, gc)
         wi, wd = orc.vq_assign(x[:n], cb)[:2]
         assert np.array_equal(idx.cpu().numpy(), wi) and np.array_equal(dist.cpu().numpy(), wd)
+
+
+@pytest.mark.parametrize("D", [1, 2, 3, 4, 5, 6, 7, 8, 9])
+@pytest.mark.parametrize("N,K", [(700, 65), (3000, 1000), (70_000, 300)])
+def test_short_rows(torch, orc, D, N, K):
+    """Rows of few values, which leave several candidates each (repeated codewords among them), at
+    and off 16-byte boundaries."""
+    rng = np.random.default_rng(10 * D + K)
+    x = rng.laplace(0, 0.03, (N, D)).astype(np.float32)
+    cb = rng.laplace(0, 0.03, (K, D)).astype(np.float32)
+    cb[K // 3] = cb[K - 1] = cb[2]
+    x[::5] = cb[rng.integers(0, K, x[::5].shape[0])]
+    wi, wd = orc.vq_assign(x, cb)[:2]
+    for xs, cs in ((0, 0), (1, 0), (0, 1), (1, 1)):
+        gx = torch.empty(N * D + xs, device="cuda")[xs:].view(N, D).copy_(torch.from_numpy(x))
+        gc = torch.empty(K * D + cs, device="cuda")[cs:].view(K, D).copy_(torch.from_numpy(cb))
+        idx, dist, _ = mgs.vq_assign(gx, gc)
+        assert np.array_equal(idx.cpu().numpy(), wi) and np.array_equal(dist.cpu().numpy(), wd), (xs, cs)
