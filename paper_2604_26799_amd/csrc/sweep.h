@@ -102,7 +102,9 @@ int fill_scene(const mgs_sweep_desc* d, const float* attr, const float* imp, con
                double* err, double* bits, float* gmin, float* gmax, uint32_t* hist, SceneDesc* sc);
 bool build_plan(const uint8_t* bl, int nb, int cap_words, int G, SweepParams* p);
 int plan_for(const SceneDesc& sc, const Shape& sh, SweepParams* p, size_t* lds_bytes);
-Shape default_shape(int G, int64_t pairs, int channels);  // pairs: (group, channel) pairs of the launch
+// Launch shape of a launch of `pairs` (group, channel) pairs over up to `channels`
+// channels; G and the bit-widths are those of any of its scenes.
+Shape default_shape(const SceneDesc& sc, int64_t pairs, int channels);
 bool shape_valid(const Shape& sh, int G);
 // Copies `count` scene descriptors into device memory and prepares the
 // tables (NaN padding, status reset, debug histogram clearing) and each

@@ -1396,8 +1396,8 @@ int fill_scene(const mgs_sweep_desc* d, const float* attr, const float* imp, con
 
 bool shape_valid(const Shape& sh, int G) { return find_variant(sh.nt, sh.ept, G) != nullptr; }
 
-// Default launch shape, by group size G and the launch's number of (group,
-// channel) pairs.
+// Default launch shape, by group size G, the bit-widths and the launch's number
+// of (group, channel) pairs.
 //
 // Threads and elements per thread.  Each wavefront pays about 60 VALU
 // instructions per channel and bit-width around the pass over its elements, so
@@ -1430,7 +1430,19 @@ bool shape_valid(const Shape& sh, int G) { return find_variant(sh.nt, sh.ept, G)
 // three 1.08 / all 1.08 ms, 44 pairs four 1.77 / all with the split tail 1.73.
 // The chunked kernel gathers indices and weights for every channel anyway: one
 // channel per tile, persistent (4.27 against 4.39 ms, 0.95 against 1.30 ms).
-Shape default_shape(int G, int64_t pairs, int channels) {
+//
+// Short tiles.  A persistent grid hands out about 35 tiles per us (one atomic
+// each on the counters of 8 XCDs); a plain one starts workgroups faster.  Tiles
+// of little work -- evaluations, and a quarter of the bins to clear and read --
+// therefore go to a plain grid: 100,000 x 20, 4 ratios, b = 8, G = 256 172 us
+// persistent, 68 plain; 1e6 x 11, 8 ratios, b = 8, G = 2048 (23,000 per tile) 160
+// / 122, b = 2..8, G = 500 (40,000) 735 / 714; 1e6 x 1, b = 2..16, G = 2048
+// (63,000) 147 / 118.  From there on the two are level or the persistent grid is
+// ahead: 100,000 x 11, b = 2..16, G = 200 (71,000) 343 / 352 us, 100,000 x 20, G
+// = 100 (690,000) 1.11 / 1.20 ms.
+constexpr int64_t kShortTile = 65536;
+Shape default_shape(const SceneDesc& sc, int64_t pairs, int channels) {
+    const int G = sc.G;
     const int64_t cus = device_cus();
     if (G > 16384) return Shape{512, 16, 0, 1, 1};
     Shape sh;
@@ -1445,6 +1457,8 @@ Shape default_shape(int G, int64_t pairs, int channels) {
         sh.cpb = rounds < 6.0 ? 1 : rounds < 20.0 ? 2 : 3;
         sh.persist = sh.cpb > 1;
     }
+    const int64_t work = (int64_t)G * sc.nb + sc.hist_bins / 4;
+    if (work * (sh.cpb ? sh.cpb : channels) < kShortTile) sh.persist = 0;
     return sh;
 }
 
@@ -1606,7 +1620,7 @@ static int sweep_launch_scenes(mgs::SceneDesc* scs, int n, void* d_ws, size_t ws
             pairs += (int64_t)scs[i].gpc * scs[i].C;
             cm = std::max(cm, (int)scs[i].C);
         }
-        sh = default_shape(s0.G, pairs, cm);
+        sh = default_shape(s0, pairs, cm);
     }
     if (!shape_valid(sh, s0.G)) return MGS_EINVAL;
     SweepParams p;

@@ -144,3 +144,28 @@ def test_default_shape_keeps_the_tables(torch, G, n, C, T, wide):
     both = mgs.quant_sweep_multi(scenes, G, bits)[0]
     for key in ("err", "bits", "gmin", "gmax"):
         assert np.array_equal(both[key].cpu().numpy(), got[key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("G,n,C,bits", [
+    (64, 200_000, 3, [8]), (64, 200_000, 3, list(range(1, 17))),    # whole groups: plain, persistent
+    (1000, 300_000, 20, [1, 2]), (1000, 300_000, 20, [2, 9, 16]),   # runs of channels: plain, persistent
+])
+def test_short_tiles(torch, orc, G, n, C, bits):
+    """Launches of many tiles on both sides of the line between plain and persistent grids: the oracle's
+    tables, and those of one-channel tiles in a plain grid, bit for bit."""
+    attr, imp = synth.scene(n, 20, seed=G)
+    attr = np.ascontiguousarray(attr[:C])
+    k = np.array([n, n // 2 + 1], np.int64)
+    kept = orc.prune_select(imp, k)
+    got = sweep(torch, attr, imp, kept, k, G, bits)
+    nt, ept, cap = 256, (1 if G <= 256 else 4), 40960
+    try:
+        mgs.sweep_set_shape(G, len(bits), max(bits), nt, ept, cap, 1, 0)
+        want = sweep(torch, attr, imp, kept, k, G, bits)
+    finally:
+        mgs.sweep_set_shape(G, len(bits), max(bits), 0, 0, 0, 0)
+    for key in ("err", "bits", "gmin", "gmax"):
+        assert np.array_equal(got[key], want[key], equal_nan=True), key
+    few = slice(0, 2)  # (the oracle takes its time over two channels)
+    ref = orc.quant_sweep(np.ascontiguousarray(attr[few]), imp, kept, k, G, bits)
+    assert_tables({key: got[key][:, few] for key in got}, ref)
