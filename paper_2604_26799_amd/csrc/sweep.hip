@@ -905,14 +905,16 @@ void sweep_kernel(SweepParams p) {
                 // 2^rlog copies from its adjacent words (16-byte reads); the
                 // wavefronts take the bins in 64-bin slices, the first slice
                 // of each entry on a wavefront that rotates with the entry, and
-                // only wavefronts that held a slice sum their lanes.
-                if (!dbg) {
+                // only wavefronts that held a slice sum their lanes.  A sum is
+                // kept under its slice, not its wavefront: the table entry,
+                // which adds them in order, then depends neither on the plan
+                // nor on the workgroup's width.
+                {
                     for (int e = e0; e < p.batch_scan_end[bt]; ++e) {
                         const HistEntry en = p.entries[e];
                         const int rl = en.rlog, R = 1 << rl;
                         const int nq = en.nwords >> rl;  // bins (packed: words of two bins)
-                        const int first_w = (e * 5) % NW;
-                        const int slice = wave >= first_w ? wave - first_w : wave + NW - first_w;
+                        const int slice = (wave - e * 5) & (NW - 1);
                         if (slice * MGS_WAVE >= nq) continue;
                         double s = 0.0;
                         for (int q = slice * MGS_WAVE + lane; q < nq; q += NT) {
@@ -935,7 +937,7 @@ void sweep_kernel(SweepParams p) {
                                 s += hlog2h(h, lg, lgt);
                         }
                         const double tot = wave_sum63_f64(s);
-                        if (lane == 63) bitpart[en.bi][wave] += tot;
+                        if (lane == 63) bitpart[en.bi][slice] += tot;
                     }
                 }
                 // ---- the rest: incremental entries whose range underflows at
@@ -943,14 +945,14 @@ void sweep_kernel(SweepParams p) {
                 // incremental ones whose bins outgrew the LDS table (a bin of
                 // h > LGTAB got floor(h / LGTAB) full cycles of the increments plus
                 // the first h mod LGTAB of them, and needs R(T(h)) on the same
-                // grid), and, with the optional debug copy of the bins, every
-                // entry (scanned ones included)
+                // grid), and, with the optional debug copy of the bins, the
+                // copy of every entry
                 const int e_beg = dbg ? e0 : p.batch_scan_end[bt];
                 const int e_end = (any_ovf || anyzero || dbg) ? e1 : p.batch_scan_end[bt];
                 for (int e = e_beg; e < e_end; ++e) {
                     const HistEntry en = p.entries[e];
-                    const bool scan = !en.rtn || ((zero_S >> en.bi) & 1ull);
-                    const bool fix = !scan && any_ovf;
+                    const bool scan = en.rtn && ((zero_S >> en.bi) & 1ull);
+                    const bool fix = en.rtn && !scan && any_ovf;
                     uint32_t* hout = sc->hist ? sc->hist + slot * sc->hist_bins + sc->hoff[en.bi] : nullptr;
                     if (!scan && !fix && !hout) continue;
                     double s = 0.0;
@@ -1406,12 +1408,16 @@ bool shape_valid(const Shape& sh, int G) { return find_variant(sh.nt, sh.ept, G)
 // shapes keep the wide shape's sums, so the choice changes no table.  Measured
 // on 1e6 x 20, 16 ratios: G = 8192, b = 2..16, 512 x 16 1.73 ms against 2.39
 // for 1024 x 8; G = 4096, b = 1..16, 256 x 16 2.22 ms against 3.59 for 512 x 8
-// with the whole LDS.  G <= 1024 leaves out the idle elements of 256 x 8.  A
-// launch of fewer pairs than resident workgroups would be a little faster in
-// the wide shape (55 against 62 us for 160 pairs of G = 8192), but the
-// histogram plan, and with it the last bits of the sizes, goes with the shape,
-// which therefore depends on G alone: a scene's tables are the same bit for
-// bit alone and in a batch.
+// with the whole LDS.  G <= 1024 leaves out the idle elements of 256 x 8.
+//
+// Launches of one workgroup per CU, or of two that are no wider together than a
+// CU's 1024 threads, have nothing to hide barriers behind and LDS to spare: the
+// wide shape, 8 elements per thread, and all or half of the LDS (fewer bin
+// windows).  1e5 x 1, 4 ratios, b = 2..16, 30 to 114 pairs: G = 4096 38 us against
+// 62 for 256 x 16 in 40 KB, G = 8192 39 / 49, G = 2048 39 / 47; two per CU: G =
+// 500, 460 pairs 36 / 41, G = 4096, 638 pairs (three) 68 / 72.  Sizes are summed so
+// that they depend on neither width nor plan, and losses as above: a scene's
+// tables are the same bit for bit alone and in a batch.
 //
 // LDS.  A workgroup plans its histograms in its share of the CU's LDS at four
 // wavefronts per SIMD (1024 threads per CU): with a larger share fewer
@@ -1446,6 +1452,14 @@ Shape default_shape(const SceneDesc& sc, int64_t pairs, int channels) {
     const int64_t cus = device_cus();
     if (G > 16384) return Shape{512, 16, 0, 1, 1};
     Shape sh;
+    const int64_t per_cu = (pairs + cus - 1) / cus;
+    if (G <= 8192 && per_cu <= 2 && per_cu * loss_width(G) <= 1024) {
+        sh.nt = loss_width(G);
+        sh.ept = G <= 256 ? 1 : G <= 512 ? 2 : G <= 1024 ? 4 : 8;
+        sh.lds_cap = per_cu == 2 ? device_lds_bytes() / 2 : 0;
+        sh.cpb = 1;
+        return sh;
+    }
     sh.nt = G <= 4096 ? 256 : G <= 8192 ? 512 : 1024;
     sh.ept = G <= 256 ? 1 : G <= 512 ? 2 : G <= 1024 ? 4 : G <= 2048 ? 8 : 16;
     sh.lds_cap = sh.nt >= 1024 ? 0 : (int)((int64_t)device_lds_bytes() * sh.nt / 1024);

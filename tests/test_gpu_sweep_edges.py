@@ -169,3 +169,33 @@ def test_short_tiles(torch, orc, G, n, C, bits):
     few = slice(0, 2)  # (the oracle takes its time over two channels)
     ref = orc.quant_sweep(np.ascontiguousarray(attr[few]), imp, kept, k, G, bits)
     assert_tables({key: got[key][:, few] for key in got}, ref)
+
+
+@pytest.mark.parametrize("G,shapes", [
+    (300, [(256, 2)]), (2048, [(256, 8)]), (3000, [(512, 8), (256, 16)]), (4096, [(512, 8), (256, 16)]),
+    (5000, [(1024, 8), (512, 16)]), (8192, [(1024, 8), (512, 16)]),
+])
+def test_sizes_do_not_depend_on_the_plan(torch, orc, G, shapes):
+    """A small launch and a large one of the same groups differ in the workgroup's width and in the LDS
+    that its histograms are planned in: the tables are the same bit for bit, sizes too, and so are
+    those of a call that also returns the histograms."""
+    n = 3 * G + G // 3
+    attr, imp = synth.scene(n, 11, seed=G)
+    attr = np.ascontiguousarray(attr[:6])
+    attr[5] = np.round(attr[5] * 2)  # few values: bins of many elements
+    k, bits = np.array([n, 2 * G], np.int64), [1, 3, 4, 5, 7, 8, 9, 12, 14, 15, 16]
+    kept = orc.prune_select(imp, k)
+    want = orc.quant_sweep(attr, imp, kept, k, G, bits)
+    first = sweep(torch, attr, imp, kept, k, G, bits)  # (the default of a small launch)
+    assert_tables(first, want)
+    d = [dev(torch, a) for a in (attr, imp, kept.astype(np.int32))]
+    try:
+        for nt, ept in shapes:
+            for cap in (0, 81920, 40960):
+                mgs.sweep_set_shape(G, len(bits), max(bits), nt, ept, cap, 1, 0)
+                for hist in (False, True):
+                    got = mgs.quant_sweep(*d, k, G, bits, want_hist=hist)
+                    for key in ("err", "bits", "gmin", "gmax"):
+                        assert np.array_equal(got[key].cpu().numpy(), first[key], equal_nan=True), (nt, cap, hist, key)
+    finally:
+        mgs.sweep_set_shape(G, len(bits), max(bits), 0, 0, 0, 0)
