@@ -82,3 +82,22 @@ def test_nonfinite_then_clean(torch, orc, n, bad):
     assert (out[int(k.sum()):] == -7).all()
     got = mgs.prune_select(torch.from_numpy(imp).cuda(), k, ws=ws, out=out[:int(k.sum())]).cpu().numpy()
     np.testing.assert_array_equal(got, orc.prune_select(imp, k))
+
+
+@pytest.mark.parametrize("n", [64, 700, 16384, 16385, 50_000, 65_536])
+@pytest.mark.parametrize("crowd", [1, 7, 8, 9, 40, 64])
+def test_crowded_bins(torch, orc, n, crowd):
+    """Up to `crowd` of every 64 keys in one bin (equal, or close together), in the first lanes or from
+    the middle on; thresholds inside the crowd, beside it and at its edges."""
+    rng = np.random.default_rng(n + crowd)
+    for shift in (0, 32):
+        imp = rng.lognormal(0, 2, n).astype(np.float32)
+        lane = (np.arange(n) - shift) % 64
+        hit = (lane < crowd) & (rng.random(n) < 0.95)
+        imp[hit] = np.float32(0.5)
+        near = hit & (rng.random(n) < 0.3)
+        imp[near] += rng.integers(0, 5, int(near.sum())).astype(np.float32) * np.float32(2 ** -24)
+        above, below = int((imp > 0.6).sum()), int((imp >= 0.5).sum())
+        k = np.array([0, n, above, below, (above + below) // 2, n // 2, max(below - 1, 0)], np.int64)
+        got = mgs.prune_select(torch.from_numpy(imp).cuda(), k).cpu().numpy()
+        np.testing.assert_array_equal(got, orc.prune_select(imp, k))
