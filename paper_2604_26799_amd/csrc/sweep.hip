@@ -1445,7 +1445,9 @@ bool shape_valid(const Shape& sh, int G) { return find_variant(sh.nt, sh.ept, G)
 // / 122, b = 2..8, G = 500 (40,000) 735 / 714; 1e6 x 1, b = 2..16, G = 2048
 // (63,000) 147 / 118.  From there on the two are level or the persistent grid is
 // ahead: 100,000 x 11, b = 2..16, G = 200 (71,000) 343 / 352 us, 100,000 x 20, G
-// = 100 (690,000) 1.11 / 1.20 ms.
+// = 100 (690,000) 1.11 / 1.20 ms.  Tiles of 1024 threads, one per CU, stay
+// persistent whatever they hold: 1e6 x 11, 8 ratios, b = 8, G = 12000 170 / 181
+// us, G = 16384 136 / 136.
 constexpr int64_t kShortTile = 65536;
 Shape default_shape(const SceneDesc& sc, int64_t pairs, int channels) {
     const int G = sc.G;
@@ -1472,7 +1474,7 @@ Shape default_shape(const SceneDesc& sc, int64_t pairs, int channels) {
         sh.persist = sh.cpb > 1;
     }
     const int64_t work = (int64_t)G * sc.nb + sc.hist_bins / 4;
-    if (work * (sh.cpb ? sh.cpb : channels) < kShortTile) sh.persist = 0;
+    if (sh.nt < 1024 && work * (sh.cpb ? sh.cpb : channels) < kShortTile) sh.persist = 0;
     return sh;
 }
 
