@@ -312,7 +312,9 @@ int mgs_vq_retain(const float* d_x, int64_t N, int32_t D, const int32_t* d_top, 
  * weight w1, value a1; the other: w2, a2):
  *   L = (sqrt(w1) a1 + sqrt(w2) a2) / sqrt(w1 + w2)   (weight w1 + w2, goes up)
  *   H = (sqrt(w1) a2 - sqrt(w2) a1) / sqrt(w1 + w2)   (AC coefficient)
- * in FP64, in that order of operations.  mgs_raht_forward reads d_attr[C][ld]
+ * in FP64, in that order of operations; a quotient is within half a unit in
+ * the last place plus 2^-104 of its exact value, so it may differ from the
+ * division's in its last bit.  mgs_raht_forward reads d_attr[C][ld]
  * (attributes in the order of the codes) and writes d_coef[C][ld]: column 0
  * the DC (the root's value), columns 1 .. N-1 the AC coefficients in the
  * order they are made (step by step; within a step by Morton code), FP32.

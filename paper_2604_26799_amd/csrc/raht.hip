@@ -14,8 +14,9 @@
 // A merged node keeps the slot of its first leaf.  Output per channel:
 // coefficient 0 = DC (the root's value), then the AC coefficients in the
 // order they are made (step by step, within a step in Morton order).  FP64
-// arithmetic in exactly the order above, FP32 storage.  The inverse undoes
-// the merges in reverse:  a1 = (sqrt(w1) L - sqrt(w2) H) / sqrt(w1 + w2),
+// arithmetic in the order above, FP32 storage; a quotient is within half a unit in
+// the last place plus 2^-104 of its exact value (see quotients()).  The inverse
+// undoes the merges in reverse:  a1 = (sqrt(w1) L - sqrt(w2) H) / sqrt(w1 + w2),
 //                         a2 = (sqrt(w2) L + sqrt(w1) H) / sqrt(w1 + w2).
 //
 // The merge structure follows from the codes alone: every merge joins the
@@ -28,12 +29,12 @@
 // in (step, boundary) order: counts per (step, block of leaves), a scan over
 // them, and the rank within the block by wavefront ballots.
 //
-// Most merges are local: a run of 256 neighbouring leaves contains all but a
-// dozen of its merges whole, so the steps are not run one after the other over
+// Most merges are local: a run of 256 neighbouring leaves contains all but
+// about eight of its merges whole, so the steps are not run one after the other over
 // all nodes.  One wavefront takes a tile of 256 leaves, does every merge whose
 // run [L, R] lies inside the tile, in step order, on values in LDS, and hands
 // on the nodes that are left: the maximal subtrees of a contiguous run of
-// leaves, at most two per step (6 depth), about 13 of 256 in a scene.  The
+// leaves, at most two per step (6 depth), about eight of 256 in a scene.  The
 // next level joins 16 such lists in the same way, and so on: five levels reach
 // the root of 8 million leaves.  The inverse builds the lists bottom-up without
 // values and undoes the merges level by level from the root.
@@ -67,7 +68,7 @@ constexpr int RH_THREADS = RH_WAVES * MGS_WAVE;
 constexpr int RH_SPAN = RH_TILE * RH_WAVES;          // leaves per block of the counts
 constexpr int RH_MAX_SPANS = 4096;                   // N - 1 <= RH_SPAN * RH_MAX_SPANS
 constexpr int RH_MAX_BLOCKS = RH_MAX_SPANS + 1;       // blocks of RH_SPAN leaves
-constexpr int RH_CH = 4;                             // channels in LDS at a time (77 KB per block: two per CU)
+constexpr int RH_CH = 4;                             // channels in LDS at a time (78.5 KB per block: two per CU)
 constexpr int RH_UCH = 4;                            // the same at the upper levels
 constexpr int RH_VS = RH_TILE + 1;                   // row stride of the values (channels in different banks)
 constexpr int RH_GROUP = 16;                         // lists that an upper level joins
@@ -103,7 +104,7 @@ struct RahtArgs {
     uint32_t* bad;         // [nblk] codes of the block out of order or range
     // scratch of a group whose lists hold more than RH_TILE nodes, per node of the level below
     uint64_t* big_code;
-    int32_t* big_i;        // [6][big_stride]
+    int32_t* big_i;        // [RH_BIG_ARRAYS][big_stride]
     int64_t big_stride;
     mgs_status_block* status;
     int32_t nblk;          // blocks of RH_SPAN leaves
@@ -261,9 +262,10 @@ __device__ __forceinline__ double2 reciprocal(double s) {
 }
 
 // n1 / s and n2 / s, s = sqrt(w1 + w2).  n yh + n yl is within 2^-104 of the
-// quotient before its one rounding: the division's result (a last bit could
-// differ where the quotient lies that close to the middle of two doubles, one in
-// 2^50), in two operations instead of its dozen, zeros with their sign included
+// quotient before its one rounding: the division's result but where the quotient
+// lies that close to the middle of two doubles, and then one of the two next to it
+// (of the weights up to 256, 23 have such numerators, one or two in 2^52 each), in
+// two operations instead of its dozen, zeros with their sign included
 // (both terms have n's).  Infinities, whose products with a yl of 0 are none,
 // and what they could come from take the division (the roots give the weights).
 // With two corrections by the FMA remainder (Markstein) in place of yl, five

@@ -163,8 +163,8 @@ __device__ __forceinline__ uint32_t lds_add(uint32_t addr, uint32_t v) {
 // REPL: 2^rl copies of every bin, bin q of lane l in word (q << rl) | cpy with
 // cpy = l mod 2^rl, so lanes that share a bin hit different LDS banks.
 // WIN: only the words at byte addresses [wlo, wlo + wbytes) live in LDS this
-// pass; elements past the ragged end carry w = 0 and x = 0, so they add
-// nothing to the loss.
+// pass; elements past the ragged end carry w = 0 and repeat the last value, so
+// they add nothing to the loss.
 // Returns the OR of the counters the pass read (RTN) in `seen`.
 template <int NT, int EPT, int SUB, bool PACKED, bool CHECK, bool RTN, bool REPL, bool WIN, bool ERR>
 __device__ __forceinline__ Part<SUB> eval_fast(const float (&u)[EPT], const float (&xv)[EPT],
@@ -402,19 +402,21 @@ __device__ __forceinline__ float max3_raw(float a, float b, float c) {
 template <int NT, int EPT, bool CHUNKED>
 constexpr int sweep_min_waves() { return (EPT <= 16 && !CHUNKED) ? 4 : 1; }
 
-// What bounds it: VALU issue (three quarters of the kernel with 17.9 lane
-// slots per evaluation, 9 of them the pass itself on scanned histograms; the
-// rest is each channel's gather, minimum / maximum and quotients, and each
-// wavefront's reductions per bit-width).  So the work outside the passes is
-// kept short: values are gathered by 32-bit byte offset from a scalar row base,
+// What bounds it: VALU issue (units busy 82 % of the time at 5.3e6 x 20, 32 ratios,
+// G = 16384, b = 1..16; 16.1 lane slots per evaluation executed, 11 on average in
+// the passes -- 9 on scanned histograms, about 11.5 with increments, 16.5 packed --
+// and 5 in each channel's gather, minimum / maximum and quotients and in each
+// wavefront's reductions per bit-width).  So the work outside the passes is kept
+// short: values are gathered by 32-bit byte offset from a scalar row base,
 // elements past a ragged end repeat the last one instead of being masked, one
 // instruction takes two elements' minimum, maximum or NaN check, weights are
 // checked once per tile, wavefront minima go through DPP steps on ordered
 // integers, the bit-widths' parameters sit in the lanes of every wavefront
 // (no barrier and no LDS round trip before the passes), and the loss totals
-// are rescaled only in the table entry.  One-workgroup-per-tile launches, before
-// and after: 5.3e6 x 20, 32 ratios, G = 16384, b = 1..16 16.2 -> 15.2 ms;
-// 1e6 x 20, 16 ratios, b = 2..16, G = 8192 2.69 -> 2.39 ms.
+// are rescaled only in the table entry.  With that 17.9 slots became 16.1 and, in
+// one-workgroup-per-tile launches, 16.2 ms 15.2 at the above and 2.69 ms 2.39 at
+// 1e6 x 20, 16 ratios, b = 2..16, G = 8192; the default shapes take 14.5 and 1.70.
+// The price is registers: 1024 x 16 keeps 60 bytes per thread in scratch (20 before).
 template <int NT, int EPT, bool CHUNKED, int SUB>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sweep_min_waves<NT, EPT, CHUNKED>())))
 void sweep_kernel(SweepParams p) {
@@ -1406,7 +1408,7 @@ bool shape_valid(const Shape& sh, int G) { return find_variant(sh.nt, sh.ept, G)
 // a thread takes up to 16 elements; and two or more workgroups per CU hide each
 // other's barriers, so they stay as narrow as 16 elements allow.  Half-width
 // shapes keep the wide shape's sums, so the choice changes no table.  Measured
-// on 1e6 x 20, 16 ratios: G = 8192, b = 2..16, 512 x 16 1.73 ms against 2.39
+// on 1e6 x 20, 16 ratios: G = 8192, b = 2..16, 512 x 16 1.70 ms against 2.39
 // for 1024 x 8; G = 4096, b = 1..16, 256 x 16 2.22 ms against 3.59 for 512 x 8
 // with the whole LDS.  G <= 1024 leaves out the idle elements of 256 x 8.
 //

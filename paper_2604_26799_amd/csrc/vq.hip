@@ -37,8 +37,8 @@
 //      scored at least that previous minimum, so above the final threshold
 //      (the row minimum only falls), and cannot hold the winner.  Thresholds
 //      only fall, so each mask holds every codeword under the final
-//      threshold.  The row's candidates are then re-scored, one per lane at a time,
-//      with the FP64 definition (same operation order) and the smallest
+//      threshold.  The row's candidates are then re-scored, one per lane at a time
+//      (rows of few values two), with the FP64 definition (same operation order) and the smallest
 //      (distance, index) wins.  Rows with more candidate tiles than slots go
 //      to an exact FP64 full scan.  Padding codewords (up to whole chunks)
 //      score +inf and never become candidates.
