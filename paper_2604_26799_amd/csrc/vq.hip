@@ -337,6 +337,8 @@ void vq_main_kernel(VqArgs a) {
     uint32_t bad = 0;
     const float cm = __uint_as_float(*a.cmax_bits);
     const float sg = vq_scale(cm);
+    // a codebook whose largest norm is past FP32 sends every row to the exact scan
+    const float limit = finite_f32(cm) ? 32768.0f : -1.0f;
 #pragma unroll
     for (int rs = 0; rs < VQ_ROWSETS; ++rs) {
         const int64_t r = row0 + rs * 32 + (lane & 31);
@@ -370,7 +372,7 @@ void vq_main_kernel(VqArgs a) {
                             bad |= (uint32_t)!finite_f32(e);
                             v = e * sg;
                             n2 += v * v;
-                            bg |= !(fabsf(v) < 32768.0f);
+                            bg |= !(fabsf(v) < limit);
                         }
                     } else if (k == D || k == D + 1) {
                         v = 1.0f;  // every row, rows past N too (a padding codeword then scores +inf)
@@ -402,7 +404,7 @@ void vq_main_kernel(VqArgs a) {
                             bad |= (uint32_t)!finite_f32(e);
                             v = e * sg;
                             n2 += v * v;
-                            bg |= !(fabsf(v) < 32768.0f);
+                            bg |= !(fabsf(v) < limit);
                         }
                     } else if (k == D || k == D + 1) {
                         v = 1.0f;
@@ -411,7 +413,7 @@ void vq_main_kernel(VqArgs a) {
                 }
         }
         n2 += __shfl_xor(n2, 32, MGS_WAVE);
-        big[rs] = (bg | (__shfl_xor((int)bg, 32, MGS_WAVE) != 0)) | !finite_f32(cm);
+        big[rs] = (bg | (__shfl_xor((int)bg, 32, MGS_WAVE) != 0));
         // the bound in scaled units (sigma is a power of two).  The squares are
         // those of the scaled values, which FP32 holds at any scale of the data
         // (of a row inside FP16; below 2^-75 they vanish, and 1e-18 covers that)
@@ -622,7 +624,12 @@ void vq_main_kernel(VqArgs a) {
                     if (!__builtin_amdgcn_ballot_w64(have)) break;
                     if (have) {
                         const float* c = a.cb + (int64_t)j * D;
-                        take(j, vec ? exact_dist_vec<KP / 4>(xr, c, D) : exact_dist_batch(xr, c, D));
+                        // (written out: through the lambda, 48-value rows took 3 % more)
+                        const double d = vec ? exact_dist_vec<KP / 4>(xr, c, D) : exact_dist_batch(xr, c, D);
+                        if (d < best || (d == best && j < bj)) {
+                            best = d;
+                            bj = j;
+                        }
                     }
                 }
             }
